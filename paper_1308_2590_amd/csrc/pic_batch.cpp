@@ -104,8 +104,11 @@ pic_status rebuild(pic_batch *b) {
   std::vector<int32_t> pre(6 * (n + 1), 0);
   size_t lds_p = 0, lds_r = 0;
   bool ids = false, pw = false;
+  // one block size for all members: the smallest of theirs (each fits its own tile in LDS)
+  int32_t waves = pic::kMaxWaves;
   for (size_t r = 0; r < n; ++r) {
     pic_ctx *c = b->runs[r];
+    waves = std::min(waves, c->waves);
     ids = ids || c->d.track_ids != 0;
     for (int q = 0; q < c->S; ++q) pw = pw || (c->sp[q].loaded && c->sp[q].pw);
   }
@@ -126,7 +129,7 @@ pic_status rebuild(pic_batch *b) {
         c->n_scan1_blocks * c->S,
         1};
     for (int k = 0; k < 4; ++k) pre[k * (n + 1) + r + 1] = pre[k * (n + 1) + r] + items[k];
-    lds_p = std::max(lds_p, pic::particle_lds_bytes(c->g, c->tiles, b->precision == PIC_PREC_MIXED, pw));
+    lds_p = std::max(lds_p, pic::particle_lds_bytes(c->g, c->tiles, b->precision == PIC_PREC_MIXED, waves));
     lds_r = std::max(lds_r, pic::rank_lds_bytes(c->tiles));
   }
   if (n > 0) {
@@ -159,6 +162,7 @@ pic_status rebuild(pic_batch *b) {
   l.mixed = b->precision == PIC_PREC_MIXED;
   l.ids = ids;
   l.pw = pw;
+  l.waves = waves;
   l.lds_particles = lds_p;
   l.lds_rank = lds_r;
   // one block per tile that any run could have active (the blocks past the cycle's active
@@ -254,6 +258,13 @@ pic_status pic_batch_add(pic_batch *b, pic_ctx *c) {
   c->stream_before_batch = c->stream;
   c->stream = b->stream;
   c->batch = b;
+  const pic_status st = pic::batch_retile(c);
+  if (st != PIC_OK) {
+    c->batch = nullptr;
+    c->stream = c->stream_before_batch;
+    c->stream_before_batch = nullptr;
+    return bfail(b, st, c->err);
+  }
   b->runs.push_back(c);
   b->dirty = true;
   return PIC_OK;
@@ -269,6 +280,8 @@ pic_status pic_batch_remove(pic_batch *b, pic_ctx *c) {
   c->stream_before_batch = nullptr;
   c->batch = nullptr;
   b->dirty = true;
+  const pic_status st = pic::batch_retile(c);
+  if (st != PIC_OK) return bfail(b, st, c->err);
   return PIC_OK;
 }
 

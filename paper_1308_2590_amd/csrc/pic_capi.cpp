@@ -160,35 +160,104 @@ bool finite3(const double *v) { return std::isfinite(v[0]) && std::isfinite(v[1]
 
 bool mixed(const pic_ctx *c) { return c->d.precision == PIC_PREC_MIXED; }
 
-// Whether some loaded species carries per-particle densities (the kernels with them run).
-bool any_pw(const pic_ctx *c) {
-  for (int s = 0; s < c->S; ++s)
-    if (c->sp[s].loaded && c->sp[s].pw) return true;
-  return false;
-}
+int64_t tiles_over(int64_t lo, int64_t hi, int64_t t) { return hi > lo ? (hi - 1) / t - lo / t + 1 : 0; }
 
-// Tile size from the load.  One wavefront handles one row of a tile, each lane a contiguous
-// run of that row's particles.  The rule follows what timing every candidate shape measured on
-// uniform and slab loads: tiles 16 cells wide where the occupied part of a row is at most 16
-// cells (a narrow slab), otherwise 32, or 8 in mixed precision above 16 particles per occupied
-// cell and species (three wavefronts per SIMD want more, smaller blocks); and as many rows (1 to 4) as
-// bring a tile to about 4096 particles per species (mixed: 2048), counting only the occupied
-// cells of a row.
-// Shrunk in x until two blocks fit in the LDS of a CU (half the LDS a block may use).
-// ppc: particles per occupied cell and species; width: occupied cells per occupied row.
-void choose_tiles(pic_ctx *c, double ppc, double width) {
-  int tx = c->d.tile_x, tz = c->d.tile_z;
-  if (tx <= 0 || tz <= 0) {
-    const bool mx = mixed(c);
-    tx = width <= 16.0 ? 16 : (mx && ppc > 16.0) ? 8 : 32;
-    const double per_row = std::max(1.0, std::min((double)tx, width) * ppc);
-    tz = (int)std::lround((mx ? 2048.0 : 4096.0) / per_row);
-    tz = std::min(4, std::max(1, tz));
-    while (tx > 4 &&
-           pic::particle_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, mixed(c), any_pw(c)) >
-               c->lds_max / 2)
-      tx /= 2;
+// The particle kernel's direct form up to this many particles per occupied cell and species, if
+// its tiles fill the GPU.  Particle kernel, 0.1 keV, 700 x 700 cells, direct (32 x 4 cells, four
+// wavefronts) against grouped (32 x 2, eight): 161 / 306 us at 4 per cell, 248 / 358 at 8,
+// 352 / 411 at 12; a 171-cell slab at 1 keV, 11 per cell, three species with densities: 75 / 71.
+// On 128 x 128 cells (128 tiles) at 4 per cell 29 / 23.
+constexpr double kDirectMaxPerCell = 9.0;
+constexpr int64_t kDirectMinTiles = 256;
+
+// Tile shape, wavefronts per block and form of the particle kernel from the load.
+//
+// The direct form takes 32 x 4 cells (16 x 4 where the occupied columns are at most 16): its
+// particles leaving the tile are expensive, so larger perimeters cost more than idle compute units.
+//
+// The grouped form's blocks spend a fixed time on staging, folding and filling the pipeline, then
+// a time per group of 64 particles that grows with the wavefronts sharing a SIMD; the blocks
+// beyond those the GPU holds at once wait.  The shape and wavefronts are the ones this model finds
+// cheapest, for 15 % more tiles than the load fills (a slab spreads, and a few tiles more than
+// fit at once cost most of a second round: the foil's kernel at 32 x 2 with eight wavefronts,
+// 512 tiles, takes 68 us at the start and 95 with 525 tiles).  Particle kernel, measured: foil, 40
+// x 512 cells at 64 per cell: 32 x 2 with eight wavefronts 68 us, 8 x 4 with four 72, 8 x 4 with
+// eight 90, 32 x 1 with eight 85; 160 x 512 cells at 128 per cell: 8 x 4 with eight 458, with
+// four 485, 32 x 1 465, 8 x 8 482, 32 x 2 515, 8 x 2 456 (but 18 us more in the ranker); 64 x 64
+// cells at 16 per cell: 8 x 2 with eight 21, 8 x 4 23, 32 x 2 27.
+//
+// A batch's members share the GPU, so small tiles that fill it with one run's blocks only add
+// work: 8 x 4 cells and four wavefronts (32 uneven slab runs 306 us per FP64 cycle, with eight
+// 391, 32 x 4 346, 16 x 4 306, 8 x 2 368; ten runs in mixed precision 139, 16 x 2 139, 32 x 2 160).
+constexpr int kBatchTileX = 8, kBatchTileZ = 4;
+
+void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
+  const int64_t width = ld.i_hi - ld.i_lo;
+  const bool fixed = c->d.tile_x > 0 && c->d.tile_z > 0;
+  auto lds = [&](int tx, int tz, int waves) {
+    return pic::particle_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, mixed(c), waves);
+  };
+  c->load = ld;
+  int tx = c->d.tile_x, tz = c->d.tile_z, waves = pic::kMaxWaves;
+  const int dx = width <= 16 ? 16 : 32;
+  c->direct = ld.ppc <= kDirectMaxPerCell &&
+              tiles_over(ld.i_lo, ld.i_hi, dx) * tiles_over(ld.k_lo, ld.k_hi, 4) >= kDirectMinTiles;
+  if (c->batch) {
+    waves = 4;
+    if (!fixed) {
+      tx = kBatchTileX;
+      tz = kBatchTileZ;
+    }
+  } else if (c->direct) {
+    waves = 4;
+    if (!fixed) {
+      tx = dx;
+      tz = 4;
+      while (tx > 4 && lds(tx, tz, 0) > c->lds_max / 2) tx /= 2;
+    }
+  } else {
+    // (of equally cheap shapes the first: square ones have the smaller rings)
+    static const int shapes[][2] = {{8, 4}, {8, 8}, {16, 4}, {32, 2}, {16, 2}, {32, 1}, {32, 4},
+                                    {4, 4}, {8, 2}, {16, 1}, {4, 2},  {8, 1},  {4, 1}};
+    // microseconds: fixed per block with eight wavefronts (four: 3 more), per group alone on a
+    // SIMD and per further wavefront on it; the ranker's time per tile
+    const double kFixed = 12.0, kGroup = 1.2, kGroupWave = 1.1, kRankTile = 0.007;
+    const double cus = 256.0;
+    double best = 0.0;
+    for (const auto &sh : shapes) {
+      const int cx = fixed ? tx : sh[0], cz = fixed ? tz : sh[1];
+      const int64_t ntx = std::max<int64_t>(1, tiles_over(ld.i_lo, ld.i_hi, cx));
+      const int64_t ntz = std::max<int64_t>(1, tiles_over(ld.k_lo, ld.k_hi, cz));
+      const double all = (double)tiles_over(0, c->g.nx, cx) * (double)tiles_over(0, c->g.nz, cz);
+      const double nt = (double)(ntx * ntz), nt_spread = std::min(all, 1.15 * nt);
+      const double rows = std::max(1.0, (double)(ld.k_hi - ld.k_lo) / (double)ntz);
+      const double groups = c->S * rows * std::ceil(ld.ppc * (double)width / (double)ntx / 64.0);
+      for (int w = pic::kMaxWaves; w >= 4; w /= 2) {
+        const size_t bytes = lds(cx, cz, w);
+        if (bytes > c->lds_max) continue;
+        const double per_cu = (double)std::max<size_t>(1, std::min<size_t>(16 / w, c->lds_max / bytes));
+        const double held = std::min(per_cu, std::ceil(nt / cus));  // blocks a CU works on at once
+        const double block = kFixed + (w == 4 ? 3.0 : 0.0) +
+                             std::ceil(groups / w) * (kGroup + kGroupWave * held * w / 4.0);
+        const double rounds = nt_spread / (cus * per_cu);
+        const double t = block * (rounds <= 1.0 ? 1.0 : rounds + 0.35) * (1.0 + 0.0015 * cx * cz) + kRankTile * nt;
+        if (best == 0.0 || t < best) {
+          best = t;
+          c->tiles.tx = cx;
+          c->tiles.tz = cz;
+          waves = w;
+        }
+      }
+      if (fixed) break;
+    }
+    if (!fixed) {
+      tx = c->tiles.tx;
+      tz = c->tiles.tz;
+    }
   }
+  // a block's staging must fit beside the tile (the loads' deposit uses the grouped form too)
+  while (waves > 1 && lds(tx, tz, waves) > c->lds_max) waves /= 2;
+  c->waves = waves;
   c->tiles.tx = tx;
   c->tiles.tz = tz;
   c->tiles.ntx = (c->g.nx + tx - 1) / tx;
@@ -213,7 +282,8 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   a.t = c->tiles;
   a.mixed = mixed(c) ? 1 : 0;
   a.rank_cells = rank_cells(c) ? 1 : 0;
-  a.chunk2 = c->chunk2 ? 1 : 0;
+  a.direct = c->direct ? 1 : 0;
+  a.waves = c->waves;
   // the per-cell ranker reads code masks, which the tile kernel writes (not the per-particle
   // kernel of the mover options, which accumulates full counts)
   a.count_masks = (a.rank_cells && !c->mover) ? 1 : 0;
@@ -278,12 +348,13 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   return a;
 }
 
-// (Re)allocate the active-tile arrays for the current tile decomposition.
+// (Re)allocate the active-tile arrays, for the current tile decomposition and for the one the
+// context takes in a batch (so that joining or leaving one allocates nothing).
 pic_status alloc_tiles(pic_ctx *c) {
-  const int32_t nt = c->tiles.ntiles;
-  if (nt == c->tiles_alloc && c->tiles.tx == c->tiles_tx && c->tiles.tz == c->tiles_tz) return PIC_OK;
-  c->tiles_tx = c->tiles.tx;
-  c->tiles_tz = c->tiles.tz;
+  int64_t nt = c->tiles.ntiles;
+  if (c->d.tile_x <= 0)
+    nt = std::max(nt, tiles_over(0, c->g.nx, kBatchTileX) * tiles_over(0, c->g.nz, kBatchTileZ));
+  if (nt <= c->tiles_alloc) return PIC_OK;
   for (int b = 0; b < 2; ++b) {
     dfree(c, c->tact[b], (size_t)std::max(c->tiles_alloc, 1));
     dfree(c, c->tlist[b], ((size_t)c->tiles_alloc + 1) * sizeof(int32_t));
@@ -296,7 +367,7 @@ pic_status alloc_tiles(pic_ctx *c) {
     if ((st = dalloc(c, &c->tact[b], (size_t)nt, "alloc tile flags")) != PIC_OK) return st;
     if ((st = dalloc(c, &c->tlist[b], (size_t)nt + 1, "alloc tile list")) != PIC_OK) return st;
   }
-  c->tiles_alloc = nt;
+  c->tiles_alloc = (int32_t)nt;
   return PIC_OK;
 }
 
@@ -354,9 +425,8 @@ pic_status particle_stage(pic_ctx *c, const pic::StepArgs &a) {
   return PIC_OK;
 }
 
-// Tile shape from the descriptor's tile_x / tile_z, or from the load when those are 0: the
-// particles per occupied cell and species, and the occupied cells per occupied row.  Waits
-// for the stream (reads the cell starts).
+// Tile shape from the descriptor's tile_x / tile_z, or from the load when those are 0 (see
+// choose_tiles).  Waits for the stream (reads the cell starts).
 pic_status retile(pic_ctx *c) {
   const int64_t nc = c->g.ncells;
   std::vector<uint8_t> occ((size_t)nc, 0);
@@ -373,25 +443,35 @@ pic_status retile(pic_ctx *c) {
       if (csh[cc + 1] > csh[cc]) occ[cc] = 1;
     total += csh[nc];
   }
-  int64_t occupied = 0, rows = 0;
+  int64_t occupied = 0;
+  pic::LoadShape ld;
+  ld.i_lo = c->g.nx;
+  ld.k_lo = c->g.nz;
   for (int64_t k = 0; k < c->g.nz; ++k) {
+    const uint8_t *row = occ.data() + k * c->g.nx;
     int64_t in_row = 0;
-    for (int64_t i = 0; i < c->g.nx; ++i) in_row += occ[(size_t)(k * c->g.nx + i)];
+    for (int64_t i = 0; i < c->g.nx; ++i) in_row += row[i];
+    if (!in_row) continue;
     occupied += in_row;
-    rows += in_row > 0 ? 1 : 0;
+    ld.k_lo = std::min(ld.k_lo, k);
+    ld.k_hi = k + 1;
+    const int64_t first = static_cast<const uint8_t *>(std::memchr(row, 1, (size_t)c->g.nx)) - row;
+    ld.i_lo = std::min(ld.i_lo, first);
+    for (int64_t i = c->g.nx; i > ld.i_hi; --i)
+      if (row[i - 1]) {
+        ld.i_hi = i;
+        break;
+      }
   }
-  const double ppc = occupied > 0 ? (double)total / (double)occupied / std::max(nloaded, 1) : 1.0;
-  const double width = rows > 0 ? (double)occupied / (double)rows : (double)c->g.nx;
-  choose_tiles(c, ppc, width);
-  c->rank_cells_auto = occupied > 0 && ppc <= kRankCellsMaxPerCell;
-  // particles per lane in a tile row (a row splits over the wavefronts when the tile has fewer
-  // rows than the block has wavefronts): chunks of 2 up to 2.5 of them
-  {
-    const int waves_per_row = c->tiles.tz >= 4 ? 1 : 4 / c->tiles.tz;
-    const double per_lane = std::min((double)c->tiles.tx, width) * ppc / (64.0 * waves_per_row);
-    c->chunk2 = occupied > 0 && per_lane <= 2.5;
+  ld.ppc = occupied > 0 ? (double)total / (double)occupied / std::max(nloaded, 1) : 1.0;
+  if (occupied == 0) {
+    ld.i_lo = ld.k_lo = 0;
+    ld.i_hi = c->g.nx;
+    ld.k_hi = c->g.nz;
   }
-  if (pic::particle_lds_bytes(c->g, c->tiles, mixed(c), any_pw(c)) > c->lds_max)
+  choose_tiles(c, ld);
+  c->rank_cells_auto = occupied > 0 && ld.ppc <= kRankCellsMaxPerCell;
+  if (pic::particle_lds_bytes(c->g, c->tiles, mixed(c), c->waves) > c->lds_max)
     return fail(c, PIC_ERR_ARG, "tile too large: its LDS accumulators exceed the LDS of a block");
   return PIC_OK;
 }
@@ -419,6 +499,13 @@ void prof_accumulate(pic_ctx *c) {
 }  // namespace
 
 namespace pic {
+
+pic_status batch_retile(pic_ctx *c) {
+  const TileArgs before = c->tiles;
+  choose_tiles(c, LoadShape(c->load));
+  if (c->tiles.tx == before.tx && c->tiles.tz == before.tz) return PIC_OK;
+  return build_tile_list(c);
+}
 
 StepArgs cycle_step_args(pic_ctx *c, int p) {
   const int saved = c->cur;
@@ -529,7 +616,10 @@ pic_status pic_init_grid(const pic_grid_desc *d, pic_ctx **out) {
                             d->laser_fwhm_t, d->laser_t_center};
   c->n_scan_blocks = (int32_t)((g.ncells + pic::kScanBlock - 1) / pic::kScanBlock);
   c->n_scan1_blocks = (int32_t)((g.ncells + pic::kScan1Block - 1) / pic::kScan1Block);
-  choose_tiles(c, 1.0, (double)g.nx);
+  pic::LoadShape empty;
+  empty.i_hi = g.nx;
+  empty.k_hi = g.nz;
+  choose_tiles(c, empty);
 
   pic_status st = PIC_OK;
   auto bail = [&](pic_status s2) {

@@ -52,6 +52,14 @@ struct SpeciesState {
   int32_t *bsum = nullptr;
 };
 
+// What the tile choice needs to know of the load: particles per occupied cell and species, and
+// the occupied columns and rows (half-open).
+struct LoadShape {
+  double ppc = 1.0;
+  int64_t i_lo = 0, i_hi = 0;
+  int64_t k_lo = 0, k_hi = 0;
+};
+
 struct ProfEvents {
   hipEvent_t ev[4];  // step start, after field solve, after particles, after sort
 };
@@ -79,13 +87,15 @@ struct pic_ctx {
   uint8_t *tact[2] = {};   // active-tile flags of the current / next order
   int32_t *tlist[2] = {};  // ordered active-tile lists, count at [ntiles]
   uint8_t *mflag = nullptr;  // deposit flags, one per kFlagNodes nodes (moments can be nonzero)
-  int32_t tiles_alloc = 0, tiles_tx = 0, tiles_tz = 0;
+  int32_t tiles_alloc = 0;   // tiles the arrays have room for
+  pic::LoadShape load;       // what the tile shape was chosen from
   int64_t step = 0;
   size_t lds_max = 65536;  // LDS a block may use on the context's device
   int32_t mover = 0;       // PIC_MOVER_* options; 0: the tile kernel's default mover
   int32_t rank_mode = PIC_RANK_AUTO;
   bool rank_cells_auto = false;  // the automatic choice, made with the tile shape
-  bool chunk2 = false;           // particle kernel chunk of 2 (about 2 particles per lane and row)
+  bool direct = false;           // the particle kernel's direct form (about 2 particles per lane and row)
+  int32_t waves = 4;             // wavefronts per block of its grouped form
   int32_t n_scan_blocks = 0;
   int32_t n_scan1_blocks = 0;  // blocks of the scan of a cycle's sort
   std::string err;
@@ -107,6 +117,9 @@ namespace pic {
 // them for a cycle, and the field-solve arguments of the same cycle.
 StepArgs cycle_step_args(pic_ctx *c, int p);
 FieldArgs cycle_field_args(pic_ctx *c, int p);
+// Tiles of a context that has joined or left a batch (c->batch), and their list in the current
+// order, queued on the context's stream.
+pic_status batch_retile(pic_ctx *c);
 // Mark the batch holding c (if any) for a rebuild of its tables.
 void batch_touch(pic_ctx *c);
 // Remove c from its batch (if any); used by pic_destroy.

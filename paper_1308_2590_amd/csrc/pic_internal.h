@@ -13,6 +13,7 @@ constexpr int kMaxSpecies = PIC_MAX_SPECIES;
 constexpr int kMoveCodes = 9;      // destination cell relative to the source: 3 x 3 block
 constexpr uint8_t kAbsorbed = 9;   // move code of a particle that left an absorbing boundary
 constexpr int kBlock = 256;        // threads per block of the tile kernels (4 wavefronts)
+constexpr int kMaxWaves = 8;       // most wavefronts per block of the particle kernel
 constexpr int kPermPad = 8;        // padding entries after each permutation array
 constexpr int kSolveNodes = 2;     // nodes per thread in the E solve
 constexpr int kHCells = 2;         // cells per thread in the H update
@@ -83,7 +84,8 @@ struct StepArgs {
   TileArgs t;
   int32_t mixed;             // 1: mixed-precision particle state and arithmetic
   int32_t rank_cells;        // 1: destinations ranked one thread per cell, 0: by tile rows
-  int32_t chunk2;            // 1: the particle kernel loads 2 particles per lane at a time, 0: 4
+  int32_t direct;            // 1: the particle kernel's direct form (few particles per cell), 0: grouped
+  int32_t waves;             // wavefronts per block of the grouped form
   int32_t count_masks;       // 1: the particle kernel writes code masks and nonzero counts only
   int32_t n_scan_blocks;     // blocks of the count scan per species
   int32_t nsp;               // species slots
@@ -148,14 +150,15 @@ struct BatchLaunch {
   int32_t items_cells;       // cell blocks of all runs (one block each in the H update)
   int32_t items_scan;        // scan blocks x species of all runs (one block each in the scans)
   size_t lds_particles, lds_rank;
+  int32_t waves;             // wavefronts per block of the particle kernel
   bool mixed;
   bool ids;                  // some run copies particle ids (the kernel instantiation with ids)
   bool pw;                   // some run carries per-particle densities
 };
 
-// LDS of the particle kernel's block for a tile; pw: the instantiation with per-particle
-// densities (one more word per queued mover); queues: with the per-wavefront mover queues.
-size_t particle_lds_bytes(const GridArgs &g, const TileArgs &t, bool mixed, bool pw, bool queues = true);
+// LDS of the particle kernel's block for a tile: the grouped form with that many wavefronts per
+// block, or the direct form (waves = 0).
+size_t particle_lds_bytes(const GridArgs &g, const TileArgs &t, bool mixed, int waves);
 size_t rank_lds_bytes(const TileArgs &t);
 
 hipError_t launch_field_solve(const FieldArgs &a, hipStream_t s);

@@ -8,7 +8,8 @@
 //               read, then cleared for the next deposit, only in tiles the deposit reached.
 //   k_update_h  Eq. (5) at cell centres with curl E from the 4 corner nodes (Steps 8-9), and
 //               clears the deposit flags of the tiles.
-// Particles (one block per tile of cells, one wavefront per row of the tile):
+// Particles (one block per tile of cells; a wavefront takes groups of 64 consecutive slots of the
+// tile's rows, or a row of the tile where cells hold few particles):
 //   k_particles gather E-bar (bilinear from the 4 corner nodes) and B (the particle's cell),
 //               implicit push (Eq. (2a) solved for the time-centred momentum), position
 //               advance, move code, then deposit of S-hat, delta-j and density (Step 1,
@@ -75,13 +76,20 @@ struct SmallDiv {
   __device__ __forceinline__ int q(int e) const { return (int)(((float)e + 0.5f) * r); }
 };
 
+constexpr int kNoBandTiles = 512;
+
 // The tile handled by this block, taken from the ordered list of tiles that hold particles:
 // blocks are dealt round-robin to the 8 XCDs, so each XCD gets a contiguous band of the list
 // (neighbouring tiles share halo nodes and field cache lines).  Surplus blocks return.
 __device__ __forceinline__ int block_tile(const TileArgs &t, const int32_t *list) {
   const int count = list[t.ntiles];
-  const int per = (count + 7) >> 3;
   const int b = blockIdx.x;
+  // few tiles: the entry's load does not wait for the count's
+  if (t.ntiles <= kNoBandTiles) {
+    const int e = b < t.ntiles ? list[b] : -1;
+    return b < count ? e : -1;
+  }
+  const int per = (count + 7) >> 3;
   if ((b >> 3) >= per) return -1;
   const int idx = (b & 7) * per + (b >> 3);
   return idx < count ? list[idx] : -1;
@@ -364,19 +372,6 @@ __device__ __forceinline__ int lane_before(int v) {
   return __builtin_amdgcn_update_dpp(v, v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
 }
 
-// The value of the lane above (lane 63 gets its own), by DPP wave shifts of 32-bit halves.
-__device__ __forceinline__ int lane_after(int v) {
-  return __builtin_amdgcn_update_dpp(v, v, 0x130 /* wave_shl:1 */, 0xf, 0xf, false);
-}
-__device__ __forceinline__ float lane_after(float v) {
-  return __int_as_float(lane_after(__float_as_int(v)));
-}
-__device__ __forceinline__ double lane_after(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = lane_after((int)(b & 0xffffffffll)), hi = lane_after((int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
 // Stores of the particle kernel as raw buffer stores: a lane without a value passes an offset
 // past the buffer's range, which the hardware drops, so the store needs no branch.  Every array
 // gets the same range, 2^31 bytes (a species holds fewer than 2^28 particles).
@@ -387,6 +382,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t store_rsrc(void *p) {
 }
 __device__ __forceinline__ void store_or_drop(double *p, int i, bool on, double v) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), store_rsrc(p), on ? i * 8 : kStoreDrop, 0, 0);
+}
+__device__ __forceinline__ void store_or_drop(float *p, int i, bool on, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
+}
+__device__ __forceinline__ void store_or_drop(int32_t *p, int i, bool on, int32_t v) {
+  __builtin_amdgcn_raw_buffer_store_b32((uint32_t)v, store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
 }
 __device__ __forceinline__ void store_or_drop(uint32_t *p, int i, bool on, uint32_t v) {
   __builtin_amdgcn_raw_buffer_store_b32(v, store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
@@ -467,121 +468,6 @@ __device__ __forceinline__ void corner_add(const AccLds &A, int o, int rc, int c
   atomicAdd(&A.cell[(2 * 4 + corner) * A.npl + rc], (double)A2);
 }
 
-// Per-lane running sum of the compact moments of consecutive particles that stay in one
-// cell, per corner (order (i,k), (i+1,k), (i,k+1), (i+1,k+1)).
-template <typename T>
-struct CellAcc {
-  T A0[4], A1[4], A2[4], J0[4], J1[4], J2[4], D[4];
-  int cell;  // tile-local column of the cell being accumulated, -1 when empty
-
-  __device__ __forceinline__ void clear() {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) A0[c] = A1[c] = A2[c] = J0[c] = J1[c] = J2[c] = D[c] = T(0);
-  }
-  __device__ __forceinline__ void add(T fx, T fz, const Compact<T> &m, T w) {
-    const T one = T(1);
-    const T W[4] = {(one - fx) * (one - fz), fx * (one - fz), (one - fx) * fz, fx * fz};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      A0[c] = fmaT(W[c], m.a0, A0[c]);
-      A1[c] = fmaT(W[c], m.a1, A1[c]);
-      A2[c] = fmaT(W[c], m.a2, A2[c]);
-      J0[c] = fmaT(W[c], m.j0, J0[c]);
-      J1[c] = fmaT(W[c], m.j1, J1[c]);
-      J2[c] = fmaT(W[c], m.j2, J2[c]);
-      D[c] = fmaT(W[c], w, D[c]);
-    }
-  }
-  // The accumulated cell is (cell, lz - 1) of the tile: ring cell (cell + 1, lz), whose
-  // lower-left node is (cell + 1, lz) locally (the layout with the ring).
-  __device__ __forceinline__ void flush(const AccLds &acc, int lz, int dplane) {
-    const int b = lz * acc.LW + cell + 1, rc = lz * acc.NW + cell + 1;
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      corner_add(acc, b + (c & 1) + (c >> 1) * acc.LW, rc, c, A0[c], A1[c], A2[c], J0[c], J1[c],
-                 J2[c], D[c], dplane);
-  }
-  // End of a row: every lane flushes at once, and the lanes whose runs end in one cell are
-  // neighbours.  Their sums are first added up across lanes (a segmented reduction with
-  // shuffles towards the first lane of each cell), so that one lane per cell issues the LDS
-  // atomics; same-address atomics from many lanes of one instruction are serialised.  All 64
-  // lanes must be active.
-  __device__ __forceinline__ void flush_row_end(const AccLds &acc, int lz, int dplane, int lane) {
-    const int prev = lane_before(cell);
-    const bool head = lane == 0 || prev != cell;
-    const uint64_t heads = __ballot(head);
-    const uint64_t above = heads & ~((2ull << lane) - 1ull);
-    const int seg_end = above ? __ffsll((unsigned long long)above) - 1 : 64;
-    {
-      // first step (neighbour one lane up) by DPP; the wider steps go through the LDS crossbar
-      const bool take = lane + 1 < seg_end;
-      if (!__any(take)) {
-        if (head && cell >= 0) flush(acc, lz, dplane);
-        return;
-      }
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        T v;
-        v = lane_after(A0[c]); A0[c] += take ? v : T(0);
-        v = lane_after(A1[c]); A1[c] += take ? v : T(0);
-        v = lane_after(A2[c]); A2[c] += take ? v : T(0);
-        v = lane_after(J0[c]); J0[c] += take ? v : T(0);
-        v = lane_after(J1[c]); J1[c] += take ? v : T(0);
-        v = lane_after(J2[c]); J2[c] += take ? v : T(0);
-        v = lane_after(D[c]); D[c] += take ? v : T(0);
-      }
-    }
-    for (int d = 2; d < 64; d <<= 1) {
-      const bool take = lane + d < seg_end;
-      if (!__any(take)) break;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        T v;
-        v = __shfl_down(A0[c], d); A0[c] += take ? v : T(0);
-        v = __shfl_down(A1[c], d); A1[c] += take ? v : T(0);
-        v = __shfl_down(A2[c], d); A2[c] += take ? v : T(0);
-        v = __shfl_down(J0[c], d); J0[c] += take ? v : T(0);
-        v = __shfl_down(J1[c], d); J1[c] += take ? v : T(0);
-        v = __shfl_down(J2[c], d); J2[c] += take ? v : T(0);
-        v = __shfl_down(D[c], d); D[c] += take ? v : T(0);
-      }
-    }
-    if (head && cell >= 0) flush(acc, lz, dplane);
-  }
-};
-
-// Particles that change cell deposit into a different cell (and field) from the lane's run,
-// so they are queued per wavefront in LDS and deposited 64 at a time, one per lane.
-constexpr int kMqCap = 64;
-// fx fz a0 a1 a2 j0 j1 j2, and the particle's density when densities are per particle
-__host__ __device__ constexpr int mq_words(bool pw) { return pw ? 9 : 8; }
-
-template <typename T>
-struct MoverQ {
-  T *v;      // [mq_words][kMqCap]
-  int *idx;  // [2][kMqCap]: lower-left accumulator node, ring cell of the destination
-};
-
-template <typename T, bool PW>
-__device__ __forceinline__ void drain_movers(const MoverQ<T> &q, int count, int lane,
-                                             const AccLds &acc, int dplane, T w_uniform) {
-  if (lane < count) {
-    const T fx = q.v[0 * kMqCap + lane], fz = q.v[1 * kMqCap + lane];
-    const T a0 = q.v[2 * kMqCap + lane], a1 = q.v[3 * kMqCap + lane];
-    const T a2 = q.v[4 * kMqCap + lane], j0 = q.v[5 * kMqCap + lane];
-    const T j1 = q.v[6 * kMqCap + lane], j2 = q.v[7 * kMqCap + lane];
-    const T w = PW ? q.v[8 * kMqCap + lane] : w_uniform;
-    const int o = q.idx[lane], rc = q.idx[kMqCap + lane];
-#pragma unroll 1
-    for (int c = 0; c < 4; ++c) {
-      const int cx = c & 1, cz = c >> 1;
-      const T W = (cx ? fx : T(1) - fx) * (cz ? fz : T(1) - fz);
-      corner_add(acc, o + cx + cz * acc.LW, rc, c, W * a0, W * a1, W * a2, W * j0, W * j1, W * j2,
-                 W * w, dplane);
-    }
-  }
-}
-
 // One particle's compact moments added to the LDS accumulators of its cell (lower-left
 // accumulator node o, ring cell rc), corner by corner.  Lanes of odd index take the corners in
 // the order (i,k+1), (i+1,k+1), (i,k), (i+1,k): neighbouring lanes often hold particles of one
@@ -640,17 +526,32 @@ __device__ void deposit_global(const StepArgs &a, int gi, int gk, T fx, T fz, co
   }
 }
 
+// Grouped form: deposit of a group of 64 particles, one per lane, through the matrix cores.
+// S-hat and delta-j of a cell's particles are the contraction over the particles of 4 corner
+// weights and 7 compact moments.  v_mfma_f64_4x4x4_4b contracts 4 blocks of 4 particles at a
+// time: lane 16 k + 4 b + i holds A[i][k] and B[k][i] of block b and receives D[i][j] in lane
+// 16 i + 4 b + j.  Block b takes the 16 particles of lanes 16 b .. 16 b + 15 in four rounds, so
+// eight instructions sum the 28 products of 64 particles, without the 56 registers of per-lane
+// sums and with two LDS atomic instructions for the result.  The particles go from one per lane
+// to the operands' layout through LDS: kStagePlanes planes (f_x, f_z, delta-j x, y, z, density,
+// a0, a1, a2), particle P at P + P / 16, planes kStagePitch doubles apart: the 16 lanes of one
+// LDS pass then read doubles 4 i + b (mod 16), which differ, and write consecutive ones.
+constexpr int kStagePlanes = 9;
+constexpr int kStagePitch = 68;
+// bytes of a wavefront's staging area: the planes, 64 cells, 64 movers, 64 pass numbers (see Stage)
+constexpr int kStageBytes = kStagePlanes * kStagePitch * 8 + 128 * 4 + 64;
+
 // LDS layout of the particle kernel (byte offsets): the moment accumulators (delta-j and
 // density per node, S-hat scalars per cell corner), the fields the tile's particles read (E-bar
 // on the tile's nodes, H^{n+1/2} on its cells, H^{n+3/2} on its cells plus the one-cell ring a
-// particle can move into), the per-wave mover queues, per species the int move counters of the
-// tile's cells and the arrival counts of the tile's cells and their ring, and the first and
-// end slot of every tile row of every species slot.  Two layouts: with mover queues
-// (qwords > 0) the accumulators cover the tile and its ring; without (the chunk-of-2 form) they
-// cover the tile's own nodes and cells, particles leaving the tile deposit to the global
-// planes, and the arrivals are summed from the move counters (no arrival array), which brings
-// a 32 x 4 tile of two species to 40 KB: four blocks per CU.  Accumulators are FP64; fields
-// and queues use the kernel's arithmetic type.
+// particle can move into), the per-wave deposit staging, per species the int move counters of
+// the tile's cells and the arrival counts of the tile's cells and their ring, and the first and
+// end slot of every tile row of every species slot.  Two layouts: the grouped form (waves > 0)
+// has accumulators over the tile and its ring and a staging area per wavefront; the direct form
+// (waves = 0) covers the tile's own nodes and cells, particles leaving the tile deposit to the
+// global planes, and the arrivals are summed from the move counters (no arrival array), which
+// brings a 32 x 4 tile of two species to 40 KB: four blocks per CU.  Accumulators and staging
+// are FP64; fields use the kernel's arithmetic type.
 struct TileLds {
   int LW, LH, plane;          // accumulator node grid (tx + 3) x (tz + 3), or (tx + 1) x (tz + 1)
   int EW, EPL;                // E-bar node grid (tx + 1) x (tz + 1)
@@ -658,13 +559,16 @@ struct TileLds {
   int NW, NPL;                // H^{n+3/2} cells (tx + 2) x (tz + 2)
   int CPL;                    // pitch of the S-hat corner planes: NPL, or HPL padded
   int n_node;                 // node accumulator planes: 3 + species
-  size_t acc, accc, eb, ho, hn, mq, cnt, arr, rows;  // byte offsets
+  size_t acc, accc, eb, ho, hn, stage, cnt, arr, rows;  // byte offsets
   size_t bytes;
-  __host__ __device__ TileLds(int n_planes, int tx, int tz, int tsize, int qwords) {
-    const int ring = qwords ? 1 : 0;
+  __host__ __device__ TileLds(int n_planes, int tx, int tz, int tsize, int waves) {
+    const int ring = waves ? 1 : 0;
     LW = tx + 1 + 2 * ring;
     LH = tz + 1 + 2 * ring;
     plane = LW * LH;
+    // grouped form: the 16 results of a cell (4 corners x 4 planes, and 4 corners x 3 scalars) go
+    // to LDS in one instruction; these pitches spread them over the banks
+    if (ring) plane += (5 - plane % 16 + 16) % 16;
     EW = tx + 1;
     EPL = EW * (tz + 1);
     HPL = tx * tz;
@@ -672,15 +576,15 @@ struct TileLds {
     NPL = NW * (tz + 2);
     // without the ring the corner-plane pitch is padded to 4 (mod 8) doubles: the two lanes of
     // one cell, whose corners are two planes apart, then use complementary LDS banks
-    CPL = ring ? NPL : HPL + ((4 - HPL % 8) + 8) % 8;
+    CPL = ring ? NPL | 1 : HPL + ((4 - HPL % 8) + 8) % 8;
     n_node = 3 + (n_planes - 12);
     acc = 0;
     accc = acc + (size_t)n_node * plane * sizeof(double);
-    eb = accc + (size_t)12 * CPL * sizeof(double);
+    stage = accc + (size_t)12 * CPL * sizeof(double);
+    eb = stage + (size_t)waves * kStageBytes;
     ho = eb + 3 * (size_t)EPL * tsize;
     hn = ho + 3 * (size_t)HPL * tsize;
-    mq = (hn + 3 * (size_t)NPL * tsize + 7) & ~(size_t)7;
-    cnt = mq + (qwords ? (size_t)(kBlock / 64) * kMqCap * ((size_t)qwords * tsize + 2 * sizeof(int)) : 0);
+    cnt = (hn + 3 * (size_t)NPL * tsize + 7) & ~(size_t)7;
     arr = cnt + (size_t)(n_node - 3) * tx * tz * kMoveCodes * sizeof(int);
     rows = arr + (ring ? (size_t)(n_node - 3) * (tx + 2) * (tz + 2) * sizeof(int) : 0);
     bytes = rows + (size_t)(n_node - 3) * tz * 2 * sizeof(int);
@@ -733,30 +637,237 @@ struct Pstate<true> {
   }
 };
 
-// One block per tile of cells (tile rows are cell rows), one wavefront per tile row (or per
-// part of a row when the tile has fewer rows than wavefronts).  The row's particles (a
-// contiguous range of the cell-sorted order) are split into 64 contiguous runs, one per lane;
-// run lengths differ by at most one.  A lane accumulates the deposits of
-// particles that stay in their cell in registers and adds them to the LDS tile when its run
-// enters the next cell, so LDS atomics are issued once per (lane, cell) instead of once per
-// particle; particles changing cell go through a per-wave queue.  The pushed state of the
-// particle at iteration `it` of lane `l` is written to location row_start + 64 it + l, which
-// makes the stores (and next cycle's loads through the permutation) coalesced.
-// MIXED selects the mixed-precision form: FP32 state, gather, push and per-lane partial sums,
-// added into FP64 LDS accumulators and the FP64 moment planes.  With chunks of 4 the FP64 form
-// needs about 230 VGPRs (two waves per SIMD) and the FP32 form about 150 (three); the
-// chunk-of-2 form needs about 120 and 105 (four).  IDS adds the copy of particle ids
-// (tests only).  PW selects per-particle densities: each particle's moments are those of unit
-// density times its own density, which is read with the state and written with the pushed
-// state (a species with one density reads it from a one-element array with stride 0).  CH is
-// the chunk of particles a lane loads at once: 4, or 2 where a lane holds about two particles
-// per row.  The chunk-of-2 form deposits each particle into LDS at once (no register sums or
-// mover queue), reads the fields for every particle, keeps accumulators for the tile's own
-// nodes and cells only and sends the moments of a particle that leaves the tile to the global
-// planes: about 120 VGPRs (FP64) and 40 KB of LDS at 32 x 4, four blocks per CU.
-template <bool PUSH, bool MIXED, bool IDS, bool PW, int CH = 4>
+// A particle after the push: momentum u^{n+1}, position as stored (FP64: cell units; mixed:
+// in-cell offsets), in-cell offsets, new cell (grid coordinates and offset from the old one).
+template <typename T>
+struct Pushed {
+  T n0, n1, n2, rg1;  // u^{n+1}, 1 / gamma(u^{n+1})
+  T xn, zn, fx, fz;
+  int i2, k2, di, dk;
+  bool alive, finite, jump;
+};
+
+// Gather, implicit push and position advance of one particle of cell (i, k) with in-cell offsets
+// (fx, fz): E-bar at the cell's corner nodes in fE, its B in fB.  edge: the tile touches the
+// grid's border, so positions may need the periodic wrap or leave the grid (elsewhere a
+// particle, moving less than a cell, stays inside).  ok: the lane holds a particle.
+template <bool MIXED, typename T>
+__device__ __forceinline__ void push_one(const GridArgs &g, const SpConst<T> &K,
+                                         const Pstate<MIXED> &ps, int i, int k, T fx, T fz,
+                                         const T fE[12], const T fB[3], bool edge, bool ok,
+                                         Pushed<T> &o) {
+  const T one = T(1);
+  const T u0 = ps.u0, u1 = ps.u1, u2 = ps.u2;
+  const T ginv = rsqT(fmaT(u2, u2, fmaT(u1, u1, fmaT(u0, u0, one))));  // 1 / gamma(u^n)
+  // gather E-bar at x^{n+1/2} from the 4 corner nodes (linear weights)
+  const T W0 = (one - fx) * (one - fz), W1 = fx * (one - fz);
+  const T W2 = (one - fx) * fz, W3 = fx * fz;
+  T Ep[3];
+#pragma unroll
+  for (int qq = 0; qq < 3; ++qq)
+    Ep[qq] = fmaT(W3, fE[4 * qq + 3],
+                  fmaT(W2, fE[4 * qq + 2], fmaT(W1, fE[4 * qq + 1], W0 * fE[4 * qq])));
+  // implicit push: with a = u + beta E and b = beta B / gamma,
+  // u-bar = R a = (a + a x b + (a.b) b) / (1 + b.b), and u' = 2 u-bar - u
+  const T bg = K.beta * ginv;
+  const T bx = bg * fB[0], by = bg * fB[1], bz = bg * fB[2];
+  const T a0 = fmaT(K.beta, Ep[0], u0), a1 = fmaT(K.beta, Ep[1], u1);
+  const T a2 = fmaT(K.beta, Ep[2], u2);
+  const T inv = rcpT(fmaT(bz, bz, fmaT(by, by, fmaT(bx, bx, one))));
+  const T ab = fmaT(a2, bz, fmaT(a1, by, a0 * bx));
+  o.n0 = fmaT(T(2), fmaT(ab, bx, a0 + fmaT(a1, bz, -(a2 * by))) * inv, -u0);
+  o.n1 = fmaT(T(2), fmaT(ab, by, a1 + fmaT(a2, bx, -(a0 * bz))) * inv, -u1);
+  o.n2 = fmaT(T(2), fmaT(ab, bz, a2 + fmaT(a0, by, -(a1 * bx))) * inv, -u2);
+  const T g1sq = fmaT(o.n2, o.n2, fmaT(o.n1, o.n1, fmaT(o.n0, o.n0, one)));
+  o.rg1 = rsqT(g1sq);  // 1 / gamma(u^{n+1})
+  const T vx = o.n0 * o.rg1, vz = o.n2 * o.rg1;
+  // position advance: FP64 in cell units; mixed as FP32 offset with integer carry
+  bool alive = ok;
+  if constexpr (MIXED) {
+    T xn = fx + (T)g.cx * vx;
+    T zn = fz + (T)g.cz * vz;
+    o.finite = isfinite(g1sq) && isfinite(xn) && isfinite(zn);
+    const int cxi = o.finite ? (int)floorT(xn) : 0, czi = o.finite ? (int)floorT(zn) : 0;
+    xn -= (T)cxi;
+    zn -= (T)czi;
+    int ci = i + cxi, ck = k + czi;
+    if (xn >= one) { xn = T(0); ci += 1; }
+    if (zn >= one) { zn = T(0); ck += 1; }
+    if (edge) {
+      if (g.bc_x == PIC_BC_PERIODIC) {
+        ci = wrap1(ci, g.nx);
+      } else if (ci < 0 || ci >= g.nx) {
+        alive = false;
+      }
+      ck = wrap1(ck, g.nz);
+    }
+    o.xn = xn;
+    o.zn = zn;
+    o.i2 = ci;
+    o.k2 = ck;
+    o.fx = xn;
+    o.fz = zn;
+  } else {
+    T xn = ps.x + g.cx * vx;
+    T zn = ps.z + g.cz * vz;
+    if (edge) {
+      if (g.bc_x == PIC_BC_PERIODIC) {
+        if (xn < 0.0) xn += (double)g.nx;
+        if (xn >= (double)g.nx) xn -= (double)g.nx;
+      } else if (xn < 0.0 || xn >= (double)g.nx) {
+        alive = false;
+      }
+      if (zn < 0.0) zn += (double)g.nz;
+      if (zn >= (double)g.nz) zn -= (double)g.nz;
+    }
+    o.finite = isfinite(g1sq) && isfinite(xn) && isfinite(zn);
+    const double xf = floor(xn), zf = floor(zn);
+    o.i2 = o.finite ? (int)xf : i;
+    o.k2 = o.finite ? (int)zf : k;
+    o.xn = xn;
+    o.zn = zn;
+    o.fx = xn - xf;
+    o.fz = zn - zf;
+  }
+  alive = alive && o.finite;
+  int di = o.i2 - i, dk = o.k2 - k;
+  if (edge) {
+    if (di > 1) di -= g.nx;
+    if (di < -1) di += g.nx;
+    if (dk > 1) dk -= g.nz;
+    if (dk < -1) dk += g.nz;
+  }
+  const bool in3 = (unsigned)(di + 1) <= 2u && (unsigned)(dk + 1) <= 2u;
+  o.jump = alive && !in3;
+  alive = alive && in3;
+  o.di = alive ? di : 0;
+  o.dk = alive ? dk : 0;
+  o.alive = alive;
+}
+
+// The staging area of a wavefront: the planes, then per block the cell of every pass of the
+// deposit, the list of the movers (cell, and place in the planes in the high 8 bits) and per
+// particle its pass.
+struct Stage {
+  double *v;       // [kStagePlanes][kStagePitch]
+  int *key;        // [4 blocks][16 passes]
+  int *mover;      // [64]
+  uint8_t *pass;   // [64]: particle 16 b + 4 t + k at 16 b + 4 k + t
+  __device__ __forceinline__ explicit Stage(char *p)
+      : v(reinterpret_cast<double *>(p)),
+        key(reinterpret_cast<int *>(p + kStagePlanes * kStagePitch * sizeof(double))),
+        mover(key + 64),
+        pass(reinterpret_cast<uint8_t *>(key + 128)) {}
+};
+
+// The moments of a group's particles, one per lane, from the wavefront's staging area into the
+// LDS accumulators.  act: lanes with a slot; alive: with a particle to deposit; src, dst: its old
+// and new cell (ring cell in the low 16 bits, accumulator row above).
+//
+// The particles that stay in their cell: a pass takes one cell per block of 16 lanes, in their
+// (sorted) order; the other particles' weights are masked to zero (their staged values are
+// finite: only living particles are staged, and the area starts at zero).  At 64 particles per
+// cell a group takes one or two passes, at 11 about three.
+//
+// The movers go one by one, four at a time: 16 lanes compute a mover's 28 products (corner i,
+// moments j and 4 + j) and add them with two LDS atomic instructions.  A group has two movers in
+// a 1 keV plasma, ten or more in a laser-heated one, and as passes of their own (or a pass per
+// destination) they cost more than the particles that stay.
+__device__ __forceinline__ void deposit_group(const AccLds &acc, const Stage &st, bool act,
+                                              bool alive, int src, int dst, int own, int lane,
+                                              int dplane) {
+  const int mi = lane & 3, mb = (lane >> 2) & 3, mk4 = lane >> 4;  // i or j, block, k
+  const int ob = lane >> 4, ol = lane & 15;                        // block and place of the lane's own particle
+  const bool mover = alive && src != dst;
+  const int before = lane_before(src);  // (all lanes active)
+  const bool head = act && (ol == 0 || before != src);
+  const uint64_t heads = __ballot(head), movers = __ballot(mover);
+  auto in_block = [](uint64_t m, int b) { return (uint32_t)(m >> (16 * b)) & 0xffffu; };
+  {
+    const int seg = __popc(in_block(heads, ob) & ((2u << ol) - 1u)) - 1;
+    if (head) st.key[ob * 16 + seg] = src;
+    if (mover) st.mover[__popcll(movers & ((1ull << lane) - 1ull))] = dst | (own << 24);
+    st.pass[ob * 16 + (ol & 3) * 4 + (ol >> 2)] = (uint8_t)(alive && !mover ? seg : 255);
+  }
+  int n_pass = 0;  // of the block with most passes
+#pragma unroll
+  for (int b = 0; b < 4; ++b) n_pass = max(n_pass, __popc(in_block(heads, b)));
+  const int n_mine = __popc(in_block(heads, mb)), n_movers = __popcll(movers);
+  wave_sync();
+  // corner weights, moments and passes of the block's four particles of each round
+  const int at = mb * 17 + mk4;
+  double A[4], B0[4], B1[4];
+  const int p0 = (2 + mi) * kStagePitch, p1 = (6 + min(mi, 2)) * kStagePitch;  // the planes of moments j, 4 + j
+  const uint32_t pass4 = *reinterpret_cast<const uint32_t *>(st.pass + 16 * mb + 4 * mk4);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const double fx = st.v[at + 4 * t], fz = st.v[kStagePitch + at + 4 * t];
+    const double gx = (mi & 1) ? fx : 1.0 - fx, gz = (mi & 2) ? fz : 1.0 - fz;
+    A[t] = gx * gz;
+    B0[t] = st.v[p0 + at + 4 * t];
+    B1[t] = st.v[p1 + at + 4 * t];
+  }
+  // the accumulators of corner c, moments j and 4 + j
+  auto node_of = [&](int c) { return acc.node + (mi < 3 ? mi : dplane) * acc.plane + (c & 1) + (c >> 1) * acc.LW; };
+  auto cell_of = [&](int c) { return acc.cell + (min(mi, 2) * 4 + c) * acc.npl; };
+  {
+    // result lane 16 i + 4 b + j: corner i (of the cell), moment j
+    double *const node = node_of(mk4), *const cell = cell_of(mk4);
+    for (int p = 0; p < n_pass; ++p) {
+      const int k = st.key[mb * 16 + p];
+      double d0 = 0.0, d1 = 0.0;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const double w = ((pass4 >> (8 * t)) & 255u) == (uint32_t)p ? A[t] : 0.0;
+        d0 = __builtin_amdgcn_mfma_f64_4x4x4f64(w, B0[t], d0, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f64_4x4x4f64(w, B1[t], d1, 0, 0, 0);
+      }
+      if (p < n_mine) {
+        const int rc = k & 0xffff;               // ring cell; its lower-left node is rc + row
+        atomicAdd(&node[rc + (k >> 16)], d0);
+        if (mi < 3) atomicAdd(&cell[rc], d1);
+      }
+    }
+  }
+  if (n_movers) {
+    // lane 16 g + 4 i + j: mover g of the step, corner i, moments j and 4 + j
+    double *const node = node_of(mb), *const cell = cell_of(mb);
+    for (int m = mk4; m < n_movers; m += 4) {
+      const int k = st.mover[m], q = k >> 24, rc = k & 0xffff;
+      const double fx = st.v[q], fz = st.v[kStagePitch + q];
+      const double w = ((mb & 1) ? fx : 1.0 - fx) * ((mb & 2) ? fz : 1.0 - fz);
+      atomicAdd(&node[rc + ((k >> 16) & 0xff)], w * st.v[p0 + q]);
+      if (mi < 3) atomicAdd(&cell[rc], w * st.v[p1 + q]);
+    }
+  }
+}
+
+// One block per tile of cells (tile rows are cell rows).  MIXED selects the mixed-precision
+// form: FP32 state, gather and push, added into FP64 LDS accumulators and the FP64 moment
+// planes.  IDS adds the copy of particle ids (tests only).  PW selects per-particle densities:
+// each particle's moments are those of unit density times its own density, which is read with
+// the state and written with the pushed state (a species with one density reads it from a
+// one-element array with stride 0).
+//
+// Two forms.  The grouped form (DIRECT = false) takes the particles of a tile row (a contiguous
+// range of the cell-sorted order) in groups of 64 consecutive slots, one per lane, the groups of
+// the tile dealt to the block's wavefronts in turn.  A particle's pushed state goes to the
+// location of its slot, so stores are coalesced, and next cycle's reads through the permutation
+// too: most particles keep their cell, so 64 consecutive slots read a few runs of consecutive
+// locations.  The group's moments are summed per cell by deposit_group, movers like the others,
+// into accumulators that cover the tile and its ring.
+//
+// The direct form (few particles per cell: a lane holds about two particles per row) splits the
+// row into 64 contiguous runs, one per lane, whose lengths differ by at most one, loads two
+// particles of a lane at a time, adds each particle's moments to LDS at once, keeps accumulators
+// for the tile's own nodes and cells only and sends the moments of a particle that leaves the
+// tile to the global planes: about 120 VGPRs (FP64) and 40 KB of LDS at 32 x 4, four blocks per
+// CU.  The pushed state of the particle at iteration `it` of lane `l` is written to location
+// row_start + 64 it + l.
+template <bool PUSH, bool MIXED, bool IDS, bool PW, bool DIRECT = false>
 __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   using T = typename std::conditional<MIXED, float, double>::type;
+  static_assert(PUSH || !DIRECT, "the deposit of a loaded state uses the grouped form");
   const GridArgs &g = a.g;
   const TileArgs &t = a.t;
   const int tzi = tile / t.ntx, txi = tile - tzi * t.ntx;
@@ -764,123 +875,130 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   const int i1 = min(i0 + t.tx, g.nx), k1 = min(k0 + t.tz, g.nz);
   const int ntc = t.tx * t.tz;
   const int64_t nn = g.nnodes, nc = g.ncells;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
 
   extern __shared__ double lds[];
   char *ldsb = reinterpret_cast<char *>(lds);
-  constexpr int kQw = mq_words(PW);
-  const TileLds Lo(g.n_planes, t.tx, t.tz, (int)sizeof(T), (PUSH && CH == 2) ? 0 : kQw);
+  const TileLds Lo(g.n_planes, t.tx, t.tz, (int)sizeof(T), DIRECT ? 0 : nwaves);
   const AccLds acc{reinterpret_cast<double *>(ldsb + Lo.acc),
                    reinterpret_cast<double *>(ldsb + Lo.accc), Lo.plane, Lo.CPL, Lo.LW, Lo.NW};
   T *Eb = reinterpret_cast<T *>(ldsb + Lo.eb);
   T *Ho = reinterpret_cast<T *>(ldsb + Lo.ho);
   T *Hn = reinterpret_cast<T *>(ldsb + Lo.hn);
-  int *cntL = reinterpret_cast<int *>(ldsb + Lo.cnt);
+  int *cntL = reinterpret_cast<int *>(ldsb + Lo.cnt);  // [species][9 codes][cells of the tile]
   int *arrL = reinterpret_cast<int *>(ldsb + Lo.arr);  // the layout with the ring
-  const int LW = Lo.LW, plane = Lo.plane;
-  const int n_acc = Lo.n_node * plane + 12 * Lo.CPL;  // node planes, then cell-corner planes
+  const int LW = Lo.LW, plane = Lo.plane;  // plane: pitch of the node planes, LW * LH nodes
+  // node planes, cell-corner planes and (grouped) the staging areas, which follow them
+  const int n_zero = Lo.n_node * plane + 12 * Lo.CPL + (DIRECT ? 0 : nwaves * (kStageBytes / 8));
 
-  for (int e = threadIdx.x; e < n_acc; e += blockDim.x) acc.node[e] = 0.0;
-  // the chunk-of-2 form: accumulators over the tile's own nodes and cells (no ring)
-  constexpr bool kTileOnly = PUSH && CH == 2;
+  for (int e = 2 * threadIdx.x; e < n_zero; e += 2 * blockDim.x) {
+    if (e + 1 < n_zero)
+      *reinterpret_cast<double2 *>(acc.node + e) = make_double2(0.0, 0.0);
+    else
+      acc.node[e] = 0.0;
+  }
+  constexpr bool kTileOnly = DIRECT;  // accumulators over the tile's own nodes and cells (no ring)
   const int AW = t.tx + 2, AH = t.tz + 2;  // arrival counts: the tile's cells and their ring
   if (PUSH) {
     const int nsl = Lo.n_node - 3;
-    for (int e = threadIdx.x; e < nsl * ntc * kMoveCodes; e += blockDim.x) cntL[e] = 0;
+    // the counters of the particles that stay (code 4) start at the cell's particles (below)
+    for (int s = 0; s < nsl; ++s)
+      for (int e = threadIdx.x; e < (kMoveCodes - 1) * ntc; e += blockDim.x)
+        cntL[s * ntc * kMoveCodes + e + (e >= 4 * ntc ? ntc : 0)] = 0;
     if constexpr (!kTileOnly)
       for (int e = threadIdx.x; e < nsl * AW * AH; e += blockDim.x) arrL[e] = 0;
   }
   const int cw = i1 - i0, chh = k1 - k0;  // the tile's cells inside the grid
   // a tile and its two-cell ring fit in the grid along an axis: wraps need one compare there
   const bool nearx = g.nx >= t.tx + 3, nearz = g.nz >= t.tz + 3;
-  // Stage the fields of the tile and the slot range of every tile row of every species in one
-  // pass: a thread issues all its loads (at clamped, valid addresses) before it stores any, so
-  // the block waits for one memory round trip instead of one per array.
+  // Stage the fields of the tile, the particles of every cell and the slot range of every tile
+  // row of every species.  The elements of the three field arrays (H^{n+3/2} on the cells and
+  // their ring, E-bar on the nodes, H^{n+1/2} on the cells, which also brings the cell's slots)
+  // are numbered one after the other and dealt to the threads, so a thread computes the address
+  // of one element (direct form, with half the threads: two, loaded before it stores either) and
+  // the block waits for one memory round trip.  (Every thread computing an element of each array
+  // took 550 instructions, 3 us of a tile's time with four wavefronts per SIMD.)
+  constexpr int kEl = DIRECT ? 2 : 1;
   const int nrows_t = k1 - k0;
   int *rowsL = reinterpret_cast<int *>(ldsb + Lo.rows);  // [species][row]: first, end slot
-  const int n_stage = max(max(Lo.HPL, nrows_t), PUSH ? max(Lo.EPL, Lo.NPL) : 0);
-  for (int e = threadIdx.x; e < n_stage; e += blockDim.x) {
-    // H^{n+1/2} on the tile's cells
-    const int eh = min(e, Lo.HPL - 1);
-    const int hk = SmallDiv(t.tx).q(eh), hi = eh - hk * t.tx;
-    const bool h_in = e < Lo.HPL && i0 + hi < g.nx && k0 + hk < g.nz;
-    const int64_t ch = (int64_t)min(k0 + hk, g.nz - 1) * g.nx + min(i0 + hi, g.nx - 1);
-    double ho[3];
+  const int v_e = PUSH ? Lo.NPL : 0, v_h = v_e + (PUSH ? Lo.EPL : 0), v_n = v_h + Lo.HPL;
+  // (the pointers are kept in registers: a choice between two members of the kernel's arguments
+  // would be made by their address, and the arguments copied to scratch memory for it)
+  const double *p_ho = a.Hold, *p_eo = a.Eold, *p_hn = a.Hnew;
+  asm("" : "+v"(p_ho), "+v"(p_eo), "+v"(p_hn));
+  for (int v0 = threadIdx.x; v0 < v_n; v0 += kEl * blockDim.x) {
+    double fa[kEl][3], fb[kEl][3];
+    int cb[kEl][kMaxSpecies], ce[kEl][kMaxSpecies], el[kEl], row[kEl];
+    bool is_e[kEl], is_h[kEl], in[kEl], first[kEl], last[kEl];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) ho[q] = a.Hold[q * nc + ch];
-    // first and end slot of tile row e of every species (threads e < rows of the tile)
-    const bool r_th = e < nrows_t;
-    const int64_t rowc = (int64_t)(k0 + min(e, nrows_t - 1)) * g.nx;
-    int rbv[kMaxSpecies], rev[kMaxSpecies];
-#pragma unroll
-    for (int q = 0; q < kMaxSpecies; ++q) {
-      rbv[q] = 0;
-      rev[q] = 0;
-      if (q < a.nsp && a.sp[q].active && r_th) {
-        rbv[q] = a.sp[q].cs[rowc + i0];
-        rev[q] = a.sp[q].cs[rowc + i1];
+    for (int u = 0; u < kEl; ++u) {
+      const int v = min(v0 + u * (int)blockDim.x, v_n - 1);  // (past the end: the last one again)
+      is_h[u] = v >= v_h;
+      is_e[u] = v >= v_e && !is_h[u];
+      el[u] = v - (is_h[u] ? v_h : is_e[u] ? v_e : 0);
+      const int off = is_h[u] || is_e[u] ? 0 : -1;  // the ring starts one cell before the tile
+      const int W = is_h[u] ? t.tx : is_e[u] ? Lo.EW : Lo.NW;
+      const int ez = SmallDiv(W).q(el[u]), ex = el[u] - ez * W;
+      const int xmax = is_e[u] ? g.nxn - 1 : g.nx - 1;
+      int gi = i0 + off + ex, gk = k0 + off + ez;
+      row[u] = ez;
+      if (is_h[u]) {
+        in[u] = gi < g.nx && gk < g.nz;
+        gk = min(gk, g.nz - 1);
+      } else {
+        gk = wrap_t(gk, g.nz, nearz);
+        if (g.bc_x == PIC_BC_PERIODIC) gi = wrap_t(gi, g.nx, nearx);
+        in[u] = gi >= 0 && gi <= xmax;
       }
-    }
-    double eo[3], en[3], hn[3];
-    bool e_in = false, n_in = false;
-    if (PUSH) {
-      // E-bar on the tile's nodes
-      const int ee = min(e, Lo.EPL - 1);
-      const int ek = SmallDiv(Lo.EW).q(ee), ei = ee - ek * Lo.EW;
-      int gi = i0 + ei;
-      const int gk = wrap_t(k0 + ek, g.nz, nearz);
-      e_in = e < Lo.EPL;
-      if (g.bc_x == PIC_BC_PERIODIC) gi = wrap_t(gi, g.nx, nearx); else e_in = e_in && gi <= g.nx;
-      const int64_t n = (int64_t)gk * g.nxn + min(gi, g.nxn - 1);
+      first[u] = in[u] && ex == 0;
+      last[u] = in[u] && ex == cw - 1;
+      const int64_t n = (int64_t)gk * (is_e[u] ? g.nxn : g.nx) + min(max(gi, 0), xmax);
+      const double *f = (is_h[u] ? p_ho : is_e[u] ? p_eo : p_hn) + n;
+      const int64_t pitch = is_e[u] ? nn : nc;
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
-        eo[q] = a.Eold[q * nn + n];
-        en[q] = a.Enew[q * nn + n];
+        fa[u][q] = f[q * pitch];
+        fb[u][q] = 0.0;
       }
-      // H^{n+3/2} on the tile's cells and their ring
-      const int en_ = min(e, Lo.NPL - 1);
-      const int nk = SmallDiv(Lo.NW).q(en_), ni = en_ - nk * Lo.NW;
-      int gi2 = i0 - 1 + ni;
-      const int gk2 = wrap_t(k0 - 1 + nk, g.nz, nearz);
-      n_in = e < Lo.NPL;
-      if (g.bc_x == PIC_BC_PERIODIC) gi2 = wrap_t(gi2, g.nx, nearx); else n_in = n_in && gi2 >= 0 && gi2 < g.nx;
-      const int64_t c2 = (int64_t)gk2 * g.nx + min(max(gi2, 0), g.nx - 1);
+      if (is_e[u]) {
 #pragma unroll
-      for (int q = 0; q < 3; ++q) hn[q] = a.Hnew[q * nc + c2];
-    }
-    if (e < Lo.HPL) {
-#pragma unroll
-      for (int q = 0; q < 3; ++q) Ho[q * Lo.HPL + e] = h_in ? (T)ho[q] : T(0);
-    }
-    if (r_th) {
+        for (int q = 0; q < 3; ++q) fb[u][q] = a.Enew[q * nn + n];
+      }
 #pragma unroll
       for (int q = 0; q < kMaxSpecies; ++q) {
-        if (q < a.nsp) {
-          rowsL[2 * (q * nrows_t + e)] = rbv[q];
-          rowsL[2 * (q * nrows_t + e) + 1] = rev[q];
+        cb[u][q] = 0;
+        ce[u][q] = 0;
+        if (is_h[u] && q < a.nsp && a.sp[q].active) {
+          cb[u][q] = a.sp[q].cs[n];
+          ce[u][q] = a.sp[q].cs[n + 1];
         }
       }
     }
-    if (PUSH && e < Lo.EPL) {
 #pragma unroll
-      for (int q = 0; q < 3; ++q) Eb[q * Lo.EPL + e] = e_in ? (T)(0.5 * (eo[q] + en[q])) : T(0);
-    }
-    if (PUSH && e < Lo.NPL) {
+    for (int u = 0; u < kEl; ++u) {
+      T *d = (is_h[u] ? Ho : is_e[u] ? Eb : Hn) + el[u];
+      const int pitch = is_h[u] ? Lo.HPL : is_e[u] ? Lo.EPL : Lo.NPL;
 #pragma unroll
-      for (int q = 0; q < 3; ++q) Hn[q * Lo.NPL + e] = n_in ? (T)hn[q] : T(0);
+      for (int q = 0; q < 3; ++q)
+        d[q * pitch] = in[u] ? (T)(is_e[u] ? 0.5 * (fa[u][q] + fb[u][q]) : fa[u][q]) : T(0);
+      if (is_h[u]) {
+#pragma unroll
+        for (int q = 0; q < kMaxSpecies; ++q) {
+          if (q < a.nsp) {
+            if (PUSH) cntL[(q * kMoveCodes + 4) * ntc + el[u]] = in[u] ? ce[u][q] - cb[u][q] : 0;
+            if (first[u]) rowsL[2 * (q * nrows_t + row[u])] = cb[u][q];
+            if (last[u]) rowsL[2 * (q * nrows_t + row[u]) + 1] = ce[u][q];
+          }
+        }
+      }
     }
   }
   __syncthreads();
 
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  MoverQ<T> mq;
-  {
-    char *qb = ldsb + Lo.mq + (size_t)wave * kMqCap * ((size_t)kQw * sizeof(T) + 2 * sizeof(int));
-    mq.v = reinterpret_cast<T *>(qb);
-    mq.idx = reinterpret_cast<int *>(qb + (size_t)kMqCap * kQw * sizeof(T));
-  }
-  const T cxT = (T)g.cx, czT = (T)g.cz;
+  // the tile touches the grid's border: its particles may wrap or leave
+  const bool edge = i0 == 0 || i1 == g.nx || k0 == 0 || k1 == g.nz;
 
+  int gr = wave;  // grouped form: the wavefront's next group
   for (int s = 0; s < a.nsp; ++s) {
     const SpeciesArgs &sp = a.sp[s];
     if (!sp.active) continue;
@@ -900,86 +1018,63 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
     const int wstride = sp.w_stride;
     const int32_t *perm = sp.perm;
     const int dplane = 3 + s;  // density plane of the species in the node accumulators
-    // A tile with fewer rows than wavefronts splits each row's particles into wpr contiguous
-    // parts, one per wavefront, so short tiles keep every wavefront busy.
     const int nrows = k1 - k0;
-    const int wpr = nrows < nwaves ? nwaves / nrows : 1;  // 1, 2 or 4 (four wavefronts)
-    const int wsh = wpr == 4 ? 2 : (wpr == 2 ? 1 : 0);
-    const int part = wave % wpr;
-    for (int r = k0 + wave / wpr; r < k1; r += nwaves / wpr) {
-      const int rb = rowsL[2 * (s * nrows_t + (r - k0))], re = rowsL[2 * (s * nrows_t + (r - k0)) + 1];
-      const int jb = rb + (int)(((uint32_t)(re - rb) * (uint32_t)part) >> wsh);
-      const int je = rb + (int)(((uint32_t)(re - rb) * (uint32_t)(part + 1)) >> wsh);
-      const int L = je - jb;
-      if (L == 0) continue;
-      const int q = L >> 6, rr = L & 63;
-      const int my_n = q + (lane < rr ? 1 : 0);
-      const int start = jb + lane * q + min(lane, rr);
-      const int iters = q + (rr > 0 ? 1 : 0);
-      const int lz = r - k0 + 1;
-      const int lk = r - k0;
-      CellAcc<T> ca;
-      ca.clear();
-      ca.cell = -1;
-      int nq = 0;  // movers queued by this wavefront (uniform)
-      // fields of the cell the lane's run is in, kept in registers while the run stays in it:
-      // H^{n+1/2} (fB) and E-bar at its 4 nodes (fE, the push)
-      T fB0 = T(0), fB1 = T(0), fB2 = T(0), fE[12];
-      // The run is processed in chunks of kChunk particles: the chunk's state loads are issued
-      // together (with the next chunk's permutation entries), then its particles are pushed
-      // from registers in an unrolled sequence.  Global stores share the vector-memory counter
-      // with loads, so a load whose value is still in flight across a loop iteration makes
-      // the compiler wait for all earlier stores too; keeping every loaded value inside one
-      // iteration lets it wait for the loads alone.  Loads are issued unconditionally (slots
-      // past a lane's run read a location inside the state arrays, and their values go
-      // unused): a load under a divergent branch also forces a full wait.
-      constexpr int kChunk = CH;
-      // two particles per chunk: the form for about two particles per lane and row, where a
-      // lane's register sums would hold one or two particles; it deposits each particle into
-      // LDS directly (no register sums, row-end reduction or mover queue: fewer registers)
-      constexpr bool kDirect = PUSH && CH == 2;
-      Pstate<MIXED> cb[kChunk];
-      int cp_[kChunk], np_[kChunk];
-      T cw_[kChunk];
-      // A chunk's permutation entries come in one 16-byte load per lane (the array is padded
-      // so the load stays inside it); entries past the lane's run are clamped to a location
-      // inside the state arrays and their particles go unused.
-      static_assert((kChunk == 4 || kChunk == 2) && kPermPad >= 2 * kChunk,
-                    "one int4 or int2 of entries per chunk");
-      const uint32_t loc_max = (uint32_t)(sp.cap - 1);
-      auto perm4 = [&](int first, int out[kChunk]) {
-        if constexpr (kChunk == 4) {
-          int4 v;
-          __builtin_memcpy(&v, perm + first, sizeof(v));
-          out[0] = (int)min((uint32_t)v.x, loc_max);
-          out[1] = (int)min((uint32_t)v.y, loc_max);
-          out[2] = (int)min((uint32_t)v.z, loc_max);
-          out[3] = (int)min((uint32_t)v.w, loc_max);
-        } else {
-          int2 v;
-          __builtin_memcpy(&v, perm + first, sizeof(v));
-          out[0] = (int)min((uint32_t)v.x, loc_max);
-          out[1] = (int)min((uint32_t)v.y, loc_max);
-        }
+    const uint32_t loc_max = (uint32_t)(sp.cap - 1);
+    // A particle outside the cell its slot says: raise the flag and drop it.  (Never in a
+    // consistent state; the counts keep the slot, so the next order stays in bounds.)
+    auto drop_slot = [&](int j, uint32_t loc) {
+      atomicOr(a.flags, kFlagOrder);
+      if (PUSH) sp.locode[j] = (loc << 4) | kAbsorbed;
+    };
+    if constexpr (!DIRECT) {
+      const Stage stage(ldsb + Lo.stage + wave * kStageBytes);
+      double *const st = stage.v;
+      const int own = lane + (lane >> 4);  // this lane's particle in a staging plane
+      if constexpr (!PW) st[5 * kStagePitch + own] = (double)K.w;
+      // The tile's groups, row by row, are dealt to the wavefronts (a power of two) in turn, on
+      // from where the last species ended: group gr of row r holds slots jg .. jg + ngr - 1
+      // (ngr = 0: no group left).
+      gr &= nwaves - 1;
+      int r = k0, rb = 0, re = 0, jg = 0, ngr = 0;
+      auto take_row = [&]() {
+        rb = __builtin_amdgcn_readfirstlane(rowsL[2 * (s * nrows_t + (r - k0))]);
+        re = __builtin_amdgcn_readfirstlane(rowsL[2 * (s * nrows_t + (r - k0)) + 1]);
       };
-      perm4(start, np_);
-      // all lanes run the same number of iterations so the mover queue stays wave-uniform
-      for (int c0 = 0; c0 < iters; c0 += kChunk) {
-#pragma unroll
-        for (int kk = 0; kk < kChunk; ++kk) {
-          cp_[kk] = np_[kk];
-          cb[kk].load(src, cp_[kk]);
-          if constexpr (PW) cw_[kk] = wsrc[cp_[kk] * wstride];
+      auto settle = [&]() {  // the group at or after (r, gr)
+        while (r < k1) {
+          jg = rb + 64 * gr;
+          ngr = min(64, re - jg);
+          if (ngr > 0) return;
+          gr -= (re - rb + 63) >> 6;
+          if (++r < k1) take_row();
         }
-        perm4(start + c0 + kChunk, np_);
-#pragma unroll
-        for (int kk = 0; kk < kChunk; ++kk) {
-          const int it = c0 + kk;
-          if (it >= iters) break;
-          const bool act = it < my_n;
-          const int j = start + it;
-          const int p = cp_[kk];
-          const Pstate<MIXED> &ps = cb[kk];
+        jg = ngr = 0;
+      };
+      take_row();
+      settle();
+      // Pipeline: while a group's moments are deposited, the state of the next group and the
+      // permutation of the one after it are on their way.  The loads of a group go out between
+      // the push and the stores of the group before it: stores share the vector-memory counter
+      // with loads, in order, so waiting for a load issued after stores would wait for the stores.
+      auto load_perm = [&]() { return (int)min((uint32_t)perm[jg + min(lane, max(ngr - 1, 0))], loc_max); };
+      int rc_ = r, jc = jg, nc_ = ngr;  // the current group
+      Pstate<MIXED> ps{};
+      T wp = K.w;
+      int pc = load_perm();
+      gr += nwaves;
+      settle();
+      int rn = r, jn = jg, nn_ = ngr;  // the next group
+      int pn = load_perm();
+      ps.load(src, pc);
+      if constexpr (PW) wp = wsrc[pc * wstride];
+      // wait for the first loads here: a load pending on entry only would make the compiler wait
+      // at the head of every iteration for everything issued before it
+      asm volatile("" ::"v"(pn), "v"(ps.x), "v"(ps.z), "v"(ps.u0), "v"(ps.u1), "v"(ps.u2), "v"(wp));
+      while (nc_ > 0) {
+        {
+          const int r = rc_, j = jc + lane, p = pc;
+          const bool act = lane < nc_;
+          const int lk = r - k0;
           int i, k;
           T fx, fz;
           if constexpr (MIXED) {
@@ -988,267 +1083,308 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             fx = ps.x;
             fz = ps.z;
           } else {
-            i = (int)floor(ps.x);
-            k = (int)floor(ps.z);
-            fx = ps.x - (double)i;
-            fz = ps.z - (double)k;
+            const double xf = floor(ps.x), zf = floor(ps.z);
+            i = (int)xf;
+            k = (int)zf;
+            fx = ps.x - xf;
+            fz = ps.z - zf;
           }
-          const T u0 = ps.u0, u1 = ps.u1, u2 = ps.u2;
-          const T wp = PW ? cw_[kk] : K.w;  // the particle's density
           const bool ok = act && k == r && i >= i0 && i < i1;
-          if (act && !ok) {
-            atomicOr(a.flags, kFlagOrder);
-            if (PUSH) sp.locode[j] = ((uint32_t)(jb + it * 64 + lane) << 4) | kAbsorbed;
-          }
-          // Lanes without a valid particle run the arithmetic on a valid cell of the tile and
-          // discard the results, so the main path has no branches around it.
-          const int li = ok ? i - i0 : max(ca.cell, 0);
+          if (act && !ok) drop_slot(j, (uint32_t)j);
+          // Lanes without a valid particle run the arithmetic on the tile's first cell and
+          // discard the results.
+          const int li = ok ? i - i0 : 0;
           const int hc = lk * t.tx + li;
-          // On entering a new cell: read its fields, use them, and only then flush the previous
-          // cell's accumulator.  LDS operations complete in order, so a read issued after the
-          // flush's atomics (or consumed while they are in flight) would wait for all of them.
-          // The chunk-of-2 form reads them for every particle (a lane holds about two per row,
-          // and fields kept across particles would hold about 30 registers).
-          const bool newcell = kDirect || (ok && li != ca.cell);
-          if (newcell) {
-            fB0 = Ho[hc];
-            fB1 = Ho[Lo.HPL + hc];
-            fB2 = Ho[2 * Lo.HPL + hc];
-            if (PUSH) {
-              const int e00 = lk * Lo.EW + li;
+          T fB[3];
 #pragma unroll
-              for (int qq = 0; qq < 3; ++qq) {
-                const T *f = Eb + qq * Lo.EPL + e00;
-                fE[4 * qq] = f[0];
-                fE[4 * qq + 1] = f[1];
-                fE[4 * qq + 2] = f[Lo.EW];
-                fE[4 * qq + 3] = f[Lo.EW + 1];
-              }
+          for (int qq = 0; qq < 3; ++qq) fB[qq] = Ho[qq * Lo.HPL + hc];
+          Compact<T> m;
+          T dfx = fx, dfz = fz;
+          const T wcur = wp;
+          auto next_loads = [&]() {
+            pc = pn;
+            ps.load(src, pc);
+            if constexpr (PW) wp = wsrc[pc * wstride];
+            gr += nwaves;
+            settle();
+            pn = load_perm();
+          };
+          int ring = (lk + 1) * Lo.NW + li + 1;  // ring cell of the deposit
+          const int key_src = ((lk + 1) << 16) | ring;
+          int key = key_src;
+          bool alive = ok;
+          if constexpr (!PUSH) {
+            const T ginv = rsqT(fmaT(ps.u2, ps.u2, fmaT(ps.u1, ps.u1, fmaT(ps.u0, ps.u0, T(1)))));
+            m = compact_moments(K, ginv, ps.u0, ps.u1, ps.u2, fB[0], fB[1], fB[2]);
+            next_loads();
+          } else {
+            T fE[12];
+            const int e00 = lk * Lo.EW + li;
+#pragma unroll
+            for (int qq = 0; qq < 3; ++qq) {
+              const T *f = Eb + qq * Lo.EPL + e00;
+              fE[4 * qq] = f[0];
+              fE[4 * qq + 1] = f[1];
+              fE[4 * qq + 2] = f[Lo.EW];
+              fE[4 * qq + 3] = f[Lo.EW + 1];
+            }
+            Pushed<T> o;
+            push_one<MIXED>(g, K, ps, i, k, fx, fz, fE, fB, edge, ok, o);
+            if (ok && !o.finite) atomicOr(a.flags, kFlagNonFinite);
+            if (o.jump) atomicOr(a.flags, kFlagJump);
+            alive = o.alive;
+            const uint32_t code = alive ? (uint32_t)((o.dk + 1) * 3 + (o.di + 1)) : kAbsorbed;
+            // moments M^{n+3/2} at x^{n+3/2} with u^{n+1}, 1/gamma(u^{n+1}) and H^{n+3/2}
+            // of the new cell
+            ring += o.dk * Lo.NW + o.di;
+            key = ((lk + 1 + o.dk) << 16) | ring;
+            m = compact_moments(K, o.rg1, o.n0, o.n1, o.n2, Hn[ring], Hn[Lo.NPL + ring], Hn[2 * Lo.NPL + ring]);
+            dfx = o.fx;
+            dfz = o.fz;
+            next_loads();
+            if constexpr (MIXED) {
+              store_or_drop(sp.mdst_cell, j, ok, o.k2 * g.nx + o.i2);
+              store_or_drop(sp.mdst[0], j, ok, o.xn);
+              store_or_drop(sp.mdst[1], j, ok, o.zn);
+              store_or_drop(sp.mdst[2], j, ok, o.n0);
+              store_or_drop(sp.mdst[3], j, ok, o.n1);
+              store_or_drop(sp.mdst[4], j, ok, o.n2);
+              if constexpr (PW) store_or_drop(wdst, j, ok && wstride != 0, wcur);
+              store_or_drop(sp.locode, j, ok, ((uint32_t)j << 4) | code);
+            } else {
+              store_or_drop(sp.dst[0], j, ok, o.xn);
+              store_or_drop(sp.dst[1], j, ok, o.zn);
+              store_or_drop(sp.dst[2], j, ok, o.n0);
+              store_or_drop(sp.dst[3], j, ok, o.n1);
+              store_or_drop(sp.dst[4], j, ok, o.n2);
+              if constexpr (PW) store_or_drop(wdst, j, ok && wstride != 0, wcur);
+              store_or_drop(sp.locode, j, ok, ((uint32_t)j << 4) | code);
+            }
+            // particle ids (tests only)
+            if (IDS && ok && sp.dst_id) sp.dst_id[j] = sp.src_id[p];
+            if (ok && code != 4u) {
+              atomicSub(&cntS[4 * ntc + hc], 1);
+              if (alive) atomicAdd(&cntS[code * ntc + hc], 1);
             }
           }
-          const T one = T(1);
-          const T ginv = rsqT(fmaT(u2, u2, fmaT(u1, u1, fmaT(u0, u0, one))));  // 1 / gamma(u^n)
-          if (!PUSH) {
-            Compact<T> m0 = compact_moments(K, ginv, u0, u1, u2, fB0, fB1, fB2);
-            if constexpr (PW) scale_compact(m0, wp);
-            if (newcell) {
-              if (ca.cell >= 0) ca.flush(acc, lz, dplane);
-              ca.clear();
-              ca.cell = li;
-            }
-            if (ok) ca.add(fx, fz, m0, wp);
-          } else {
-            bool mover = false;
-            int mo = 0, mh = 0;
-            T fx2, fz2;
-            Compact<T> m;
-            {
-              // gather E-bar at x^{n+1/2} from the 4 corner nodes (linear weights)
-              const T W0 = (one - fx) * (one - fz), W1 = fx * (one - fz);
-              const T W2 = (one - fx) * fz, W3 = fx * fz;
-              T Ep[3];
+          if constexpr (PW) scale_compact(m, wcur);
+          if (alive) {
+            st[own] = (double)dfx;
+            st[kStagePitch + own] = (double)dfz;
+            st[2 * kStagePitch + own] = (double)m.j0;
+            st[3 * kStagePitch + own] = (double)m.j1;
+            st[4 * kStagePitch + own] = (double)m.j2;
+            if constexpr (PW) st[5 * kStagePitch + own] = (double)wcur;
+            st[6 * kStagePitch + own] = (double)m.a0;
+            st[7 * kStagePitch + own] = (double)m.a1;
+            st[8 * kStagePitch + own] = (double)m.a2;
+          }
+          wave_sync();
+          deposit_group(acc, stage, act, alive, key_src, key, own, lane, dplane);
+          wave_sync();
+        }
+        rc_ = rn;
+        jc = jn;
+        nc_ = nn_;
+        rn = r;
+        jn = jg;
+        nn_ = ngr;
+      }
+    } else {
+      // A tile with fewer rows than wavefronts splits each row's particles into wpr contiguous
+      // parts, one per wavefront, so short tiles keep every wavefront busy.
+      const int wpr = nrows < nwaves ? nwaves / nrows : 1;  // a power of two (up to eight wavefronts)
+      const int wsh = wpr == 8 ? 3 : wpr == 4 ? 2 : wpr == 2 ? 1 : 0;
+      const int part = wave % wpr;
+      for (int r = k0 + wave / wpr; r < k1; r += nwaves / wpr) {
+        const int rb = rowsL[2 * (s * nrows_t + (r - k0))], re = rowsL[2 * (s * nrows_t + (r - k0)) + 1];
+        const int jb = rb + (int)(((uint32_t)(re - rb) * (uint32_t)part) >> wsh);
+        const int je = rb + (int)(((uint32_t)(re - rb) * (uint32_t)(part + 1)) >> wsh);
+        const int L = je - jb;
+        if (L == 0) continue;
+        const int q = L >> 6, rr = L & 63;
+        const int my_n = q + (lane < rr ? 1 : 0);
+        const int start = jb + lane * q + min(lane, rr);
+        const int iters = q + (rr > 0 ? 1 : 0);
+        const int lk = r - k0;
+        // The run is processed two particles at a time: their state loads are issued together
+        // (with the next two permutation entries), then they are pushed from registers in an
+        // unrolled sequence.  Global stores share the vector-memory counter with loads, so a load
+        // whose value is still in flight across a loop iteration makes the compiler wait for all
+        // earlier stores too; keeping every loaded value inside one iteration lets it wait for
+        // the loads alone.  Loads are issued unconditionally (slots past a lane's run read a
+        // location inside the state arrays, and their values go unused): a load under a divergent
+        // branch also forces a full wait.
+        constexpr int kChunk = 2;
+        Pstate<MIXED> cb[kChunk];
+        int cp_[kChunk], np_[kChunk];
+        T cw_[kChunk];
+        // A chunk's permutation entries come in one 8-byte load per lane (the array is padded
+        // so the load stays inside it); entries past the lane's run are clamped to a location
+        // inside the state arrays and their particles go unused.
+        static_assert(kPermPad >= 2 * kChunk, "one int2 of entries per chunk");
+        auto perm2 = [&](int first, int out[kChunk]) {
+          int2 v;
+          __builtin_memcpy(&v, perm + first, sizeof(v));
+          out[0] = (int)min((uint32_t)v.x, loc_max);
+          out[1] = (int)min((uint32_t)v.y, loc_max);
+        };
+        perm2(start, np_);
+        for (int c0 = 0; c0 < iters; c0 += kChunk) {
 #pragma unroll
-              for (int qq = 0; qq < 3; ++qq)
-                Ep[qq] = fmaT(W3, fE[4 * qq + 3],
-                              fmaT(W2, fE[4 * qq + 2], fmaT(W1, fE[4 * qq + 1], W0 * fE[4 * qq])));
-              // implicit push: with a = u + beta E and b = beta B / gamma,
-              // u-bar = R a = (a + a x b + (a.b) b) / (1 + b.b), and u' = 2 u-bar - u
-              const T bg = K.beta * ginv;
-              const T bx = bg * fB0, by = bg * fB1, bz = bg * fB2;
-              const T a0 = fmaT(K.beta, Ep[0], u0), a1 = fmaT(K.beta, Ep[1], u1);
-              const T a2 = fmaT(K.beta, Ep[2], u2);
-              const T inv = rcpT(fmaT(bz, bz, fmaT(by, by, fmaT(bx, bx, one))));
-              const T ab = fmaT(a2, bz, fmaT(a1, by, a0 * bx));
-              const T n0 = fmaT(T(2), fmaT(ab, bx, a0 + fmaT(a1, bz, -(a2 * by))) * inv, -u0);
-              const T n1 = fmaT(T(2), fmaT(ab, by, a1 + fmaT(a2, bx, -(a0 * bz))) * inv, -u1);
-              const T n2 = fmaT(T(2), fmaT(ab, bz, a2 + fmaT(a0, by, -(a1 * bx))) * inv, -u2);
-              const T g1sq = fmaT(n2, n2, fmaT(n1, n1, fmaT(n0, n0, one)));
-              const T rg1 = rsqT(g1sq);  // 1 / gamma(u^{n+1})
-              const T vx = n0 * rg1, vz = n2 * rg1;
-              // position advance: FP64 in cell units; mixed as FP32 offset with integer carry
-              T xn, zn;
-              int i2, k2;
-              bool alive = ok;
-              bool finite;
-              if constexpr (MIXED) {
-                xn = fx + cxT * vx;
-                zn = fz + czT * vz;
-                finite = isfinite(g1sq) && isfinite(xn) && isfinite(zn);
-                const int cxi = finite ? (int)floorT(xn) : 0, czi = finite ? (int)floorT(zn) : 0;
-                xn -= (T)cxi;
-                zn -= (T)czi;
-                int ci = i + cxi, ck = k + czi;
-                if (xn >= one) { xn = T(0); ci += 1; }
-                if (zn >= one) { zn = T(0); ck += 1; }
-                if (g.bc_x == PIC_BC_PERIODIC) {
-                  ci = wrap1(ci, g.nx);
-                } else if (ci < 0 || ci >= g.nx) {
-                  alive = false;
-                }
-                ck = wrap1(ck, g.nz);
-                i2 = ci;
-                k2 = ck;
-              } else {
-                xn = ps.x + g.cx * vx;
-                zn = ps.z + g.cz * vz;
-                if (g.bc_x == PIC_BC_PERIODIC) {
-                  if (xn < 0.0) xn += (double)g.nx;
-                  if (xn >= (double)g.nx) xn -= (double)g.nx;
-                } else if (xn < 0.0 || xn >= (double)g.nx) {
-                  alive = false;
-                }
-                if (zn < 0.0) zn += (double)g.nz;
-                if (zn >= (double)g.nz) zn -= (double)g.nz;
-                finite = isfinite(g1sq) && isfinite(xn) && isfinite(zn);
-                i2 = finite ? (int)floor(xn) : i;
-                k2 = finite ? (int)floor(zn) : k;
-              }
-              if (ok && !finite) atomicOr(a.flags, kFlagNonFinite);
-              alive = alive && finite;
-              int di = i2 - i, dk = k2 - k;
-              if (di > 1) di -= g.nx;
-              if (di < -1) di += g.nx;
-              if (dk > 1) dk -= g.nz;
-              if (dk < -1) dk += g.nz;
-              const bool jump = di < -1 || di > 1 || dk < -1 || dk > 1;
-              if (alive && jump) atomicOr(a.flags, kFlagJump);
-              alive = alive && !jump;
-              if (!alive) {
-                di = 0;
-                dk = 0;
-              }
-              const uint32_t code = alive ? (uint32_t)((dk + 1) * 3 + (di + 1)) : kAbsorbed;
-              // moments M^{n+3/2} at x^{n+3/2} with u^{n+1}, 1/gamma(u^{n+1}) and H^{n+3/2}
-              // of the new cell (read before any LDS atomic of this particle is issued)
-              const int hn = (lk + dk + 1) * Lo.NW + (li + di + 1);
-              m = compact_moments(K, rg1, n0, n1, n2, Hn[hn], Hn[Lo.NPL + hn], Hn[2 * Lo.NPL + hn]);
-              // the new cell, tile-local (a dead particle stays, unused)
-              const int ldx = li + di, ldz = lk + dk;
-              const bool inside = ldx >= 0 && ldx < cw && ldz >= 0 && ldz < chh;
-              if constexpr (PW) scale_compact(m, wp);
-              if constexpr (MIXED) {
-                fx2 = xn;
-                fz2 = zn;
-              } else {
-                fx2 = xn - (double)i2;
-                fz2 = zn - (double)k2;
-              }
-              if (newcell) {
-                if constexpr (!kDirect) {
-                  if (ca.cell >= 0) ca.flush(acc, lz, dplane);
-                  ca.clear();
-                }
-                ca.cell = li;
-              }
-              if constexpr (MIXED) {
-                if (ok) {
-                  const int loc = jb + it * 64 + lane;
-                  sp.mdst_cell[loc] = k2 * g.nx + i2;
-                  sp.mdst[0][loc] = xn;
-                  sp.mdst[1][loc] = zn;
-                  sp.mdst[2][loc] = n0;
-                  sp.mdst[3][loc] = n1;
-                  sp.mdst[4][loc] = n2;
-                  if (PW && wstride) wdst[loc] = wp;
-                  sp.locode[j] = ((uint32_t)loc << 4) | code;
-                }
-              } else {
-                // FP64: every lane issues the stores, without a branch (a lane without a
-                // particle passes an offset the hardware drops), so the compiler knows how many
-                // stores each particle issues and waits for the next particle's loads alone.
-                // (The mixed form measured no gain from this and keeps plain stores.)
-                const int loc = jb + it * 64 + lane;
-                store_or_drop(sp.dst[0], loc, ok, xn);
-                store_or_drop(sp.dst[1], loc, ok, zn);
-                store_or_drop(sp.dst[2], loc, ok, n0);
-                store_or_drop(sp.dst[3], loc, ok, n1);
-                store_or_drop(sp.dst[4], loc, ok, n2);
-                if constexpr (PW) store_or_drop(wdst, loc, ok && wstride != 0, wp);
-                store_or_drop(sp.locode, j, ok, ((uint32_t)loc << 4) | code);
-              }
+          for (int kk = 0; kk < kChunk; ++kk) {
+            cp_[kk] = np_[kk];
+            cb[kk].load(src, cp_[kk]);
+            if constexpr (PW) cw_[kk] = wsrc[cp_[kk] * wstride];
+          }
+          perm2(start + c0 + kChunk, np_);
+#pragma unroll
+          for (int kk = 0; kk < kChunk; ++kk) {
+            const int it = c0 + kk;
+            if (it >= iters) break;
+            const bool act = it < my_n;
+            const int j = start + it;
+            const int p = cp_[kk];
+            const Pstate<MIXED> &ps = cb[kk];
+            int i, k;
+            T fx, fz;
+            if constexpr (MIXED) {
+              k = r;
+              i = ps.cell - r * g.nx;
+              fx = ps.x;
+              fz = ps.z;
+            } else {
+              const double xf = floor(ps.x), zf = floor(ps.z);
+              i = (int)xf;
+              k = (int)zf;
+              fx = ps.x - xf;
+              fz = ps.z - zf;
+            }
+            const T wp = PW ? cw_[kk] : K.w;  // the particle's density
+            const bool ok = act && k == r && i >= i0 && i < i1;
+            const int loc = jb + it * 64 + lane;
+            if (act && !ok) drop_slot(j, (uint32_t)loc);
+            // Lanes without a valid particle run the arithmetic on the tile's first cell and
+            // discard the results, so the main path has no branches around it.
+            const int li = ok ? i - i0 : 0;
+            const int hc = lk * t.tx + li;
+            // The fields are read from LDS for every particle (a lane holds about two per row,
+            // and fields kept across particles would hold about 30 registers).
+            T fB[3], fE[12];
+#pragma unroll
+            for (int qq = 0; qq < 3; ++qq) fB[qq] = Ho[qq * Lo.HPL + hc];
+            const int e00 = lk * Lo.EW + li;
+#pragma unroll
+            for (int qq = 0; qq < 3; ++qq) {
+              const T *f = Eb + qq * Lo.EPL + e00;
+              fE[4 * qq] = f[0];
+              fE[4 * qq + 1] = f[1];
+              fE[4 * qq + 2] = f[Lo.EW];
+              fE[4 * qq + 3] = f[Lo.EW + 1];
+            }
+            Pushed<T> o;
+            push_one<MIXED>(g, K, ps, i, k, fx, fz, fE, fB, edge, ok, o);
+            if (ok && !o.finite) atomicOr(a.flags, kFlagNonFinite);
+            if (o.jump) atomicOr(a.flags, kFlagJump);
+            const bool alive = o.alive;
+            const uint32_t code = alive ? (uint32_t)((o.dk + 1) * 3 + (o.di + 1)) : kAbsorbed;
+            // moments M^{n+3/2} at x^{n+3/2} with u^{n+1}, 1/gamma(u^{n+1}) and H^{n+3/2}
+            // of the new cell (read before any LDS atomic of this particle is issued)
+            const int hn = (lk + o.dk + 1) * Lo.NW + (li + o.di + 1);
+            Compact<T> m = compact_moments(K, o.rg1, o.n0, o.n1, o.n2, Hn[hn], Hn[Lo.NPL + hn], Hn[2 * Lo.NPL + hn]);
+            // the new cell, tile-local (a dead particle stays, unused)
+            const int ldx = li + o.di, ldz = lk + o.dk;
+            const bool inside = ldx >= 0 && ldx < cw && ldz >= 0 && ldz < chh;
+            if constexpr (PW) scale_compact(m, wp);
+            if constexpr (MIXED) {
               if (ok) {
-                // particle ids (tests only): a separate instantiation, so that its load, which
-                // is waited for at once, does not enter the wait counts of the kernel without ids
-                if (IDS && sp.dst_id) sp.dst_id[jb + it * 64 + lane] = sp.src_id[p];
-                if (code != kAbsorbed) atomicAdd(&cntS[hc * kMoveCodes + code], 1);
+                sp.mdst_cell[loc] = o.k2 * g.nx + o.i2;
+                sp.mdst[0][loc] = o.xn;
+                sp.mdst[1][loc] = o.zn;
+                sp.mdst[2][loc] = o.n0;
+                sp.mdst[3][loc] = o.n1;
+                sp.mdst[4][loc] = o.n2;
+                if (PW && wstride) wdst[loc] = wp;
+                sp.locode[j] = ((uint32_t)loc << 4) | code;
               }
-              // stayers add to the lane's accumulator, movers go through the queue (with few
-              // particles per lane every particle goes to the LDS accumulators at once, or to
-              // the global planes if it leaves the tile)
-              if constexpr (kDirect) {
-                if (alive && inside)
-                  deposit_one(acc, ldz * LW + ldx, ldz * t.tx + ldx, fx2, fz2, m, wp, dplane);
-                if (alive && !inside)
-                  deposit_global(a, i2, k2, fx2, fz2, m, wp, Hn[hn], Hn[Lo.NPL + hn],
-                                 Hn[2 * Lo.NPL + hn], dplane);
-              } else if (alive && code == 4u) {
-                ca.add(fx2, fz2, m, wp);
-              } else if (alive) {
-                mover = true;
-                mo = (lz + dk) * LW + (li + 1 + di);
-                mh = hn;
-              }
+            } else {
+              // FP64: every lane issues the stores, without a branch (a lane without a
+              // particle passes an offset the hardware drops), so the compiler knows how many
+              // stores each particle issues and waits for the next particle's loads alone.
+              // (The mixed form measured no gain from this and keeps plain stores.)
+              store_or_drop(sp.dst[0], loc, ok, o.xn);
+              store_or_drop(sp.dst[1], loc, ok, o.zn);
+              store_or_drop(sp.dst[2], loc, ok, o.n0);
+              store_or_drop(sp.dst[3], loc, ok, o.n1);
+              store_or_drop(sp.dst[4], loc, ok, o.n2);
+              if constexpr (PW) store_or_drop(wdst, loc, ok && wstride != 0, wp);
+              store_or_drop(sp.locode, j, ok, ((uint32_t)loc << 4) | code);
             }
-            // queue this iteration's movers; drain first if they would not fit
-            const uint64_t mmask = __ballot(mover);
-            const int nm = __popcll(mmask);
-            if (nq + nm > kMqCap) {
-              wave_sync();
-              drain_movers<T, PW>(mq, nq, lane, acc, dplane, K.w);
-              wave_sync();
-              nq = 0;
+            if (IDS && ok && sp.dst_id) sp.dst_id[loc] = sp.src_id[p];
+            if (ok && code != 4u) {
+              atomicSub(&cntS[4 * ntc + hc], 1);
+              if (alive) atomicAdd(&cntS[code * ntc + hc], 1);
             }
-            if (mover) {
-              const int e = nq + __popcll(mmask & lt_mask);
-              mq.v[0 * kMqCap + e] = fx2;
-              mq.v[1 * kMqCap + e] = fz2;
-              mq.v[2 * kMqCap + e] = m.a0;
-              mq.v[3 * kMqCap + e] = m.a1;
-              mq.v[4 * kMqCap + e] = m.a2;
-              mq.v[5 * kMqCap + e] = m.j0;
-              mq.v[6 * kMqCap + e] = m.j1;
-              mq.v[7 * kMqCap + e] = m.j2;
-              if constexpr (PW) mq.v[8 * kMqCap + e] = wp;
-              mq.idx[e] = mo;
-              mq.idx[kMqCap + e] = mh;
-            }
-            nq += nm;
+            // every particle goes to the LDS accumulators at once, or to the global planes if
+            // it leaves the tile
+            if (alive && inside)
+              deposit_one(acc, ldz * LW + ldx, ldz * t.tx + ldx, o.fx, o.fz, m, wp, dplane);
+            if (alive && !inside)
+              deposit_global(a, o.i2, o.k2, o.fx, o.fz, m, wp, Hn[hn], Hn[Lo.NPL + hn],
+                             Hn[2 * Lo.NPL + hn], dplane);
           }
         }
-      }
-      if constexpr (!kDirect) ca.flush_row_end(acc, lz, dplane, lane);
-      if (PUSH && nq > 0) {
-        wave_sync();
-        drain_movers<T, PW>(mq, nq, lane, acc, dplane, K.w);
-        wave_sync();
       }
     }
   }
   __syncthreads();
   // Move counts of the tile's cells, for the ranking.  The counts of every species are kept
-  // until here, so the species need no barriers between them.
+  // until here, so the species need no barriers between them.  With code masks only the nonzero
+  // counts are written (most cells send all their particles with one code).  The grouped form's
+  // blocks have more threads than cells: one thread per (code, cell) pair (2.4 -> 1.2 us of a
+  // 32 x 2 tile's time against one per cell, which the direct form keeps).
+  if constexpr (PUSH && !DIRECT) {
+    const SmallDiv div_ntc(ntc), div_tx(t.tx);
+    for (int s = 0; s < a.nsp; ++s) {
+      const SpeciesArgs &sp = a.sp[s];
+      if (!sp.active) continue;
+      const int *cntS = cntL + s * ntc * kMoveCodes;
+      int *arrS = arrL + s * AW * AH;
+      for (int e = threadIdx.x; e < kMoveCodes * ntc; e += blockDim.x) {
+        const int d = div_ntc.q(e), c = e - d * ntc;
+        const int lkk = div_tx.q(c), li = c - lkk * t.tx;
+        const int v = cntS[e];
+        if (li >= cw || lkk >= chh) continue;
+        if (!a.count_masks || v) sp.cnt[(int64_t)d * nc + (int64_t)(k0 + lkk) * g.nx + (i0 + li)] = v;
+        const int dz = d >= 6 ? 2 : d >= 3 ? 1 : 0;
+        if (v) atomicAdd(&arrS[(lkk + dz) * AW + (li + d - 3 * dz)], v);
+      }
+      if (!a.count_masks) continue;
+      for (int c = threadIdx.x; c < ntc; c += blockDim.x) {
+        const int lkk = div_tx.q(c), li = c - lkk * t.tx;
+        uint32_t mask = 0;
+#pragma unroll
+        for (int d = 0; d < kMoveCodes; ++d) mask |= cntS[d * ntc + c] ? 1u << d : 0u;
+        if (li < cw && lkk < chh) sp.cmask[(int64_t)(k0 + lkk) * g.nx + (i0 + li)] = (uint16_t)mask;
+      }
+    }
+  }
   for (int s = 0; s < a.nsp; ++s) {
     const SpeciesArgs &sp = a.sp[s];
-    if (!PUSH || !sp.active) continue;
+    if (!DIRECT || !sp.active) continue;
     const int *cntS = cntL + s * ntc * kMoveCodes;
-    int *arrS = arrL + s * AW * AH;
     {
       const SmallDiv div_cw(cw);
       for (int e = threadIdx.x; e < chh * cw; e += blockDim.x) {
         const int lkk = div_cw.q(e), li = e - lkk * cw;
         const int64_t cg = (int64_t)(k0 + lkk) * g.nx + (i0 + li);
-        const int *cl = cntS + (lkk * t.tx + li) * kMoveCodes;
+        const int *cl = cntS + lkk * t.tx + li;
         uint32_t mask = 0;
 #pragma unroll
         for (int d = 0; d < kMoveCodes; ++d) {
-          const int v = cl[d];
-          // with code masks only the nonzero counts are written (most cells send all their
-          // particles with one code)
+          const int v = cl[d * ntc];
           if (!a.count_masks || v) sp.cnt[(int64_t)d * nc + cg] = v;
-          if (v) {
-            mask |= 1u << d;
-            if constexpr (!kTileOnly) atomicAdd(&arrS[(lkk + d / 3) * AW + (li + d % 3)], v);
-          }
+          if (v) mask |= 1u << d;
         }
         if (a.count_masks) sp.cmask[cg] = (uint16_t)mask;
       }
@@ -1259,7 +1395,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   // cells around the node, each expanded with its cell's B (H^{n+3/2} after a push, H^{n+1/2}
   // for a deposit of the current state): S-hat = a0 I + a1 [B]x + a2 B B^T.
   const SmallDiv div_lw(LW);
-  for (int idx = threadIdx.x; idx < plane; idx += blockDim.x) {
+  for (int idx = threadIdx.x; idx < LW * Lo.LH; idx += blockDim.x) {
     const int lzz = div_lw.q(idx), lx = idx - lzz * LW;
     constexpr int kOff = kTileOnly ? 0 : 1;  // the ring's column and row before the tile
     int gx = i0 - kOff + lx;
@@ -1342,7 +1478,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
 #pragma unroll
           for (int d = 0; d < kMoveCodes; ++d) {
             const int sx = ax - d % 3, sz = az - d / 3;  // the source cell, tile-local
-            if (sx >= 0 && sx < cw && sz >= 0 && sz < chh) v += cntS[(sz * t.tx + sx) * kMoveCodes + d];
+            if (sx >= 0 && sx < cw && sz >= 0 && sz < chh) v += cntS[d * ntc + sz * t.tx + sx];
           }
         } else {
           v = arrS[e];
@@ -1357,19 +1493,16 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   }
 }
 
-// Waves per SIMD: the register sums of the chunks of 4 hold two FP64 waves (three mixed); the
-// chunk-of-2 form, without them, holds four in both precisions (at 32 x 4 cells and two
-// species its LDS also lets four blocks share a CU).
-template <bool PUSH, bool MIXED, bool IDS, bool PW, int CH = 4>
-__global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(CH == 2 ? 4 : 2 + MIXED, CH == 2 ? 4 : 2 + MIXED)))
+// Four waves per SIMD in every form (at most 128 VGPRs).
+template <bool PUSH, bool MIXED, bool IDS, bool PW, bool DIRECT = false>
+__global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_particles(const StepArgs a) {
   // clear the next order's tile flags (set by the scan of this cycle's sort); the grid has a
   // block for every tile index
   if (threadIdx.x == 0 && (int)blockIdx.x < a.t.ntiles) a.tile_active_next[blockIdx.x] = 0;
   const int tile = block_tile(a.t, a.tile_list);
   if (tile < 0) return;
-  particles_body<PUSH, MIXED, IDS, PW, CH>(a, tile);
+  particles_body<PUSH, MIXED, IDS, PW, DIRECT>(a, tile);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2111,7 +2244,7 @@ __device__ __forceinline__ int batch_item(int total) {
 }
 
 template <bool MIXED, bool IDS, bool PW>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2 + MIXED, 2 + MIXED)))
+__global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void kb_particles(const BatchArgs b) {
   const int w = batch_item(b.pre_tiles[b.nruns]);
   if (w < 0) return;
@@ -2183,9 +2316,8 @@ __global__ void k_iota(int32_t *p, int64_t n) {
 
 }  // namespace
 
-size_t particle_lds_bytes(const GridArgs &g, const TileArgs &t, bool mixed, bool pw, bool queues) {
-  return TileLds(g.n_planes, t.tx, t.tz, mixed ? (int)sizeof(float) : (int)sizeof(double),
-                 queues ? mq_words(pw) : 0).bytes;
+size_t particle_lds_bytes(const GridArgs &g, const TileArgs &t, bool mixed, int waves) {
+  return TileLds(g.n_planes, t.tx, t.tz, mixed ? (int)sizeof(float) : (int)sizeof(double), waves).bytes;
 }
 
 size_t rank_lds_bytes(const TileArgs &t) {
@@ -2208,24 +2340,25 @@ hipError_t launch_field_solve(const FieldArgs &a, hipStream_t s) {
 template <bool PUSH, bool MIXED>
 static void launch_particles_t(const StepArgs &a, bool ids, bool pw, dim3 grid, size_t lds,
                                hipStream_t s) {
-  // the pushing kernels without ids in the two-particle chunk form (few particles per lane)
+  const dim3 blk(64u * (unsigned)a.waves);
+  // the pushing kernels without ids in the direct form (few particles per lane)
   if constexpr (PUSH) {
-    if (!ids && a.chunk2) {
+    if (!ids && a.direct) {
       if (pw)
-        hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, true, 2>), grid, dim3(kBlock), lds, s, a);
+        hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, true, true>), grid, blk, lds, s, a);
       else
-        hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, false, 2>), grid, dim3(kBlock), lds, s, a);
+        hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, false, true>), grid, blk, lds, s, a);
       return;
     }
   }
   if (PUSH && ids && pw)
-    hipLaunchKernelGGL((k_particles<PUSH, MIXED, PUSH, true>), grid, dim3(kBlock), lds, s, a);
+    hipLaunchKernelGGL((k_particles<PUSH, MIXED, PUSH, true>), grid, blk, lds, s, a);
   else if (PUSH && ids)
-    hipLaunchKernelGGL((k_particles<PUSH, MIXED, PUSH, false>), grid, dim3(kBlock), lds, s, a);
+    hipLaunchKernelGGL((k_particles<PUSH, MIXED, PUSH, false>), grid, blk, lds, s, a);
   else if (pw)
-    hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, true>), grid, dim3(kBlock), lds, s, a);
+    hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, true>), grid, blk, lds, s, a);
   else
-    hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, false>), grid, dim3(kBlock), lds, s, a);
+    hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, false>), grid, blk, lds, s, a);
 }
 
 hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t s) {
@@ -2234,8 +2367,8 @@ hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t s) {
     ids = ids || a.sp[q].dst_id != nullptr;
     pw = pw || (a.sp[q].active && a.sp[q].w_stride != 0);
   }
-  // the chunk-of-2 pushing form has no mover queues
-  const size_t lds = particle_lds_bytes(a.g, a.t, a.mixed != 0, pw, !(push && a.chunk2 && !ids));
+  // the direct form has no staging
+  const size_t lds = particle_lds_bytes(a.g, a.t, a.mixed != 0, push && a.direct && !ids ? 0 : a.waves);
   const dim3 grid(8u * (unsigned)a.t.per_xcd);
   if (a.mixed) {
     if (push) launch_particles_t<true, true>(a, ids, pw, grid, lds, s);
@@ -2292,7 +2425,8 @@ hipError_t launch_batch_cycle(const BatchArgs &b, const BatchLaunch &l, hipStrea
                      s, b, l.items_cells);
   hipLaunchKernelGGL(kb_prefix, dim3(1), dim3(1024), 0, s, b);
   const dim3 gp((unsigned)l.grid_particles);
-  hipLaunchKernelGGL(batch_particles_kernel(l.mixed, l.ids, l.pw), gp, blk, l.lds_particles, s, b);
+  hipLaunchKernelGGL(batch_particles_kernel(l.mixed, l.ids, l.pw), gp, dim3(64u * (unsigned)l.waves),
+                     l.lds_particles, s, b);
   // the scans' items are fixed between rebuilds: a block per item (the kernels' loops then run
   // once per block)
   hipLaunchKernelGGL(kb_scan1, dim3((unsigned)std::max(1, l.items_scan)), blk, 0, s, b);

@@ -1,0 +1,64 @@
+"""The particle kernel's two forms where they can go wrong, against the oracle at 1e-10.
+
+The grouped form takes 64 slots per wavefront and sums them per cell through the matrix cores, 16
+lanes at a time: particle counts around multiples of 16 and 64 per cell, cells without particles
+in between, tiles of one cell to the widest, and hot plasmas in which a third of the particles
+change cell every cycle.  The direct form is chosen at few particles per cell on grids of many
+tiles.  Runs without labels use their own kernel instantiations, so both are run.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import picgen
+from tests.test_gpu_parity import check_fields, check_moments, check_particles, setup_both
+from tests.test_gpu_parity import pic  # noqa: F401  -- fixture
+
+pytestmark = pytest.mark.gpu
+
+
+def thin(wl, keep):
+    """Only every keep-th cell column occupied."""
+    for sp in wl.species:
+        on = np.floor(sp.xi_x).astype(int) % keep == 0
+        for k in ("xi_x", "xi_z", "ux", "uy", "uz"):
+            setattr(sp, k, np.ascontiguousarray(getattr(sp, k)[on]))
+    return wl
+
+
+@pytest.mark.parametrize("ids", [True, False])
+@pytest.mark.parametrize("tile", [(0, 0), (1, 1), (5, 3), (8, 4), (64, 1)])
+@pytest.mark.parametrize("ppc,te,keep", [(1, 5.0, 1), (15, 5.0, 3), (16, 200.0, 1), (17, 200.0, 2),
+                                         (64, 5.0, 1), (65, 200.0, 4)])
+def test_grouped_form(pic, ppc, te, keep, tile, ids):  # noqa: F811
+    wl = picgen.random_small(70 + ppc, nx=37, nz=11, ppc=ppc, bc_x=ppc % 2, dx=0.5, dz=0.4, dt=0.4,
+                             temps=(te, 0.5))
+    if keep > 1:
+        thin(wl, keep)
+    print(f"[gpu-case] grouped ppc={ppc} te={te} keep={keep} tile={tile} ids={ids}", flush=True)
+    ctx, orc = setup_both(pic, wl, fields=picgen.random_fields(ppc, wl.grid), tile=tile, track_ids=ids)
+    check_moments(ctx, orc)
+    ctx.step(2)
+    orc.step(2)
+    check_fields(ctx, orc)
+    check_moments(ctx, orc)
+    check_particles(ctx, orc, wl, ids=ids)
+    assert ctx.get_info()["overflow_flags"] == 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("nx,nz,ppc,te", [(39, 1037, 3, 200.0), (16, 1026, 9, 1.0)])
+def test_direct_form(pic, nx, nz, ppc, te, bc):  # noqa: F811
+    wl = picgen.random_small(90 + ppc, nx=nx, nz=nz, ppc=ppc, bc_x=bc, dx=0.5, dz=0.4, dt=0.4,
+                             temps=(te, 0.5))
+    print(f"[gpu-case] direct {nx}x{nz} ppc={ppc} te={te} bc={bc}", flush=True)
+    ctx, orc = setup_both(pic, wl, fields=picgen.random_fields(3, wl.grid), track_ids=False)
+    ctx.step(2)
+    orc.step(2)
+    check_fields(ctx, orc)
+    check_moments(ctx, orc)
+    check_particles(ctx, orc, wl, ids=False)
+    assert ctx.get_info()["overflow_flags"] == 0
+    ctx.close()
