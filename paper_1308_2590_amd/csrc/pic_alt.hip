@@ -7,8 +7,8 @@
 //                    the particle), the implicit push of Eq. (2), position advance and move
 //                    code, then the deposit of S-hat, delta-j and density (Step 1, Eq. (3)) at
 //                    the new position with the same options, into the global moment planes with
-//                    FP64 atomics, each first summed over the lanes of a wavefront that
-//                    deposit into the same cell.  It writes the move codes, counts and arrivals
+//                    FP64 atomics, each value first summed over a block's particles per cell
+//                    (matrix cores, then LDS) and over the cells around a node.  It writes the move codes, counts and arrivals
 //                    the cycle's sort reads, exactly as the tile kernel does.  Without push it
 //                    deposits the current state.
 //   k_energy         field energy (1/2)(sum |E|^2 over nodes + sum |H|^2 over cells) dx dz and
@@ -121,35 +121,135 @@ __device__ void moments13(const SpeciesArgs &sp, double gam, const double u[3], 
 }
 
 // The threads of a wavefront follow the cell-sorted order, so lanes that add to the same
-// addresses (one cell's nodes, counter or arrival count) are neighbours.  Their values are
-// summed over each run of equal keys (a segmented reduction towards the run's first lane) and
-// the first lane issues one global atomic per value: same-address atomics from the lanes of
-// one cell would otherwise be serialised.  All 64 lanes take part; a lane without a value has
-// a key of its own (negative).
-struct Seg {
-  int lane, seg_end, steps;
-  bool head;
+// addresses (one cell's nodes, counter or arrival count) are neighbours, and their contributions
+// are summed before one global atomic per value: same-address atomics from the lanes of one cell
+// would be serialised.  The moments, 4 corner weights times 13 values per particle, are contracted
+// over the particles of a cell with v_mfma_f64_4x4x4_4b (lane 16 k + 4 b + i holds A[i][k] and
+// B[k][i] of block b and receives D[i][j] in lane 16 i + 4 b + j), four instructions per round of
+// four particles of each block of 16 lanes.  (Segmented sums by lane shuffles, 52 values times up
+// to six steps of two 32-bit LDS permutes each, were bound by the LDS: 91 us for 524,288
+// particles at 16 per cell, 52 us now with the accumulators below.)
+constexpr int kAltPlanes = 15;  // f_x, f_z, the 13 values
+constexpr int kAltPitch = 68;   // particle P at P + P / 16: the 16 lanes of an LDS pass hit 16 banks
+constexpr int kAltWaveBytes = kAltPlanes * kAltPitch * 8 + 2 * 64 * 4 * 4 + 2 * 64 + 2 * 64 * 4;
+// A block's particles lie in consecutive cells; where those are at most kAltCells, the sums go to
+// LDS accumulators per (cell, corner, value) first and from there to the nodes, each value once
+// per block: the global atomics, executed at the memory side, were half of the kernel's time
+// (16 particles per cell: 96 us with one set per wavefront block and cell, 44 without any).
+constexpr int kAltCells = 24;
+constexpr int kAltVals = 13;
+
+struct AltStage {
+  double *v;        // [kAltPlanes][kAltPitch]
+  uint32_t *seg;    // [64][4]: corner nodes of the cell of pass p of block b at 16 b + p
+  uint32_t *mov;    // [64][4]: corner nodes of mover m
+  int *segc, *movc; // [64]: the cells
+  uint8_t *movq;    // [64]: the mover's place in the planes
+  uint8_t *pass;    // [64]: pass of particle 16 b + 4 t + k at 16 b + 4 k + t (255: none)
+  __device__ __forceinline__ explicit AltStage(char *p)
+      : v(reinterpret_cast<double *>(p)),
+        seg(reinterpret_cast<uint32_t *>(p + kAltPlanes * kAltPitch * 8)),
+        mov(seg + 256),
+        segc(reinterpret_cast<int *>(mov + 256)),
+        movc(segc + 64),
+        movq(reinterpret_cast<uint8_t *>(movc + 64)),
+        pass(movq + 64) {}
 };
 
-__device__ __forceinline__ Seg seg_of(int64_t key) {
+// Deposit of a wavefront's particles, one per lane: val = f_x, f_z and the 13 values (dep lanes).
+// act: lanes with a slot; stay: the particle deposits in the cell its slot is in (node_src: its
+// corner nodes), otherwise, if dep, in another (node_dst).  head_b: first lane of its cell in its
+// block of 16.  A pass takes one cell per block, the other particles' weights masked to zero;
+// movers go one by one, four at a time (16 lanes: corner, value).  acc: the block's accumulators,
+// for the cells c0 .. c0 + span - 1 (span 0: none), everything else goes to the planes M.
+__device__ __forceinline__ void alt_deposit(const AltStage &st, bool act, bool dep, bool stay, bool head_b,
+                                            int src, int dst, const uint32_t node_src[4],
+                                            const uint32_t node_dst[4], const double val[kAltPlanes],
+                                            double *M, int64_t nn, int splane, double *acc, int c0,
+                                            int span) {
   const int lane = threadIdx.x & 63;
-  const int64_t prev = __shfl_up(key, 1, 64);
-  const bool head = lane == 0 || prev != key;
-  const uint64_t heads = __ballot(head);
-  const uint64_t above = heads & ~((2ull << lane) - 1ull);
-  Seg sg{lane, above ? __ffsll((unsigned long long)above) - 1 : 64, 0, head};
-  while (sg.steps < 6 && __any(lane + (1 << sg.steps) < sg.seg_end)) ++sg.steps;
-  return sg;
+  const int mi = lane & 3, mb = (lane >> 2) & 3, mk4 = lane >> 4;
+  const int ob = lane >> 4, ol = lane & 15, own = lane + (lane >> 4);
+  const bool mover = dep && !stay;
+  const uint64_t heads = __ballot(act && head_b), movers = __ballot(mover);
+  auto in_block = [](uint64_t m, int b) { return (uint32_t)(m >> (16 * b)) & 0xffffu; };
+  const int seg = __popc(in_block(heads, ob) & ((2u << ol) - 1u)) - 1;
+  const int mseq = __popcll(movers & ((1ull << lane) - 1ull));
+  if (act && head_b) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) st.seg[(ob * 16 + seg) * 4 + c] = node_src[c];
+    st.segc[ob * 16 + seg] = src;
+  }
+  if (mover) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) st.mov[mseq * 4 + c] = node_dst[c];
+    st.movq[mseq] = (uint8_t)own;
+    st.movc[mseq] = dst;
+  }
+  st.pass[ob * 16 + (ol & 3) * 4 + (ol >> 2)] = (uint8_t)(dep && stay ? seg : 255);
+#pragma unroll
+  for (int q = 0; q < kAltPlanes; ++q) st.v[q * kAltPitch + own] = dep ? val[q] : 0.0;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  int n_pass = 0;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) n_pass = max(n_pass, __popc(in_block(heads, b)));
+  const int n_mine = __popc(in_block(heads, mb)), n_movers = __popcll(movers);
+  // value 4 q + j of this lane's column j (the fourth set holds the density alone), its plane
+  int pl[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) pl[q] = (2 + min(4 * q + mi, 12)) * kAltPitch;
+  // value 4 q + j at corner c of cell `cell` (node n): to the block's accumulators or the planes
+  auto add = [&](int q, int c, int cell, uint32_t n, double v) {
+    if (q == 3 && mi != 0) return;
+    const uint32_t l = (uint32_t)(cell - c0);
+    if (l < (uint32_t)span)
+      atomicAdd(&acc[(l * 4 + c) * kAltVals + 4 * q + mi], v);
+    else
+      unsafeAtomicAdd(M + (int64_t)(q < 3 ? 4 * q + mi : splane) * nn + n, v);
+  };
+  {
+    const int at = mb * 17 + mk4;
+    const uint32_t pass4 = *reinterpret_cast<const uint32_t *>(st.pass + 16 * mb + 4 * mk4);
+    double A[4], B[4][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const double fx = st.v[at + 4 * t], fz = st.v[kAltPitch + at + 4 * t];
+      A[t] = ((mi & 1) ? fx : 1.0 - fx) * ((mi & 2) ? fz : 1.0 - fz);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) B[q][t] = st.v[pl[q] + at + 4 * t];
+    }
+    for (int p = 0; p < n_pass; ++p) {
+      const int ps = mb * 16 + min(p, max(n_mine - 1, 0));
+      const uint32_t n = st.seg[ps * 4 + mk4];
+      const int cell = st.segc[ps];
+      double d[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const double w = ((pass4 >> (8 * t)) & 255u) == (uint32_t)p ? A[t] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d[q] = __builtin_amdgcn_mfma_f64_4x4x4f64(w, B[q][t], d[q], 0, 0, 0);
+      }
+      if (p < n_mine) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) add(q, mk4, cell, n, d[q]);
+      }
+    }
+  }
+  for (int m = mk4; m < n_movers; m += 4) {
+    const int q0 = st.movq[m];
+    const uint32_t n = st.mov[m * 4 + mb];
+    const int cell = st.movc[m];
+    const double fx = st.v[q0], fz = st.v[kAltPitch + q0];
+    const double w = ((mb & 1) ? fx : 1.0 - fx) * ((mb & 2) ? fz : 1.0 - fz);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) add(q, mb, cell, n, w * st.v[pl[q] + q0]);
+  }
 }
 
-template <typename V>
-__device__ __forceinline__ V seg_sum(const Seg &sg, V v) {
-  for (int q = 0; q < sg.steps; ++q) {
-    const int d = 1 << q;
-    const V t = __shfl_down(v, d, 64);
-    if (sg.lane + d < sg.seg_end) v += t;
-  }
-  return v;
+// The same lane's value in the lane before (all 64 lanes active; lane 0 gets its own).
+__device__ __forceinline__ int alt_lane_before(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
 }
 
 template <bool PUSH>
@@ -170,13 +270,20 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   const int n = sp.cs[g.ncells];
   if ((int)(blockIdx.x * blockDim.x) >= n) return;  // the whole block past the particles
+  __shared__ __align__(16) char lds[(kBlock / 64) * kAltWaveBytes];
+  __shared__ double acc[kAltCells * 4 * kAltVals];
+  __shared__ int range[2];  // first and last cell of the block
+  const AltStage st(lds + (threadIdx.x >> 6) * kAltWaveBytes);
+  for (int e = threadIdx.x; e < kAltCells * 4 * kAltVals; e += blockDim.x) acc[e] = 0.0;
   const int lane = threadIdx.x & 63;
-  // what the lane adds: moments at 4 nodes (dep), a move count (cnt_on), an arrival
-  bool dep = false, cnt_on = false;
-  int64_t dkey = 0, ckey = 0, cidx = 0;
-  int64_t node[4] = {0, 0, 0, 0};
-  double W[4] = {0.0, 0.0, 0.0, 0.0}, v[13];
-  for (int r = 0; r < 13; ++r) v[r] = 0.0;
+  // the particle's old cell (act), whether it deposits (dep) and where: its old cell (stay) or not
+  bool act = false, dep = false, stay = false;
+  int src = -1, dst = -1;
+  uint32_t code = 4u;
+  uint32_t node_src[4] = {0u, 0u, 0u, 0u}, node_dst[4] = {0u, 0u, 0u, 0u};
+  double val[kAltPlanes];
+#pragma unroll
+  for (int r = 0; r < kAltPlanes; ++r) val[r] = 0.0;
   if (j < n) {
     const int p = sp.perm[j];
     const double x = sp.src[0][p], z = sp.src[1][p];
@@ -187,14 +294,23 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
       atomicOr(a.flags, kFlagOrderA);
       if (PUSH) sp.locode[j] = ((uint32_t)j << 4) | kAbsorbed;
     } else {
+      int64_t node[4];
+      double W[4], v[13];
       corners(g, i, k, x - (double)i, z - (double)k, node, W);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) node_src[c] = (uint32_t)node[c];
+      act = true;
+      src = dst = k * g.nx + i;
       double B[3];
       b_at(g, a.Hold, mover, x, z, i, k, B);
       const double gam = gamma_bar(g, a.Eold, mover, sp.beta, u, node, W);
       if (!PUSH) {
         moments13(sp, gam, u, B, wp, v);
-        dep = true;
-        dkey = (int64_t)k * g.nx + i;
+        dep = stay = true;
+        val[0] = x - (double)i;
+        val[1] = z - (double)k;
+#pragma unroll
+        for (int r = 0; r < 13; ++r) val[2 + r] = v[r];
       } else {
         // E-bar at the particle and the implicit push: a = u + beta E-bar, b = beta B / gamma-bar,
         // u-bar = (a + a x b + (a.b) b) / (1 + b.b), u' = 2 u-bar - u
@@ -237,7 +353,7 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
         const bool jump = di < -1 || di > 1 || dk < -1 || dk > 1;
         if (alive && jump) atomicOr(a.flags, kFlagJumpA);
         alive = alive && !jump;
-        const uint32_t code = alive ? (uint32_t)((dk + 1) * 3 + (di + 1)) : kAbsorbed;
+        code = alive ? (uint32_t)((dk + 1) * 3 + (di + 1)) : kAbsorbed;
         // the pushed state goes to location j of the other buffer; the sort reads the codes
         sp.dst[0][j] = xn;
         sp.dst[1][j] = zn;
@@ -248,10 +364,6 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
         if (sp.w_stride) sp.dst_w[j] = wp;
         sp.locode[j] = ((uint32_t)j << 4) | code;
         if (alive) {
-          const int64_t src_cell = (int64_t)k * g.nx + i;
-          cnt_on = true;
-          ckey = (src_cell << 4) | code;
-          cidx = (int64_t)code * g.ncells + src_cell;
           // the moments at x^{n+3/2} with u^{n+1}, B = H^{n+3/2} at the new position and
           // E^{n+1}
           corners(g, i2, k2, xn - (double)i2, zn - (double)k2, node, W);
@@ -260,25 +372,64 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
           const double gam2 = gamma_bar(g, a.Enew, mover, sp.beta, un, node, W);
           moments13(sp, gam2, un, B2, wp, v);
           dep = true;
-          dkey = (int64_t)k2 * g.nx + i2;
+          dst = k2 * g.nx + i2;
+          stay = dst == src;
+          val[0] = xn - (double)i2;
+          val[1] = zn - (double)k2;
+#pragma unroll
+          for (int r = 0; r < 13; ++r) val[2 + r] = v[r];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) node_dst[c] = (uint32_t)node[c];
         }
       }
     }
   }
-  // move counts and arrivals, then the moments, each summed over the lanes' runs
-  const Seg sd = seg_of(dep ? dkey : -1 - (int64_t)lane);
+  if (threadIdx.x == 0) range[0] = src;
+  if (threadIdx.x == min((int)blockDim.x, n - (int)(blockIdx.x * blockDim.x)) - 1) range[1] = src;
+  __syncthreads();
+  // the cells of the block, in sorted order (a misplaced particle, flagged above, can be anywhere)
+  const int c0 = range[0];
+  const int span = c0 >= 0 && range[1] >= c0 && range[1] - c0 < kAltCells ? range[1] - c0 + 1 : 0;
+  const int before = alt_lane_before(src);  // (all lanes active)
+  const bool head = act && (lane == 0 || before != src);
   if (PUSH) {
-    const Seg sc = seg_of(cnt_on ? ckey : -1 - (int64_t)lane);
-    const int nc_ = seg_sum(sc, cnt_on ? 1 : 0);
-    if (cnt_on && sc.head) atomicAdd(&sp.cnt[cidx], nc_);
-    const int na_ = seg_sum(sd, dep ? 1 : 0);
-    if (dep && sd.head) atomicAdd(&sp.arr[dkey], na_);
+    // move counts and arrivals: the particles of a run that keep their cell together, the others
+    // one by one
+    const uint64_t stays = __ballot(dep && stay && code == 4u), heads = __ballot(head);
+    const uint64_t above = heads & ~((2ull << lane) - 1ull);
+    const uint64_t run = (above ? (above & -above) - 1ull : ~0ull) & ~((1ull << lane) - 1ull);
+    const int n_stay = head ? __popcll(stays & run) : 0;
+    if (n_stay > 0) {
+      atomicAdd(&sp.cnt[4 * g.ncells + src], n_stay);
+      atomicAdd(&sp.arr[src], n_stay);
+    }
+    if (dep && !(stay && code == 4u)) {
+      atomicAdd(&sp.cnt[(int64_t)code * g.ncells + src], 1);
+      atomicAdd(&sp.arr[dst], 1);
+    }
   }
-  const int64_t nn = g.nnodes;
-  for (int c = 0; c < 4; ++c) {
-    for (int r = 0; r < 13; ++r) {
-      const double t = seg_sum(sd, W[c] * v[r]);
-      if (dep && sd.head) unsafeAtomicAdd(&a.M[(int64_t)(r < 12 ? r : 12 + s) * nn + node[c]], t);
+  alt_deposit(st, act, dep, stay, head || (act && (lane & 15) == 0), src, dst, node_src, node_dst, val,
+              a.M, g.nnodes, 12 + s, acc, c0, span);
+  if (span == 0) return;  // (the same for the whole block)
+  __syncthreads();
+  // Node column l lies between the cells c0 + l - 1 and c0 + l: the left corners of the second
+  // and the right ones of the first, one node each where the cells are neighbours in a row.
+  for (int e = threadIdx.x; e < (span + 1) * 2 * kAltVals; e += blockDim.x) {
+    const int v = e % kAltVals, up = e / kAltVals % 2, l = e / (2 * kAltVals);
+    double left = l < span ? acc[(l * 4 + 2 * up) * kAltVals + v] : 0.0;
+    const double right = l > 0 ? acc[((l - 1) * 4 + 2 * up + 1) * kAltVals + v] : 0.0;
+    double *M = a.M + (int64_t)(v < 12 ? v : 12 + s) * g.nnodes;
+    const int cr = c0 + l - 1;  // the cell with the right corners
+    const bool joined = l > 0 && l < span && (cr + 1) % g.nx != 0;
+    if (joined) left += right;
+    if (left != 0.0) {
+      const int k = (c0 + l) / g.nx, i = c0 + l - k * g.nx;
+      unsafeAtomicAdd(M + (int64_t)(up ? wrapc(k + 1, g.nz) : k) * g.nxn + i, left);
+    }
+    if (!joined && right != 0.0) {
+      const int k = cr / g.nx, i = cr - k * g.nx;
+      const int i1 = g.bc_x == PIC_BC_PERIODIC ? wrapc(i + 1, g.nx) : i + 1;
+      unsafeAtomicAdd(M + (int64_t)(up ? wrapc(k + 1, g.nz) : k) * g.nxn + i1, right);
     }
   }
 }
