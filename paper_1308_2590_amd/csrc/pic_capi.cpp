@@ -266,9 +266,13 @@ void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
   c->tiles.per_xcd = (c->tiles.ntiles + 7) / 8;
 }
 
-// The sort's ranker: one thread per cell up to this many particles per occupied cell and
-// species, the row walk above.
+// The sort's ranker: one thread per cell up to this many particles per occupied cell and species
+// on at least this many occupied cells, otherwise the row walk.  (One thread per cell waits for a
+// longer chain of loads but does less work.  Sort, rows / cells, at 4 per cell: 64 x 64 cells 21 /
+// 26 us, 256 x 256 28 / 31, 400 x 400 38 / 33, 700 x 700 78 / 53; at 16 per cell: 20 / 31, 33 / 40,
+// 62 / 59; a 171 x 259 slab at 11 per cell: 31 / 35.)
 constexpr double kRankCellsMaxPerCell = 16.0;
+constexpr int64_t kRankCellsMinCells = 100000;
 
 bool rank_cells(const pic_ctx *c) {
   if (c->rank_mode == PIC_RANK_CELLS) return true;
@@ -470,7 +474,7 @@ pic_status retile(pic_ctx *c) {
     ld.k_hi = c->g.nz;
   }
   choose_tiles(c, ld);
-  c->rank_cells_auto = occupied > 0 && ld.ppc <= kRankCellsMaxPerCell;
+  c->rank_cells_auto = occupied >= kRankCellsMinCells && ld.ppc <= kRankCellsMaxPerCell;
   if (pic::particle_lds_bytes(c->g, c->tiles, mixed(c), c->waves) > c->lds_max)
     return fail(c, PIC_ERR_ARG, "tile too large: its LDS accumulators exceed the LDS of a block");
   return PIC_OK;
