@@ -168,10 +168,11 @@ pic_status pic_set_tiles(pic_ctx *ctx, int32_t tile_x, int32_t tile_z);
 
 /* Choose how the cell sort ranks the particles (the result is the same stable order either
  * way).  PIC_RANK_ROWS: per tile, the destination of every (cell, move code) is staged in LDS
- * and one wavefront per tile row ranks 64 slots at a time with ballots (many particles per
- * cell).  PIC_RANK_CELLS: one thread per cell computes its destinations from its neighbours'
+ * and 64 or 16 lanes per cell rank its slots with ballots (many particles per cell, or few
+ * cells).  PIC_RANK_CELLS: one thread per cell computes its destinations from its neighbours'
  * counts and walks its own slots (few particles per cell).  PIC_RANK_AUTO (the default)
- * picks by the particles per occupied cell at the last load or re-tiling.
+ * picks by the particles per occupied cell and the occupied cells at the last load or
+ * re-tiling.
  * Errors: PIC_ERR_ARG for another mode. */
 pic_status pic_set_rank_mode(pic_ctx *ctx, int32_t mode);
 

@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
     const int i = (int)floor(x), k = (int)floor(z);
     if (i < 0 || i >= g.nx || k < 0 || k >= g.nz) {
       atomicOr(a.flags, kFlagOrderA);
-      if (PUSH) sp.locode[j] = ((uint32_t)j << 4) | kAbsorbed;
+      if (PUSH) reinterpret_cast<uint8_t *>(sp.locode)[j] = kAbsorbed;
     } else {
       int64_t node[4];
       double W[4], v[13];
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
         sp.dst[4][j] = un[2];
         if (sp.dst_id) sp.dst_id[j] = sp.src_id[p];
         if (sp.w_stride) sp.dst_w[j] = wp;
-        sp.locode[j] = ((uint32_t)j << 4) | code;
+        reinterpret_cast<uint8_t *>(sp.locode)[j] = (uint8_t)code;
         if (alive) {
           // the moments at x^{n+3/2} with u^{n+1}, B = H^{n+3/2} at the new position and
           // E^{n+1}

@@ -273,6 +273,8 @@ void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
 // 62 / 59; a 171 x 259 slab at 11 per cell: 31 / 35.)
 constexpr double kRankCellsMaxPerCell = 16.0;
 constexpr int64_t kRankCellsMinCells = 100000;
+// The per-tile ranker gives a cell a whole wavefront from this many particles on.
+constexpr double kRankDensePerCell = 40.0;
 
 bool rank_cells(const pic_ctx *c) {
   if (c->rank_mode == PIC_RANK_CELLS) return true;
@@ -286,7 +288,10 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   a.t = c->tiles;
   a.mixed = mixed(c) ? 1 : 0;
   a.rank_cells = rank_cells(c) ? 1 : 0;
-  a.direct = c->direct ? 1 : 0;
+  a.dense = c->load.ppc >= kRankDensePerCell ? 1 : 0;
+  // the direct form is not instantiated for particle labels, batches and mover options
+  a.direct = (c->direct && !c->batch && !c->mover && !c->d.track_ids) ? 1 : 0;
+  a.slot_codes = a.direct ? 0 : 1;
   a.waves = c->waves;
   // the per-cell ranker reads code masks, which the tile kernel writes (not the per-particle
   // kernel of the mover options, which accumulates full counts)

@@ -68,7 +68,9 @@ struct SpeciesArgs {
   int32_t *perm_new;         // next cycle's sorted slot -> location in dst
   const int32_t *cs;         // cell start offsets of the current order [ncells + 1]
   int32_t *cs_new;           // cell start offsets of the next order [ncells + 1]
-  uint32_t *locode;          // per sorted slot: (location written << 4) | move code
+  // per sorted slot: (location written << 4) | move code, or with StepArgs::slot_codes a byte, the
+  // move code (the location is the slot's)
+  uint32_t *locode;
   int32_t *cnt;              // [9][ncells] particles leaving each cell per move code
   // [ncells] bit d set when the cell sent particles with move code d; with count masks only
   // the counts of set bits are written (the others keep values from earlier cycles)
@@ -83,8 +85,10 @@ struct StepArgs {
   GridArgs g;
   TileArgs t;
   int32_t mixed;             // 1: mixed-precision particle state and arithmetic
-  int32_t rank_cells;        // 1: destinations ranked one thread per cell, 0: by tile rows
+  int32_t rank_cells;        // 1: destinations ranked one thread per cell, 0: per tile
+  int32_t dense;             // per tile: 64 lanes per cell (1) or 16 (0)
   int32_t direct;            // 1: the particle kernel's direct form (few particles per cell), 0: grouped
+  int32_t slot_codes;        // 1: the particle kernel writes a byte per slot (see locode)
   int32_t waves;             // wavefronts per block of the grouped form
   int32_t count_masks;       // 1: the particle kernel writes code masks and nonzero counts only
   int32_t n_scan_blocks;     // blocks of the count scan per species

@@ -23,7 +23,7 @@
 //               in the next order as flags and, from one extra block, as an ordered list;
 //   k_tile_flags / k_tile_compact  the same flags and list from cell starts (after loads);
 //   kb_scan1 / kb_scan2  the same two passes for every run of a batch;
-//   k_rank      stable destination of every particle: cell start + particles arriving from
+//   k_rank / k_rank_cells  stable destination of every particle: cell start + particles arriving from
 //               source cells with a smaller key + rank within (source cell, move code),
 //               written as the next cycle's slot -> location permutation.
 // Positions never move more than one cell per cycle because dt <= min(dx, dz) and |v| < c,
@@ -389,6 +389,9 @@ __device__ __forceinline__ void store_or_drop(float *p, int i, bool on, float v)
 __device__ __forceinline__ void store_or_drop(int32_t *p, int i, bool on, int32_t v) {
   __builtin_amdgcn_raw_buffer_store_b32((uint32_t)v, store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
 }
+__device__ __forceinline__ void store_or_drop(uint8_t *p, int i, bool on, uint8_t v) {
+  __builtin_amdgcn_raw_buffer_store_b8(v, store_rsrc(p), on ? i : kStoreDrop, 0, 0);
+}
 __device__ __forceinline__ void store_or_drop(uint32_t *p, int i, bool on, uint32_t v) {
   __builtin_amdgcn_raw_buffer_store_b32(v, store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
 }
@@ -590,6 +593,13 @@ struct TileLds {
     bytes = rows + (size_t)(n_node - 3) * tz * 2 * sizeof(int);
   }
 };
+
+// Location and move code of slot j as the rankers read them, (location << 4) | code: stored so by
+// the direct form; the other kernels write a particle to the location of its slot and store a byte
+// per slot, its code.
+__device__ __forceinline__ uint32_t slot_code(const StepArgs &a, const SpeciesArgs &sp, int j) {
+  return a.slot_codes ? ((uint32_t)j << 4) | reinterpret_cast<const uint8_t *>(sp.locode)[j] : sp.locode[j];
+}
 
 // Particle state in either form, as the kernel's arithmetic type: cell (i, k), in-cell offsets
 // (fx, fz) and momentum.  FP64 keeps positions in cell units; the mixed form keeps the cell key
@@ -1024,7 +1034,11 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
     // consistent state; the counts keep the slot, so the next order stays in bounds.)
     auto drop_slot = [&](int j, uint32_t loc) {
       atomicOr(a.flags, kFlagOrder);
-      if (PUSH) sp.locode[j] = (loc << 4) | kAbsorbed;
+      if (!PUSH) return;
+      if constexpr (DIRECT)
+        sp.locode[j] = (loc << 4) | kAbsorbed;
+      else
+        reinterpret_cast<uint8_t *>(sp.locode)[j] = kAbsorbed;
     };
     if constexpr (!DIRECT) {
       const Stage stage(ldsb + Lo.stage + wave * kStageBytes);
@@ -1150,7 +1164,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
               store_or_drop(sp.mdst[3], j, ok, o.n1);
               store_or_drop(sp.mdst[4], j, ok, o.n2);
               if constexpr (PW) store_or_drop(wdst, j, ok && wstride != 0, wcur);
-              store_or_drop(sp.locode, j, ok, ((uint32_t)j << 4) | code);
+              store_or_drop(reinterpret_cast<uint8_t *>(sp.locode), j, ok, (uint8_t)code);
             } else {
               store_or_drop(sp.dst[0], j, ok, o.xn);
               store_or_drop(sp.dst[1], j, ok, o.zn);
@@ -1158,7 +1172,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
               store_or_drop(sp.dst[3], j, ok, o.n1);
               store_or_drop(sp.dst[4], j, ok, o.n2);
               if constexpr (PW) store_or_drop(wdst, j, ok && wstride != 0, wcur);
-              store_or_drop(sp.locode, j, ok, ((uint32_t)j << 4) | code);
+              store_or_drop(reinterpret_cast<uint8_t *>(sp.locode), j, ok, (uint8_t)code);
             }
             // particle ids (tests only)
             if (IDS && ok && sp.dst_id) sp.dst_id[j] = sp.src_id[p];
@@ -1534,215 +1548,162 @@ __device__ int block_excl_scan(int v, int *sh, int *total) {
   return off + inc - v;
 }
 
-// Stable destinations of one tile's particles.  The destination base of every (cell, move
-// code) of the tile is computed once into LDS; then one wavefront per tile row (or part of a
-// row) walks the row's slots in order, 64 at a time: particles with the same (cell, code) in a
-// group of 64 get consecutive ranks from ballots of the code's bits, and a per-wave LDS
-// counter carries the rank across groups.
+// Stable destinations of one tile's particles.  The destination base of every (cell, move code) of
+// the tile is computed once into LDS; then the wavefronts take the tile's cells, LPC lanes per cell
+// (64, or 16 where cells hold fewer particles), and walk each cell's slots LPC at a time, the codes
+// of the next four chunks on their way.  The
+// particles that stay (most) get consecutive slots from one ballot and a running base in a
+// register; the others consecutive ranks per code from ballots of the code's bits, their bases
+// counted on in the LDS table.  (The walk along tile rows in groups of 64 slots searched every
+// lane's cell and ranked all codes alike: about 150 instructions per group, 101 us on 21M particles
+// at 128 per cell, 80 now.)
+template <int LPC>
 __device__ __forceinline__ void rank_body(const StepArgs &a, int tile, int species) {
   const GridArgs &g = a.g;
   const TileArgs &t = a.t;
+  const SpeciesArgs &sp = a.sp[species];
+  if (!sp.active) return;
   const int tzi = tile / t.ntx, txi = tile - tzi * t.ntx;
   const int i0 = txi * t.tx, k0 = tzi * t.tz;
   const int i1 = min(i0 + t.tx, g.nx), k1 = min(k0 + t.tz, g.nz);
-  const int cw = i1 - i0, ch = k1 - k0;
-  const int ntc = t.tx * t.tz;
+  const int cw = i1 - i0, ch = k1 - k0, ncell = cw * ch;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
   extern __shared__ int ldsi[];
-  const int ring_cells = (t.tx + 4) * (t.tz + 4);
-  int *btab = ldsi;                                                   // [ntc][9]
-  int *rowcs = ldsi + ntc * 9 + wave * (t.tx + 1);                    // [tx + 1] per wave
-  int *ctr = ldsi + ntc * 9 + nwaves * (t.tx + 1) + wave * (t.tx * 10);  // [tx][10] per wave
-  int *rcnt = ldsi + ntc * 9 + nwaves * (t.tx + 1 + t.tx * 10);       // [9][ring_cells]
-  int *rcsn = rcnt + kMoveCodes * ring_cells;                         // [ring_cells]
-  int *rkey = rcsn + ring_cells;                                      // [ring_cells]
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-
-  // one block per (tile, species): twice the blocks of a per-tile launch, to overlap the
-  // memory latency of the staging and walking phases
-  {
-    const int s = species;
-    const SpeciesArgs &sp = a.sp[s];
-    if (!sp.active) return;
-    // A tile with fewer rows than wavefronts splits each row's slots into wpr contiguous
-    // parts, one per wavefront.  A part that starts inside a cell first counts, per move code,
-    // that cell's slots before the part, so its ranks continue the ones of the parts before.
-    const int nrows = k1 - k0;
-    const int wpr = nrows < nwaves ? nwaves / nrows : 1;
-    const int part = wave % wpr;
-    const int r_first = k0 + wave / wpr;
-    // the first row's cell starts and counters, loaded together with the staging below
-    if (r_first < k1) {
-      for (int q = lane; q <= cw; q += 64) rowcs[q] = sp.cs[(int64_t)r_first * g.nx + i0 + q];
-      for (int q = lane; q < cw * 10; q += 64) ctr[q] = 0;
+  const int RW = t.tx + 4, RH = t.tz + 4;  // ring of two cells: destinations +-1, their sources +-1
+  int *btab = ldsi;                        // [cells][9]
+  int *cst = btab + t.tx * t.tz * kMoveCodes;  // [cells]: first slot
+  int *cen = cst + t.tx * t.tz;                // [cells]: end slot
+  int *rcnt = cen + t.tx * t.tz;               // [9][ring]
+  int *rcsn = rcnt + kMoveCodes * RW * RH;     // [ring]
+  int *rkey = rcsn + RW * RH;                  // [ring]
+  const int total = sp.cs_new[g.ncells];
+  // counts of the tile and its ring (sources of the destinations reached from the tile),
+  // next-order starts of the same region, and the slots of the tile's cells, staged in LDS; a
+  // tile and its ring fit in the grid along an axis: wraps need one compare there
+  const bool nearx = g.nx >= t.tx + 4, nearz = g.nz >= t.tz + 4;
+  const SmallDiv div_rw(RW), div_tx(t.tx), div_tz(t.tz), div_cw(cw);
+  for (int e = threadIdx.x; e < RW * RH; e += blockDim.x) {
+    const int rz = div_rw.q(e), rx = e - rz * RW;
+    int gi = i0 - 2 + rx;
+    const int gk = wrap_t(k0 - 2 + rz, g.nz, nearz);
+    bool in = true;
+    if (g.bc_x == PIC_BC_PERIODIC) gi = wrap_t(gi, g.nx, nearx); else in = gi >= 0 && gi < g.nx;
+    // The counts are valid only in tiles that held particles (the tile flag); they are
+    // loaded together with the flag (from a cell inside the grid) and kept or dropped after.
+    const int gic = min(max(gi, 0), g.nx - 1);
+    const int64_t c = (int64_t)gk * g.nx + gic;
+    const bool act = in && a.tile_active[div_tz.q(gk) * t.ntx + div_tx.q(gic)] != 0;
+    int v[kMoveCodes];
+#pragma unroll
+    for (int d = 0; d < kMoveCodes; ++d) v[d] = sp.cnt[(int64_t)d * g.ncells + c];
+    const int csn_c = sp.cs_new[c], csb = sp.cs[c], cse = sp.cs[c + 1];
+#pragma unroll
+    for (int d = 0; d < kMoveCodes; ++d) rcnt[d * RW * RH + e] = act ? v[d] : 0;
+    rcsn[e] = in ? csn_c : 0;
+    rkey[e] = in ? (int)c : -1;  // sort key of the cell; -1 outside an absorbing axis
+    if (rx >= 2 && rx < cw + 2 && rz >= 2 && rz < ch + 2) {
+      cst[(rz - 2) * cw + rx - 2] = csb;
+      cen[(rz - 2) * cw + rx - 2] = cse;
     }
-    const int total = sp.cs_new[g.ncells];
-    // counts of the tile and a one-cell ring (sources of the destinations reached from the
-    // tile), and next-order starts of the same region, staged in LDS
-    const int RW = t.tx + 4, RH = t.tz + 4;  // ring of two cells: destinations +-1, their sources +-1
-    // a tile and its ring fit in the grid along an axis: wraps need one compare there
-    const bool nearx = g.nx >= t.tx + 4, nearz = g.nz >= t.tz + 4;
-    const SmallDiv div_rw(RW), div_tx(t.tx), div_tz(t.tz);
-    for (int e = threadIdx.x; e < RW * RH; e += blockDim.x) {
-      const int rz = div_rw.q(e), rx = e - rz * RW;
-      int gi = i0 - 2 + rx;
-      const int gk = wrap_t(k0 - 2 + rz, g.nz, nearz);
-      bool in = true;
-      if (g.bc_x == PIC_BC_PERIODIC) gi = wrap_t(gi, g.nx, nearx); else in = gi >= 0 && gi < g.nx;
-      // The counts are valid only in tiles that held particles (the tile flag); they are
-      // loaded together with the flag (from a cell inside the grid) and kept or dropped after.
-      const int gic = min(max(gi, 0), g.nx - 1);
-      const int64_t c = (int64_t)gk * g.nx + gic;
-      const bool act = in && a.tile_active[div_tz.q(gk) * t.ntx + div_tx.q(gic)] != 0;
-      int v[kMoveCodes];
+  }
+  __syncthreads();
+  // one (code, cell) pair per thread, consecutive threads on consecutive cells of one code
+  // (so their LDS reads of the staged counts fall in different banks)
+  const SmallDiv div_cells(ncell);
+  for (int e = threadIdx.x; e < ncell * kMoveCodes; e += blockDim.x) {
+    const int d = div_cells.q(e), cell = e - d * ncell;
+    const int lk = div_cw.q(cell), li = cell - lk * cw;
+    // First slot, in the next order, of the particles moving from this cell with code d:
+    // the start of the destination cell plus the particles arriving there from source
+    // cells earlier in the current (cell-sorted) order.  Destination and sources lie in
+    // the ring, so they are found by ring offsets; the order uses the cells' sort keys.
+    const int rc = (lk + 2) * RW + (li + 2);
+    int b = 0;
+    if (rcnt[d * RW * RH + rc] > 0) {
+      const int rd = rc + (d / 3 - 1) * RW + (d % 3 - 1);  // destination
+      if (rkey[rd] >= 0) {
+        const int key_c = rkey[rc];
+        b = rcsn[rd];
 #pragma unroll
-      for (int d = 0; d < kMoveCodes; ++d) v[d] = sp.cnt[(int64_t)d * g.ncells + c];
-      const int csn_c = sp.cs_new[c];
-#pragma unroll
-      for (int d = 0; d < kMoveCodes; ++d) rcnt[d * RW * RH + e] = act ? v[d] : 0;
-      rcsn[e] = in ? csn_c : 0;
-      rkey[e] = in ? (int)c : -1;  // sort key of the cell; -1 outside an absorbing axis
-    }
-    __syncthreads();
-    // (a tile without particles of this species has no counts: its table stays zero and its
-    // rows are empty)
-    // one (code, cell) pair per thread, consecutive threads on consecutive cells of one code
-    // (so their LDS reads of the staged counts fall in different banks)
-    const SmallDiv div_cells(ch * cw), div_cw(cw);
-    for (int e = threadIdx.x; e < ch * cw * kMoveCodes; e += blockDim.x) {
-      const int d = div_cells.q(e), cell = e - d * (ch * cw);
-      const int lk = div_cw.q(cell), li = cell - lk * cw;
-      // First slot, in the next order, of the particles moving from this cell with code d:
-      // the start of the destination cell plus the particles arriving there from source
-      // cells earlier in the current (cell-sorted) order.  Destination and sources lie in
-      // the ring, so they are found by ring offsets; the order uses the cells' sort keys.
-      const int rc = (lk + 2) * RW + (li + 2);
-      int b = 0;
-      if (rcnt[d * RW * RH + rc] > 0) {
-        const int rd = rc + (d / 3 - 1) * RW + (d % 3 - 1);  // destination
-        if (rkey[rd] >= 0) {
-          const int key_c = rkey[rc];
-          b = rcsn[rd];
-#pragma unroll
-          for (int d2 = 0; d2 < kMoveCodes; ++d2) {
-            const int rs = rd - (d2 / 3 - 1) * RW - (d2 % 3 - 1);  // source sending d2 to rd
-            const int ks = rkey[rs];
-            if (ks >= 0 && ks < key_c) b += rcnt[d2 * RW * RH + rs];
-          }
+        for (int d2 = 0; d2 < kMoveCodes; ++d2) {
+          const int rs = rd - (d2 / 3 - 1) * RW - (d2 % 3 - 1);  // source sending d2 to rd
+          const int ks = rkey[rs];
+          if (ks >= 0 && ks < key_c) b += rcnt[d2 * RW * RH + rs];
         }
       }
-      btab[(lk * t.tx + li) * kMoveCodes + d] = b;
     }
-    __syncthreads();
-    for (int r = r_first; r < k1; r += nwaves / wpr) {
-      const int64_t rowc = (int64_t)r * g.nx;
-      const int lk = r - k0;
-      if (r != r_first) {
-        for (int q = lane; q <= cw; q += 64) rowcs[q] = sp.cs[rowc + i0 + q];
-        for (int q = lane; q < cw * 10; q += 64) ctr[q] = 0;
-      }
-      wave_sync();
-      const int rb = rowcs[0], re = rowcs[cw];
-      const int jb = rb + (int)((int64_t)(re - rb) * part / wpr);
-      const int je = rb + (int)((int64_t)(re - rb) * (part + 1) / wpr);
-      int clb = 0;  // the cell of the next group's first slot, or a cell before it
-      if (part > 0 && jb < je) {
-        int lo = 0, hi = cw - 1;  // the cell holding slot jb
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (rowcs[mid] <= jb) lo = mid; else hi = mid - 1;
-        }
-        clb = lo;
-        int before[kMoveCodes] = {};
-        for (int b0 = rowcs[lo]; b0 < jb; b0 += 64) {
-          const int j = b0 + lane;
-          const int d = j < jb ? (int)(sp.locode[j] & 15u) : kAbsorbed;
+    btab[cell * kMoveCodes + d] = b;
+  }
+  __syncthreads();
+  // The walk: sub-wavefront `sub` of LPC lanes takes cells first, first + stride, ...
+  constexpr int kSub = 64 / LPC;
+  const int sub = lane / LPC, sl = lane & (LPC - 1), stride = nwaves * kSub;
+  const uint64_t sub_mask = (LPC == 64 ? ~0ull : ((1ull << LPC) - 1ull) << (sub * LPC));
+  const uint64_t lt_mask = ((1ull << lane) - 1ull) & sub_mask;
+  int cell = wave * kSub + sub - stride, pos = 0, end = 0, base4 = 0;
+  constexpr int kAhead = LPC == 64 ? 4 : 2;  // chunks of LPC slots whose codes are loaded together
+  auto next_part = [&](int &c, int &p, int &e) {  // the part after (c, p, e); c >= ncell: none
+    p += kAhead * LPC;
+    while (p >= e) {
+      c += stride;
+      if (c >= ncell) break;
+      p = cst[c];
+      e = cen[c];
+    }
+  };
+  auto load_codes = [&](int c, int p, int e, uint32_t out[kAhead]) {
 #pragma unroll
-          for (int dd = 0; dd < kMoveCodes; ++dd) before[dd] += __popcll(__ballot(d == dd));
-        }
-        if (lane < kMoveCodes) {
+    for (int q = 0; q < kAhead; ++q) {
+      const int j = p + q * LPC + sl;
+      out[q] = c < ncell && j < e ? slot_code(a, sp, j) : (uint32_t)kAbsorbed;
+    }
+  };
+  uint32_t lc[kAhead], lcn[kAhead];
+  next_part(cell, pos, end);
+  load_codes(cell, pos, end, lc);
+  if (cell < ncell) base4 = btab[cell * kMoveCodes + 4];
+  while (__any(cell < ncell)) {
+    int ncl = cell, npos = pos, nend = end;
+    if (cell < ncell) next_part(ncl, npos, nend);
+    load_codes(ncl, npos, nend, lcn);
 #pragma unroll
-          for (int dd = 0; dd < kMoveCodes; ++dd)
-            if (lane == dd) ctr[lo * 10 + dd] = before[dd];
+    for (int q = 0; q < kAhead; ++q) {
+      const int d = (int)(lc[q] & 15u), loc = (int)(lc[q] >> 4);
+      const uint64_t stay = __ballot(d == 4) & sub_mask, move = __ballot(d != 4 && d < kMoveCodes);
+      if (!__any(d < kMoveCodes)) continue;  // past the end of every cell
+      int slot = base4 + __popcll(stay & lt_mask);
+      if (move) {
+        const bool m = d != 4 && d < kMoveCodes;
+        // the lanes of the same cell with the same move code: one ballot per bit of the code
+        uint64_t same = move & sub_mask;
+#pragma unroll
+        for (int bit = 0; bit < 4; ++bit) {
+          const bool on = (d >> bit) & 1;
+          const uint64_t w = __ballot(m && on);
+          same &= on ? w : ~w;
+        }
+        if (m) {
+          int *bt = btab + cell * kMoveCodes + d;
+          slot = *bt + __popcll(same & lt_mask);
+          // the last lane of each code carries the count to the cell's next chunk
+          if ((same >> lane) == 1ull) *bt = slot + 1;
         }
         wave_sync();
       }
-      // the row's move codes are loaded kGroups groups of 64 at a time (indices clamped into
-      // the row), then ranked group by group
-      constexpr int kGroups = 8;
-      constexpr int kProbe = 4;
-      for (int b0 = jb; b0 < je; b0 += 64 * kGroups) {
-        uint32_t lcs[kGroups];
-#pragma unroll
-        for (int q = 0; q < kGroups; ++q) lcs[q] = sp.locode[min(b0 + q * 64 + lane, je - 1)];
-#pragma unroll
-        for (int q = 0; q < kGroups; ++q) {
-          const int base = b0 + q * 64;
-          if (base >= je) break;
-          const int j = base + lane;
-          const bool act = j < je;
-          int d = kAbsorbed, cl = 0, loc = 0;
-          // the largest cl with rowcs[cl] <= j: the group's slots are consecutive, so it is
-          // one of the few cells after clb (independent probes, one LDS round trip); a lane
-          // past them searches
-          {
-            int cnt = 0;
-#pragma unroll
-            for (int t = 1; t <= kProbe; ++t) cnt += (clb + t < cw && rowcs[min(clb + t, cw)] <= j) ? 1 : 0;
-            cl = clb + cnt;
-            if (act && cnt == kProbe && cl + 1 < cw && rowcs[cl + 1] <= j) {
-              int lo = cl + 1, hi = cw - 1;
-              while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (rowcs[mid] <= j) lo = mid; else hi = mid - 1;
-              }
-              cl = lo;
-            }
-            clb = __builtin_amdgcn_readlane(cl, min(63, je - 1 - base));  // cell of the group's last slot
-          }
-          if (act) {
-            const uint32_t lc = lcs[q];
-            d = (int)(lc & 15u);
-            loc = (int)(lc >> 4);
-          }
-          const bool valid = act && d < kMoveCodes;
-          // The group's slots are in cell order, so the lanes of one cell are contiguous:
-          // [cstart, cend).  A particle's rank within its (cell, code) in this group is the
-          // number of lanes of its cell below it with the same code.
-          const int prevcl = lane_before(cl);
-          const uint64_t heads = __ballot(act && (lane == 0 || prevcl != cl));
-          const uint64_t upto = heads & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
-          const int cstart = upto ? 63 - __clzll((long long)upto) : 0;
-          const uint64_t above = heads & ~(lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
-          const int cend = above ? __ffsll((unsigned long long)above) - 1 : 64;
-          const uint64_t cellm = (cend == 64 ? ~0ull : ((1ull << cend) - 1ull)) & ~((1ull << cstart) - 1ull);
-          // the lanes with the same move code: one ballot per bit of the code
-          uint64_t same = __ballot(valid);
-#pragma unroll
-          for (int bit = 0; bit < 4; ++bit) {
-            const bool on = (d >> bit) & 1;
-            const uint64_t m = __ballot(valid && on);
-            same &= on ? m : ~m;
-          }
-          same &= cellm;
-          if (valid) {
-            const int key = cl * 10 + d;
-            const int before = ctr[key];
-            const int rank = __popcll(same & lt_mask);
-            const int slot = btab[(lk * t.tx + cl) * kMoveCodes + d] + before + rank;
-            if (slot >= 0 && slot < total) {
-              sp.perm_new[slot] = loc;
-            } else {
-              atomicOr(a.flags, kFlagSlot);
-            }
-            // the last lane of each (cell, code) carries the count to the next group
-            if ((same >> lane) == 1ull) ctr[key] = before + rank + 1;
-          }
-          wave_sync();
-        }
+      if (d < kMoveCodes) {
+        if (slot >= 0 && slot < total)
+          sp.perm_new[slot] = loc;
+        else
+          atomicOr(a.flags, kFlagSlot);
       }
-      wave_sync();
+      base4 += __popcll(stay);
     }
+    if (ncl != cell && ncl < ncell) base4 = btab[ncl * kMoveCodes + 4];
+    cell = ncl;
+    pos = npos;
+    end = nend;
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) lc[q] = lcn[q];
   }
 }
 
@@ -1895,7 +1856,7 @@ __device__ __forceinline__ void rank_cells_body(const StepArgs &a, int tile, int
     for (int j = cb; j < ce; j += 4) {
       uint32_t lc[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) lc[q] = sp.locode[min(j + q, ce - 1)];
+      for (int q = 0; q < 4; ++q) lc[q] = slot_code(a, sp, min(j + q, ce - 1));
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         if (j + q >= ce) break;
@@ -1929,10 +1890,11 @@ __global__ __launch_bounds__(kBlock) void k_rank_cells(const StepArgs a) {
     rank_cells_body<false>(a, tile, blockIdx.y);
 }
 
+template <int LPC>
 __global__ __launch_bounds__(kBlock) void k_rank(const StepArgs a) {
   const int tile = block_tile(a.t, a.tile_list);
   if (tile < 0) return;
-  rank_body(a, tile, blockIdx.y);
+  rank_body<LPC>(a, tile, blockIdx.y);
 }
 
 // Flag per tile: does it hold particles of any species in the order given by the cell starts
@@ -2297,7 +2259,7 @@ __global__ __launch_bounds__(kBlock) void kb_rank(const BatchArgs b) {
   else if (sa.rank_cells)
     rank_cells_body<false>(sa, sa.tile_list[idx], li - idx * sa.nsp);
   else
-    rank_body(sa, sa.tile_list[idx], li - idx * sa.nsp);
+    rank_body<16>(sa, sa.tile_list[idx], li - idx * sa.nsp);
 }
 
 // End of a cycle: flip every run's buffer parity and count the cycle.
@@ -2321,10 +2283,8 @@ size_t particle_lds_bytes(const GridArgs &g, const TileArgs &t, bool mixed, int 
 }
 
 size_t rank_lds_bytes(const TileArgs &t) {
-  const int nw = kBlock / 64;
   const size_t ring = (size_t)(t.tx + 4) * (t.tz + 4);
-  return ((size_t)t.tx * t.tz * kMoveCodes + (size_t)nw * ((t.tx + 1) + t.tx * 10) +
-          ring * (kMoveCodes + 2)) * sizeof(int);
+  return ((size_t)t.tx * t.tz * (kMoveCodes + 2) + ring * (kMoveCodes + 2)) * sizeof(int);
 }
 
 hipError_t launch_field_solve(const FieldArgs &a, hipStream_t s) {
@@ -2343,7 +2303,7 @@ static void launch_particles_t(const StepArgs &a, bool ids, bool pw, dim3 grid, 
   const dim3 blk(64u * (unsigned)a.waves);
   // the pushing kernels without ids in the direct form (few particles per lane)
   if constexpr (PUSH) {
-    if (!ids && a.direct) {
+    if (a.direct) {
       if (pw)
         hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, true, true>), grid, blk, lds, s, a);
       else
@@ -2368,7 +2328,7 @@ hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t s) {
     pw = pw || (a.sp[q].active && a.sp[q].w_stride != 0);
   }
   // the direct form has no staging
-  const size_t lds = particle_lds_bytes(a.g, a.t, a.mixed != 0, push && a.direct && !ids ? 0 : a.waves);
+  const size_t lds = particle_lds_bytes(a.g, a.t, a.mixed != 0, push && a.direct ? 0 : a.waves);
   const dim3 grid(8u * (unsigned)a.t.per_xcd);
   if (a.mixed) {
     if (push) launch_particles_t<true, true>(a, ids, pw, grid, lds, s);
@@ -2393,7 +2353,10 @@ hipError_t launch_sort(const StepArgs &a, hipStream_t s) {
     const unsigned threads = (unsigned)(rounded < kBlock ? rounded : kBlock);
     hipLaunchKernelGGL(k_rank_cells, grid, dim3(threads), 0, s, a);
   } else {
-    hipLaunchKernelGGL(k_rank, grid, dim3(kBlock), rank_lds_bytes(a.t), s, a);
+    if (a.dense)
+      hipLaunchKernelGGL(k_rank<64>, grid, dim3(kBlock), rank_lds_bytes(a.t), s, a);
+    else
+      hipLaunchKernelGGL(k_rank<16>, grid, dim3(kBlock), rank_lds_bytes(a.t), s, a);
   }
   return hipGetLastError();
 }
