@@ -604,6 +604,10 @@ __device__ __forceinline__ uint32_t slot_code(const StepArgs &a, const SpeciesAr
 // Particle state in either form, as the kernel's arithmetic type: cell (i, k), in-cell offsets
 // (fx, fz) and momentum.  FP64 keeps positions in cell units; the mixed form keeps the cell key
 // and FP32 offsets.  Src holds the species' source arrays in registers for the whole species.
+template <typename T>
+__device__ __forceinline__ T at(const T *p, int i) {  // i >= 0; byte offsets fit 32 bits
+  return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) + (uint32_t)i * (uint32_t)sizeof(T));
+}
 template <bool MIXED>
 struct Pstate;
 template <>
@@ -617,11 +621,11 @@ struct Pstate<false> {
     }
   };
   __device__ __forceinline__ void load(const Src &s, int p) {
-    x = s.a[0][p];
-    z = s.a[1][p];
-    u0 = s.a[2][p];
-    u1 = s.a[3][p];
-    u2 = s.a[4][p];
+    x = at(s.a[0], p);
+    z = at(s.a[1], p);
+    u0 = at(s.a[2], p);
+    u1 = at(s.a[3], p);
+    u2 = at(s.a[4], p);
   }
 };
 template <>
@@ -638,12 +642,12 @@ struct Pstate<true> {
     }
   };
   __device__ __forceinline__ void load(const Src &s, int p) {
-    cell = s.c[p];
-    x = s.a[0][p];
-    z = s.a[1][p];
-    u0 = s.a[2][p];
-    u1 = s.a[3][p];
-    u2 = s.a[4][p];
+    cell = at(s.c, p);
+    x = at(s.a[0], p);
+    z = at(s.a[1], p);
+    u0 = at(s.a[2], p);
+    u1 = at(s.a[3], p);
+    u2 = at(s.a[4], p);
   }
 };
 
@@ -885,7 +889,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   const int i1 = min(i0 + t.tx, g.nx), k1 = min(k0 + t.tz, g.nz);
   const int ntc = t.tx * t.tz;
   const int64_t nn = g.nnodes, nc = g.ncells;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
 
   extern __shared__ double lds[];
   char *ldsb = reinterpret_cast<char *>(lds);
@@ -1070,7 +1074,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
       // permutation of the one after it are on their way.  The loads of a group go out between
       // the push and the stores of the group before it: stores share the vector-memory counter
       // with loads, in order, so waiting for a load issued after stores would wait for the stores.
-      auto load_perm = [&]() { return (int)min((uint32_t)perm[jg + min(lane, max(ngr - 1, 0))], loc_max); };
+      auto load_perm = [&]() { return (int)min((uint32_t)at(perm, jg + min(lane, max(ngr - 1, 0))), loc_max); };
       int rc_ = r, jc = jg, nc_ = ngr;  // the current group
       Pstate<MIXED> ps{};
       T wp = K.w;
@@ -1080,7 +1084,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
       int rn = r, jn = jg, nn_ = ngr;  // the next group
       int pn = load_perm();
       ps.load(src, pc);
-      if constexpr (PW) wp = wsrc[pc * wstride];
+      if constexpr (PW) wp = at(wsrc, pc * wstride);
       // wait for the first loads here: a load pending on entry only would make the compiler wait
       // at the head of every iteration for everything issued before it
       asm volatile("" ::"v"(pn), "v"(ps.x), "v"(ps.z), "v"(ps.u0), "v"(ps.u1), "v"(ps.u2), "v"(wp));
@@ -1118,7 +1122,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
           auto next_loads = [&]() {
             pc = pn;
             ps.load(src, pc);
-            if constexpr (PW) wp = wsrc[pc * wstride];
+            if constexpr (PW) wp = at(wsrc, pc * wstride);
             gr += nwaves;
             settle();
             pn = load_perm();
@@ -1150,7 +1154,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             const uint32_t code = alive ? (uint32_t)((o.dk + 1) * 3 + (o.di + 1)) : kAbsorbed;
             // moments M^{n+3/2} at x^{n+3/2} with u^{n+1}, 1/gamma(u^{n+1}) and H^{n+3/2}
             // of the new cell
-            ring += o.dk * Lo.NW + o.di;
+            ring += __mul24(o.dk, Lo.NW) + o.di;
             key = ((lk + 1 + o.dk) << 16) | ring;
             m = compact_moments(K, o.rg1, o.n0, o.n1, o.n2, Hn[ring], Hn[Lo.NPL + ring], Hn[2 * Lo.NPL + ring]);
             dfx = o.fx;
@@ -1178,7 +1182,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             if (IDS && ok && sp.dst_id) sp.dst_id[j] = sp.src_id[p];
             if (ok && code != 4u) {
               atomicSub(&cntS[4 * ntc + hc], 1);
-              if (alive) atomicAdd(&cntS[code * ntc + hc], 1);
+              if (alive) atomicAdd(&cntS[__mul24((int)code, ntc) + hc], 1);
             }
           }
           if constexpr (PW) scale_compact(m, wcur);
@@ -1337,7 +1341,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             if (IDS && ok && sp.dst_id) sp.dst_id[loc] = sp.src_id[p];
             if (ok && code != 4u) {
               atomicSub(&cntS[4 * ntc + hc], 1);
-              if (alive) atomicAdd(&cntS[code * ntc + hc], 1);
+              if (alive) atomicAdd(&cntS[__mul24((int)code, ntc) + hc], 1);
             }
             // every particle goes to the LDS accumulators at once, or to the global planes if
             // it leaves the tile
@@ -1514,7 +1518,9 @@ void k_particles(const StepArgs a) {
   // clear the next order's tile flags (set by the scan of this cycle's sort); the grid has a
   // block for every tile index
   if (threadIdx.x == 0 && (int)blockIdx.x < a.t.ntiles) a.tile_active_next[blockIdx.x] = 0;
-  const int tile = block_tile(a.t, a.tile_list);
+  // (said to be uniform: after a branch on the thread the compiler takes the tile, and with it
+  // the loop over the tile's groups, to differ between lanes, and keeps both in vector registers)
+  const int tile = __builtin_amdgcn_readfirstlane(block_tile(a.t, a.tile_list));
   if (tile < 0) return;
   particles_body<PUSH, MIXED, IDS, PW, DIRECT>(a, tile);
 }
@@ -1567,7 +1573,7 @@ __device__ __forceinline__ void rank_body(const StepArgs &a, int tile, int speci
   const int i0 = txi * t.tx, k0 = tzi * t.tz;
   const int i1 = min(i0 + t.tx, g.nx), k1 = min(k0 + t.tz, g.nz);
   const int cw = i1 - i0, ch = k1 - k0, ncell = cw * ch;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
   extern __shared__ int ldsi[];
   const int RW = t.tx + 4, RH = t.tz + 4;  // ring of two cells: destinations +-1, their sources +-1
   int *btab = ldsi;                        // [cells][9]
