@@ -186,6 +186,12 @@ constexpr int64_t kDirectMinTiles = 256;
 // four 485, 32 x 1 465, 8 x 8 482, 32 x 2 515, 8 x 2 456 (but 18 us more in the ranker); 64 x 64
 // cells at 16 per cell: 8 x 2 with eight 21, 8 x 4 23, 32 x 2 27.
 //
+// A load that leaves most of the grid empty spreads over it, and tiles of a few cells, the cheapest
+// for it at the start, then number more than the GPU holds at once: 8 x 162 cells of a 179 x 162
+// grid, 16 per cell, start at 19 us with 4 x 4 and 20 with 8 x 4 and after 4,500 cycles take 41
+// and 29.  Such a load takes tiles of 32 cells or more.
+constexpr int kSlabTileCells = 32;
+
 // A batch's members share the GPU, so small tiles that fill it with one run's blocks only add
 // work: 8 x 4 cells and four wavefronts (32 uneven slab runs 306 us per FP64 cycle, with eight
 // 391, 32 x 4 346, 16 x 4 306, 8 x 2 368; ten runs in mixed precision 139, 16 x 2 139, 32 x 2 160).
@@ -224,7 +230,9 @@ void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
     const double kFixed = 12.0, kGroup = 1.2, kGroupWave = 1.1, kRankTile = 0.007;
     const double cus = 256.0;
     double best = 0.0;
+    const bool spreads = 2 * width * (ld.k_hi - ld.k_lo) < c->g.ncells;
     for (const auto &sh : shapes) {
+      if (!fixed && spreads && sh[0] * sh[1] < kSlabTileCells) continue;
       const int cx = fixed ? tx : sh[0], cz = fixed ? tz : sh[1];
       const int64_t ntx = std::max<int64_t>(1, tiles_over(ld.i_lo, ld.i_hi, cx));
       const int64_t ntz = std::max<int64_t>(1, tiles_over(ld.k_lo, ld.k_hi, cz));
