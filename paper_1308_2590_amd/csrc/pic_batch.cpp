@@ -84,9 +84,9 @@ pic_status grow(pic_batch *b, size_t n) {
   free_tables(b);
   BHIP(b, b->mem.get((void **)&b->d_step, 2 * cap * sizeof(pic::StepArgs)), "batch tables");
   BHIP(b, b->mem.get((void **)&b->d_field, 2 * cap * sizeof(pic::FieldArgs)), "batch tables");
-  BHIP(b, b->mem.get((void **)&b->d_par, cap * sizeof(int32_t)), "batch tables");
+  BHIP(b, b->mem.get((void **)&b->d_par, 2 * cap * sizeof(int32_t)), "batch tables");
   BHIP(b, b->mem.get((void **)&b->d_ctr, cap * sizeof(int64_t)), "batch tables");
-  BHIP(b, b->mem.get((void **)&b->d_pre, 6 * (cap + 1) * sizeof(int32_t)), "batch tables");
+  BHIP(b, b->mem.get((void **)&b->d_pre, 5 * (cap + 1) * sizeof(int32_t)), "batch tables");
   b->cap = cap;
   return PIC_OK;
 }
@@ -101,7 +101,7 @@ pic_status rebuild(pic_batch *b) {
   std::vector<pic::FieldArgs> fields(2 * n);
   std::vector<int32_t> par(n);
   std::vector<int64_t> ctr(n);
-  std::vector<int32_t> pre(6 * (n + 1), 0);
+  std::vector<int32_t> pre(5 * (n + 1), 0);
   size_t lds_p = 0, lds_r = 0;
   bool ids = false, pw = false;
   // one block size for all members: the smallest of theirs (each fits its own tile in LDS)
@@ -123,12 +123,11 @@ pic_status rebuild(pic_batch *b) {
     par[r] = c->cur;
     ctr[r] = c->step;
     const pic::GridArgs &g = c->g;
-    const int32_t items[4] = {
+    const int32_t items[3] = {
         (int32_t)((g.nnodes + pic::kSolveNodes * pic::kBlock - 1) / (pic::kSolveNodes * pic::kBlock)),
         (int32_t)((g.ncells + pic::kHCells * pic::kBlock - 1) / (pic::kHCells * pic::kBlock)),
-        c->n_scan1_blocks * c->S,
-        1};
-    for (int k = 0; k < 4; ++k) pre[k * (n + 1) + r + 1] = pre[k * (n + 1) + r] + items[k];
+        c->n_scan_blocks * c->S};
+    for (int k = 0; k < 3; ++k) pre[k * (n + 1) + r + 1] = pre[k * (n + 1) + r] + items[k];
     lds_p = std::max(lds_p, pic::particle_lds_bytes(c->g, c->tiles, b->precision == PIC_PREC_MIXED, waves));
     lds_r = std::max(lds_r, pic::rank_lds_bytes(c->tiles));
   }
@@ -149,15 +148,15 @@ pic_status rebuild(pic_batch *b) {
   a.step = b->d_step;
   a.field = b->d_field;
   a.par = b->d_par;
+  a.par_rank = b->d_par + n;
   a.step_ctr = b->d_ctr;
   a.nruns = (int32_t)n;
   const size_t stride = n + 1;
   a.pre_nodes = b->d_pre + 0 * stride;
   a.pre_cells = b->d_pre + 1 * stride;
   a.pre_scan = b->d_pre + 2 * stride;
-  a.pre_one = b->d_pre + 3 * stride;
-  a.pre_tiles = b->d_pre + 4 * stride;
-  a.pre_rank = b->d_pre + 5 * stride;
+  a.pre_tiles = b->d_pre + 3 * stride;
+  a.pre_rank = b->d_pre + 4 * stride;
   pic::BatchLaunch &l = b->launch;
   l.mixed = b->precision == PIC_PREC_MIXED;
   l.ids = ids;

@@ -305,7 +305,7 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   // kernel of the mover options, which accumulates full counts)
   a.count_masks = (a.rank_cells && !c->mover) ? 1 : 0;
   a.n_scan_blocks = c->n_scan_blocks;
-  a.n_scan1_blocks = c->n_scan1_blocks;
+  a.block_sums = !c->mover;
   a.nsp = c->S;
   const int cur = c->cur, nxt = 1 - c->cur;
   for (int s = 0; s < c->S; ++s) {
@@ -632,7 +632,6 @@ pic_status pic_init_grid(const pic_grid_desc *d, pic_ctx **out) {
   c->laser = pic::LaserArgs{d->laser_a0, d->laser_omega, d->laser_sigma_z, d->laser_z_center,
                             d->laser_fwhm_t, d->laser_t_center};
   c->n_scan_blocks = (int32_t)((g.ncells + pic::kScanBlock - 1) / pic::kScanBlock);
-  c->n_scan1_blocks = (int32_t)((g.ncells + pic::kScan1Block - 1) / pic::kScan1Block);
   pic::LoadShape empty;
   empty.i_hi = g.nx;
   empty.k_hi = g.nz;
@@ -757,6 +756,8 @@ pic_status pic_load_particles(pic_ctx *c, int32_t s, double q, double m, int64_t
   if (fill_wait(c, st.arr, 0, (size_t)nc * sizeof(int32_t)) != hipSuccess)
     return bail(fail(c, PIC_ERR_DEVICE, "clear arrivals"));
   if ((rs = dalloc(c, &st.bsum, (size_t)c->n_scan_blocks, "alloc scan sums")) != PIC_OK) return bail(rs);
+  if (fill_wait(c, st.bsum, 0, (size_t)c->n_scan_blocks * sizeof(int32_t)) != hipSuccess)
+    return bail(fail(c, PIC_ERR_DEVICE, "clear scan sums"));
   {
     auto up = [&](void *dst, const void *src, size_t bytes) {
       const hipError_t e = copy_wait(c, dst, src, bytes, hipMemcpyHostToDevice);

@@ -96,8 +96,7 @@ struct pic_ctx {
   bool rank_cells_auto = false;  // the automatic choice, made with the tile shape
   bool direct = false;           // the particle kernel's direct form (about 2 particles per lane and row)
   int32_t waves = 4;             // wavefronts per block of its grouped form
-  int32_t n_scan_blocks = 0;
-  int32_t n_scan1_blocks = 0;  // blocks of the scan of a cycle's sort
+  int32_t n_scan_blocks = 0;     // blocks of the scan of a cycle's sort
   std::string err;
   // profiling
   bool prof_on = false;

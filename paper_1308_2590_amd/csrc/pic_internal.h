@@ -17,11 +17,9 @@ constexpr int kMaxWaves = 8;       // most wavefronts per block of the particle 
 constexpr int kPermPad = 8;        // padding entries after each permutation array
 constexpr int kSolveNodes = 2;     // nodes per thread in the E solve
 constexpr int kHCells = 2;         // cells per thread in the H update
-constexpr int kScanItems = 4;      // cells per thread in the count scan
 constexpr int kFlagNodes = 8;      // consecutive nodes per deposit flag
+constexpr int kScanItems = 4;      // cells per thread in the scan of a cycle's sort
 constexpr int kScanBlock = kBlock * kScanItems;
-constexpr int kScan1Items = 4;      // cells per thread in the scan of a cycle's sort
-constexpr int kScan1Block = kBlock * kScan1Items;
 
 struct GridArgs {
   int32_t nx, nz, nxn, nzn;  // cells and nodes per axis
@@ -76,7 +74,7 @@ struct SpeciesArgs {
   // the counts of set bits are written (the others keep values from earlier cycles)
   uint16_t *cmask;
   int32_t *arr;              // [ncells] particles arriving in each cell; zero between cycles
-  int32_t *bsum;             // block sums of the count scan
+  int32_t *bsum;             // particles arriving per kScanBlock cells; zero between cycles
   int32_t cap;               // particle capacity of the state arrays
   int32_t active;
 };
@@ -91,7 +89,7 @@ struct StepArgs {
   int32_t slot_codes;        // 1: the particle kernel writes a byte per slot (see locode)
   int32_t waves;             // wavefronts per block of the grouped form
   int32_t count_masks;       // 1: the particle kernel writes code masks and nonzero counts only
-  int32_t n_scan_blocks;     // blocks of the count scan per species
+  int32_t block_sums;        // 1: the particle kernel sums the arrivals per scan block (bsum)
   int32_t nsp;               // species slots
   SpeciesArgs sp[kMaxSpecies];
   const double *Eold, *Enew; // E^n, E^{n+1} [3][nodes]: E-bar is their mean
@@ -106,7 +104,7 @@ struct StepArgs {
   uint8_t *tile_active_next;
   int32_t *tile_list_next;
   uint8_t *mflag;            // deposit flags (see FieldArgs): set for every node the fold adds to
-  int32_t n_scan1_blocks;   // blocks of kScan1Block cells in a cycle's sort scan
+  int32_t n_scan_blocks;     // blocks of kScanBlock cells in a cycle's sort scan
 };
 
 struct FieldArgs {
@@ -128,21 +126,20 @@ struct FieldArgs {
 };
 
 // Many independent runs stepped together, each kernel launched once for all of them (a block
-// per work item for the field, particle and rank kernels, persistent blocks looping over the
-// items of the scans).  Per run, the step and field arguments for both
+// per work item, and extra blocks for the work prefixes and the end of the cycle).  Per run, the step and field arguments for both
 // buffer parities live in device memory, and the run's current parity and cycle count are
 // device counters, so one captured cycle can be replayed for any mix of runs.
 struct BatchArgs {
   const StepArgs *step;      // [2 * nruns]: run r, parity p at 2 r + p
   const FieldArgs *field;    // [2 * nruns]
   int32_t *par;              // [nruns] buffer parity of the current cycle
+  int32_t *par_rank;         // [nruns] its copy for the rank kernel, which flips par
   int64_t *step_ctr;         // [nruns] cycles done (E^n is at step * dt)
   int32_t nruns;
   // exclusive prefix sums over runs ([nruns + 1]) of the work items of each kernel
   const int32_t *pre_nodes;  // blocks of kSolveNodes * kBlock nodes
   const int32_t *pre_cells;  // blocks of kHCells * kBlock cells
-  const int32_t *pre_scan;   // scan blocks x species slots (both passes of the sort's scan)
-  const int32_t *pre_one;    // one item per run
+  const int32_t *pre_scan;   // scan blocks x species slots
   int32_t *pre_tiles;        // active tiles of the current order (written each cycle)
   int32_t *pre_rank;         // active tiles x species slots (written each cycle)
 };
@@ -167,7 +164,7 @@ size_t rank_lds_bytes(const TileArgs &t);
 
 hipError_t launch_field_solve(const FieldArgs &a, hipStream_t s);
 // launch_particles also clears the next order's tile flags, which the sort's scan sets again;
-// launch_sort is the sort of a cycle (two-pass scan with tile flags and list, then ranks).
+// launch_sort is the sort of a cycle (scan with tile flags, then ranks and tile list).
 hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t s);
 hipError_t launch_sort(const StepArgs &a, hipStream_t s);
 // The particle stage with mover options (PIC_MOVER_* bits), one thread per slot: max_n bounds

@@ -18,14 +18,14 @@
 //               It also counts the particles leaving each cell per move code and arriving in
 //               each cell.  Instantiated for FP64 and for the mixed form (FP32 particles).
 // Sort (stable by cell, removed particles dropped):
-//   k_scan_counts / k_scan_apply  exclusive scan of the arrival counts -> next cell start
-//               offsets (per block, then the block totals added), the tiles holding particles
-//               in the next order as flags and, from one extra block, as an ordered list;
-//   k_tile_flags / k_tile_compact  the same flags and list from cell starts (after loads);
-//   kb_scan1 / kb_scan2  the same two passes for every run of a batch;
+//   k_scan      exclusive scan of the arrival counts -> next cell start offsets, and flags of
+//               the tiles holding particles in the next order;
+//   k_tile_flags / k_tile_compact  the same flags and the ordered tile list from cell starts
+//               (after loads);
 //   k_rank / k_rank_cells  stable destination of every particle: cell start + particles arriving from
 //               source cells with a smaller key + rank within (source cell, move code),
-//               written as the next cycle's slot -> location permutation.
+//               written as the next cycle's slot -> location permutation; one extra block
+//               makes the next order's tile list.
 // Positions never move more than one cell per cycle because dt <= min(dx, dz) and |v| < c,
 // which is what keeps the sort a 3x3 neighbourhood redistribution.
 //
@@ -394,6 +394,28 @@ __device__ __forceinline__ void store_or_drop(uint8_t *p, int i, bool on, uint8_
 }
 __device__ __forceinline__ void store_or_drop(uint32_t *p, int i, bool on, uint32_t v) {
   __builtin_amdgcn_raw_buffer_store_b32(v, store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
+}
+
+// Inclusive sums over the wavefront (all lanes active), by DPP: along rows of 16, then the rows.
+__device__ __forceinline__ int wave_sums(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111 /* row_shr:1 */, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142 /* row_bcast:15 */, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143 /* row_bcast:31 */, 0xc, 0xf, false);
+  return v;
+}
+
+// Arrivals v of a cell per lane (all lanes active), added per scan block of cells: the last lane of
+// each run of cells in one block adds the run's sum (a tile's rows lie in a few blocks).
+__device__ __forceinline__ void add_block_sums(int32_t *bsum, int v, int cell, int lane) {
+  const int blk = (int)((uint32_t)cell / (uint32_t)kScanBlock);
+  const int before = lane_before(blk), inc = wave_sums(v);
+  const uint64_t heads = __ballot(lane == 0 || before != blk);
+  const int first = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+  const int sum = inc - __shfl(inc - v, first, 64);
+  if ((((heads >> 1) | 1ull << 63) >> lane & 1ull) && sum) atomicAdd(&bsum[blk], sum);
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -1481,32 +1503,38 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   if (PUSH) {
     // The particles the tile's cells send to each cell of the tile and its ring (the cell
     // (x - dx, z - dz) sends count[code (dx, dz)]), added to the per-cell arrival counts: the
-    // sort's scan reads those instead of gathering nine counts per cell.
-    // (the layout with the ring sums them in LDS during the count pass)
+    // sort's scan reads those instead of gathering nine counts per cell, and to the sums per scan
+    // block.  (The layout with the ring sums them in LDS during the count pass.)
     if constexpr (!kTileOnly) __syncthreads();
-    for (int s = 0; s < a.nsp; ++s) {
+    // 64 cells per wavefront, the species dealt to the wavefronts too: with every thread doing one
+    // species after the other most wavefronts stood idle, 1.5 us of the 8 x 4 tiles' time on a foil.
+    const int n_part = (AW * AH + 63) >> 6;
+    const SmallDiv div_part(n_part), div_aw(AW);
+    for (int u = wave; u < a.nsp * n_part; u += nwaves) {
+      const int s = __builtin_amdgcn_readfirstlane(div_part.q(u));
       const SpeciesArgs &sp = a.sp[s];
       if (!sp.active) continue;
       const int *cntS = cntL + s * ntc * kMoveCodes;
       const int *arrS = arrL + s * AW * AH;
-      for (int e = threadIdx.x; e < AW * AH; e += blockDim.x) {
-        const int az = SmallDiv(AW).q(e), ax = e - az * AW;
-        int v = 0;
-        if constexpr (kTileOnly) {
+      const int e1 = (u - s * n_part) * 64 + lane, e = min(e1, AW * AH - 1);
+      const int az = div_aw.q(e), ax = e - az * AW;
+      int v = 0;
+      if constexpr (kTileOnly) {
 #pragma unroll
-          for (int d = 0; d < kMoveCodes; ++d) {
-            const int sx = ax - d % 3, sz = az - d / 3;  // the source cell, tile-local
-            if (sx >= 0 && sx < cw && sz >= 0 && sz < chh) v += cntS[d * ntc + sz * t.tx + sx];
-          }
-        } else {
-          v = arrS[e];
+        for (int d = 0; d < kMoveCodes; ++d) {
+          const int sx = ax - d % 3, sz = az - d / 3;  // the source cell, tile-local
+          if (sx >= 0 && sx < cw && sz >= 0 && sz < chh) v += cntS[d * ntc + sz * t.tx + sx];
         }
-        if (v == 0) continue;
-        int gi = i0 - 1 + ax;
-        const int gk = wrap1(k0 - 1 + az, g.nz);
-        if (g.bc_x == PIC_BC_PERIODIC) gi = wrap1(gi, g.nx);
-        atomicAdd(&sp.arr[(int64_t)gk * g.nx + gi], v);
+      } else {
+        v = arrS[e];
       }
+      if (e1 != e) v = 0;
+      int gi = i0 - 1 + ax;
+      const int gk = wrap1(k0 - 1 + az, g.nz);
+      if (g.bc_x == PIC_BC_PERIODIC) gi = wrap1(gi, g.nx);
+      const int cell = gk * g.nx + gi;
+      if (v) atomicAdd(&sp.arr[cell], v);
+      add_block_sums(sp.bsum, v, cell, lane);
     }
   }
 }
@@ -1887,22 +1915,6 @@ __device__ __forceinline__ void rank_cells_body(const StepArgs &a, int tile, int
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_rank_cells(const StepArgs a) {
-  const int tile = block_tile(a.t, a.tile_list);
-  if (tile < 0) return;
-  if (a.count_masks)
-    rank_cells_body<true>(a, tile, blockIdx.y);
-  else
-    rank_cells_body<false>(a, tile, blockIdx.y);
-}
-
-template <int LPC>
-__global__ __launch_bounds__(kBlock) void k_rank(const StepArgs a) {
-  const int tile = block_tile(a.t, a.tile_list);
-  if (tile < 0) return;
-  rank_body<LPC>(a, tile, blockIdx.y);
-}
-
 // Flag per tile: does it hold particles of any species in the order given by the cell starts
 // (the current order, or the next one when from_next is set).  One thread per tile.
 __device__ __forceinline__ void tile_flags_body(const StepArgs &a, int tile, int from_next) {
@@ -1932,10 +1944,11 @@ __global__ __launch_bounds__(kBlock) void k_tile_flags(const StepArgs a, int fro
 // neighbouring tiles.
 __device__ __forceinline__ void tile_compact_body(const StepArgs &a) {
   __shared__ int sh[1024 / 64];
-  // A pass takes 64 flags per thread (four 16-byte words; tb is a multiple of 64), counts them
-  // with popcounts (flags are 0 or 1), places them with one block scan and writes the active
-  // tiles in order.
-  constexpr int kPer = 64;
+  // A pass takes 16 flags per thread (a 16-byte word; tb is a multiple of 16), counts them with
+  // popcounts (flags are 0 or 1), places them with one block scan and writes the active tiles in
+  // order.  (More flags per thread would raise the registers of the rank kernels, which run this
+  // in one block beside their own.)
+  constexpr int kPer = 16;
   const int ntiles = a.t.ntiles;
   const uint8_t *flags = a.tile_active_next;
   int carry = 0;
@@ -1984,50 +1997,59 @@ __device__ __forceinline__ void tile_compact_body(const StepArgs &a) {
 
 __global__ __launch_bounds__(1024) void k_tile_compact(const StepArgs a) { tile_compact_body(a); }
 
-// ---- two-pass scan of a cycle's sort --------------------------------------------------------
-// Pass 1 (k_scan_counts): per block of kScan1Block cells, the exclusive scan of the arrival
-// counts within the block (cleared for the next cycle), the block total, and the next order's
-// tile flags (a tile is active when particles arrive in one of its cells; the particle kernel
-// of the cycle cleared the flags).  Pass 2 (k_scan_apply): every block adds the totals of the
-// blocks before it; one extra block compacts the tile flags into the ordered tile list.
-__device__ __forceinline__ void scan1_body(const StepArgs &a, int bx, int s) {
-  __shared__ int sh[kBlock / 64];
+// ---- scan of a cycle's sort -----------------------------------------------------------------
+// Block bx of species s: the arrivals before its kScanBlock cells from the block sums, which the
+// particle kernel makes beside the arrival counts, then the exclusive scan of its own counts
+// (cleared for the next cycle) into the next order's cell starts, and the next order's tile flags
+// (a tile is active when particles arrive in one of its cells; the particle kernel of the cycle
+// cleared the flags).  One pass over the counts, without waiting for other blocks: a second
+// kernel that added the block totals took 4 to 6 us a cycle on small grids and 32 us on 2048 x
+// 2048 cells (the list of tiles was made there too).
+__device__ __forceinline__ void scan_body(const StepArgs &a, int bx, int s) {
+  __shared__ int sh[2 * kBlock / 64];
   const SpeciesArgs &sp = a.sp[s];
   if (!sp.active) return;
   const GridArgs &g = a.g;
-  const int64_t c0 = (int64_t)bx * kScan1Block + (int64_t)threadIdx.x * kScan1Items;
-  int in[kScan1Items];
-  if (c0 + kScan1Items <= g.ncells) {
-    int4 *p4 = reinterpret_cast<int4 *>(sp.arr + c0);
-#pragma unroll
-    for (int q = 0; q < kScan1Items / 4; ++q) {
-      const int4 v = p4[q];
-      in[4 * q] = v.x;
-      in[4 * q + 1] = v.y;
-      in[4 * q + 2] = v.z;
-      in[4 * q + 3] = v.w;
-      if (v.x | v.y | v.z | v.w) p4[q] = make_int4(0, 0, 0, 0);
-    }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t c0 = (int64_t)bx * kScanBlock + (int64_t)threadIdx.x * kScanItems;
+  const bool whole = c0 + kScanItems <= g.ncells;
+  static_assert(kScanItems == 4, "one int4 per thread");
+  int in[kScanItems] = {0, 0, 0, 0};
+  if (whole) {
+    const int4 v = *reinterpret_cast<const int4 *>(sp.arr + c0);
+    in[0] = v.x;
+    in[1] = v.y;
+    in[2] = v.z;
+    in[3] = v.w;
   } else {
 #pragma unroll
-    for (int q = 0; q < kScan1Items; ++q) {
-      const int64_t c = c0 + q;
-      int v = 0;
-      if (c < g.ncells) {
-        v = sp.arr[c];
-        if (v) sp.arr[c] = 0;
-      }
-      in[q] = v;
-    }
+    for (int q = 0; q < kScanItems; ++q)
+      if (c0 + q < g.ncells) in[q] = sp.arr[c0 + q];
   }
-  int sum = 0;
-#pragma unroll
-  for (int q = 0; q < kScan1Items; ++q) sum += in[q];
+  // the sums of the blocks before this one (up to 16 per thread on a 2048 x 2048 grid): unrolled
+  // so that a thread's loads are issued together
+  int part = 0;
+#pragma unroll 8
+  for (int b = threadIdx.x; b < bx; b += kBlock) part += sp.bsum[b];
+  const int sum = in[0] + in[1] + in[2] + in[3];
+  const int inc = wave_incl_scan(sum, lane);
+  part = wave_sums(part);
+  if (lane == 63) {
+    sh[wave] = inc;
+    sh[kBlock / 64 + wave] = part;
+  }
   if (sum) {
+    if (whole) {
+      *reinterpret_cast<int4 *>(sp.arr + c0) = make_int4(0, 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kScanItems; ++q)
+        if (in[q]) sp.arr[c0 + q] = 0;
+    }
     int k = (int)(c0 / g.nx), i = (int)(c0 - (int64_t)k * g.nx);
     const SmallDiv div_tx(a.t.tx), div_tz(a.t.tz);
 #pragma unroll
-    for (int q = 0; q < kScan1Items; ++q) {
+    for (int q = 0; q < kScanItems; ++q) {
       if (in[q] && k < g.nz) a.tile_active_next[div_tz.q(k) * a.t.ntx + div_tx.q(i)] = 1;
       if (++i == g.nx) {
         i = 0;
@@ -2035,78 +2057,82 @@ __device__ __forceinline__ void scan1_body(const StepArgs &a, int bx, int s) {
       }
     }
   }
-  int total;
-  int run = block_excl_scan(sum, sh, &total);
-  if (c0 + kScan1Items <= g.ncells) {
-    int4 *o4 = reinterpret_cast<int4 *>(sp.cs_new + c0);
+  __syncthreads();
+  int run = inc - sum, total = 0;
 #pragma unroll
-    for (int q = 0; q < kScan1Items / 4; ++q) {
-      int4 v;
-      v.x = run;
-      run += in[4 * q];
-      v.y = run;
-      run += in[4 * q + 1];
-      v.z = run;
-      run += in[4 * q + 2];
-      v.w = run;
-      run += in[4 * q + 3];
-      o4[q] = v;
-    }
+  for (int w = 0; w < kBlock / 64; ++w) {
+    run += sh[kBlock / 64 + w] + (w < wave ? sh[w] : 0);
+    total += sh[kBlock / 64 + w] + sh[w];
+  }
+  if (whole) {
+    int4 v;
+    v.x = run;
+    v.y = v.x + in[0];
+    v.z = v.y + in[1];
+    v.w = v.z + in[2];
+    *reinterpret_cast<int4 *>(sp.cs_new + c0) = v;
   } else {
 #pragma unroll
-    for (int q = 0; q < kScan1Items; ++q) {
-      const int64_t c = c0 + q;
-      if (c < g.ncells) sp.cs_new[c] = run;
+    for (int q = 0; q < kScanItems; ++q) {
+      if (c0 + q < g.ncells) sp.cs_new[c0 + q] = run;
       run += in[q];
     }
   }
-  if (threadIdx.x == 0) sp.bsum[bx] = total;
+  if (bx == a.n_scan_blocks - 1 && threadIdx.x == 0) sp.cs_new[g.ncells] = total;
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_counts(const StepArgs a) {
-  scan1_body(a, blockIdx.x, blockIdx.y);
+__global__ __launch_bounds__(kBlock) void k_scan(const StepArgs a) {
+  scan_body(a, blockIdx.x, blockIdx.y);
 }
 
-// Pass 2 for block bx of species s (bx < n_scan1_blocks).
-__device__ __forceinline__ void scan2_body(const StepArgs &a, int bx, int s) {
+// The block sums from the arrival counts, after a particle kernel that does not make them.
+__global__ __launch_bounds__(kBlock) void k_block_sums(const StepArgs a) {
   __shared__ int sh[kBlock / 64];
-  const int nb = a.n_scan1_blocks;
-  const SpeciesArgs &sp = a.sp[s];
+  const SpeciesArgs &sp = a.sp[blockIdx.y];
   if (!sp.active) return;
-  // the totals of the blocks before this one (up to 16 per thread on a 2048 x 2048 grid):
-  // unrolled so that a thread's loads are issued together
-  int part = 0;
-#pragma unroll 8
-  for (int b = threadIdx.x; b < bx; b += blockDim.x) part += sp.bsum[b];
-  int prefix;
-  (void)block_excl_scan(part, sh, &prefix);
-  const GridArgs &g = a.g;
-  const int64_t c0 = (int64_t)bx * kScan1Block + (int64_t)threadIdx.x * kScan1Items;
-  if (c0 + kScan1Items <= g.ncells) {
-    int4 *o4 = reinterpret_cast<int4 *>(sp.cs_new + c0);
+  const int64_t c0 = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
+  int v = 0;
 #pragma unroll
-    for (int q = 0; q < kScan1Items / 4; ++q) {
-      int4 v = o4[q];
-      v.x += prefix;
-      v.y += prefix;
-      v.z += prefix;
-      v.w += prefix;
-      o4[q] = v;
-    }
-  } else {
-    for (int q = 0; q < kScan1Items; ++q)
-      if (c0 + q < g.ncells) sp.cs_new[c0 + q] += prefix;
-  }
-  if (bx == nb - 1 && threadIdx.x == 0) sp.cs_new[g.ncells] = prefix + sp.bsum[bx];
+  for (int q = 0; q < kScanItems; ++q)
+    if (c0 + q * kBlock < a.g.ncells) v += sp.arr[c0 + q * kBlock];
+  v = wave_sums(v);
+  if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) sp.bsum[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_apply(const StepArgs a) {
-  const int s = blockIdx.y, bx = blockIdx.x;
-  if (bx == a.n_scan1_blocks) {
-    if (s == 0) tile_compact_body(a);
+// What one extra block of the rank kernels does: the next order's tile list, and the block sums
+// cleared for the next cycle.
+__device__ __forceinline__ void sort_end_body(const StepArgs &a) {
+  tile_compact_body(a);
+  for (int s = 0; s < a.nsp; ++s)
+    if (a.sp[s].active)
+      for (int b = threadIdx.x; b < a.n_scan_blocks; b += blockDim.x) a.sp[s].bsum[b] = 0;
+}
+
+// (the extra block is the last of the first species: it starts before the other species' blocks)
+__global__ __launch_bounds__(kBlock) void k_rank_cells(const StepArgs a) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (blockIdx.y == 0) sort_end_body(a);
     return;
   }
-  scan2_body(a, bx, s);
+  const int tile = block_tile(a.t, a.tile_list);
+  if (tile < 0) return;
+  if (a.count_masks)
+    rank_cells_body<true>(a, tile, blockIdx.y);
+  else
+    rank_cells_body<false>(a, tile, blockIdx.y);
+}
+
+template <int LPC>
+__global__ __launch_bounds__(kBlock) void k_rank(const StepArgs a) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (blockIdx.y == 0) sort_end_body(a);
+    return;
+  }
+  const int tile = block_tile(a.t, a.tile_list);
+  if (tile < 0) return;
+  rank_body<LPC>(a, tile, blockIdx.y);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2140,8 +2166,8 @@ __device__ __forceinline__ int find_run(const int32_t *pre, int nruns, int w) {
 
 // The argument tables are read through the constant address space: they do not change during
 // a launch, so their fields can be loaded into scalar registers like kernel arguments.
-__device__ __forceinline__ const StepArgs &run_step(const BatchArgs &b, int r) {
-  const int p = b.par[r];
+__device__ __forceinline__ const StepArgs &run_step(const BatchArgs &b, int r, const int32_t *par) {
+  const int p = par[r];
   const StepArgs __attribute__((address_space(4))) *t =
       (const StepArgs __attribute__((address_space(4))) *)(b.step);
   return *(const StepArgs *)(t + 2 * r + p);
@@ -2165,24 +2191,19 @@ __global__ __launch_bounds__(kBlock) void kb_solve_e(const BatchArgs b, int tota
   solve_e_body(fa, tE, (int64_t)(w - b.pre_nodes[r]) * (kSolveNodes * kBlock) + threadIdx.x, kBlock);
 }
 
-__global__ __launch_bounds__(kBlock) void kb_update_h(const BatchArgs b, int total) {
-  const int w = (int)xcd_band_block(total);
-  if (w < 0) return;
-  const int r = find_run(b.pre_cells, b.nruns, w);
-  update_h_body(run_field(b, r), (int64_t)(w - b.pre_cells[r]) * (kHCells * kBlock) + threadIdx.x, kBlock);
-}
-
-// Work prefixes of the active tiles of every run's current order (one block).
-__global__ __launch_bounds__(1024) void kb_prefix(const BatchArgs b) {
-  __shared__ int sh[1024 / 64];
+// Work prefixes of the active tiles of every run's current order, and the parities' copy for the
+// rank kernel (one block of the H update).
+__device__ __forceinline__ void batch_prefix_body(const BatchArgs &b) {
+  __shared__ int sh[kBlock / 64];
   int carry_t = 0, carry_r = 0;
   for (int base = 0; base < b.nruns; base += blockDim.x) {
     const int r = base + threadIdx.x;
     int nt = 0, nr = 0;
     if (r < b.nruns) {
-      const StepArgs &sa = run_step(b, r);
+      const StepArgs &sa = run_step(b, r, b.par);
       nt = sa.tile_list[sa.t.ntiles];
       nr = nt * sa.nsp;
+      b.par_rank[r] = b.par[r];
     }
     int tot_t, tot_r;
     const int off_t = block_excl_scan(nt, sh, &tot_t);
@@ -2200,64 +2221,64 @@ __global__ __launch_bounds__(1024) void kb_prefix(const BatchArgs b) {
   }
 }
 
+__global__ __launch_bounds__(kBlock) void kb_update_h(const BatchArgs b, int total) {
+  if (blockIdx.x == gridDim.x - 1) {
+    batch_prefix_body(b);
+    return;
+  }
+  const int w = (int)xcd_band_block(total);
+  if (w < 0) return;
+  const int r = find_run(b.pre_cells, b.nruns, w);
+  update_h_body(run_field(b, r), (int64_t)(w - b.pre_cells[r]) * (kHCells * kBlock) + threadIdx.x, kBlock);
+}
+
 // The particle and rank kernels' items (active tiles, and tiles x species) change every cycle;
 // they launch one block per item any run could have, and the blocks past the cycle's items
 // return at once, so the hardware hands the items, of very unequal cost, to the CUs as they
 // free up.  Block b takes item b: consecutive items (the tiles of one run) go to different
 // XCDs.  (Contiguous bands of items per XCD, as in a single run, were measured slower: runs
 // differ in cost, so the bands load the XCDs unequally.)
-__device__ __forceinline__ int batch_item(int total) {
-  const int w = (int)blockIdx.x;
-  return w < total ? w : -1;
-}
+__device__ __forceinline__ int batch_item(int w, int total) { return w < total ? w : -1; }
 
 template <bool MIXED, bool IDS, bool PW>
 __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void kb_particles(const BatchArgs b) {
-  const int w = batch_item(b.pre_tiles[b.nruns]);
+  const int w = batch_item((int)blockIdx.x, b.pre_tiles[b.nruns]);
   if (w < 0) return;
   const int r = find_run(b.pre_tiles, b.nruns, w);
-  const StepArgs &sa = run_step(b, r);
+  const StepArgs &sa = run_step(b, r, b.par);
   particles_body<true, MIXED, IDS, PW>(sa, sa.tile_list[w - b.pre_tiles[r]]);
 }
 
-// The two-pass scan of every run's sort, as in a single run: pass 1 over (run, species, block
-// of cells) items; pass 2 over the same items, then one tile-list compaction item per run.
-// The next order's tile flags were cleared by the H update of the cycle.
-__global__ __launch_bounds__(kBlock) void kb_scan1(const BatchArgs b) {
-  const int total = b.pre_scan[b.nruns];
-  for (int w = blockIdx.x; w < total; w += gridDim.x) {
-    const int r = find_run(b.pre_scan, b.nruns, w);
-    const StepArgs &sa = run_step(b, r);
-    const int li = w - b.pre_scan[r];
-    const int s = li / sa.n_scan1_blocks;
-    scan1_body(sa, li - s * sa.n_scan1_blocks, s);
-    __syncthreads();
-  }
+// The scan of every run's sort, over (run, species, block of cells) items, which are fixed between
+// rebuilds: a block per item.  The next order's tile flags were cleared by the H update of the
+// cycle.
+__global__ __launch_bounds__(kBlock) void kb_scan(const BatchArgs b, int total) {
+  const int w = (int)blockIdx.x;
+  if (w >= total) return;
+  const int r = find_run(b.pre_scan, b.nruns, w);
+  const StepArgs &sa = run_step(b, r, b.par);
+  const int li = w - b.pre_scan[r];
+  const int s = li / sa.n_scan_blocks;
+  scan_body(sa, li - s * sa.n_scan_blocks, s);
 }
 
-__global__ __launch_bounds__(kBlock) void kb_scan2(const BatchArgs b) {
-  const int nscan = b.pre_scan[b.nruns];
-  const int total = nscan + b.nruns;
-  for (int w = blockIdx.x; w < total; w += gridDim.x) {
-    if (w >= nscan) {
-      tile_compact_body(run_step(b, w - nscan));
-    } else {
-      const int r = find_run(b.pre_scan, b.nruns, w);
-      const StepArgs &sa = run_step(b, r);
-      const int li = w - b.pre_scan[r];
-      const int s = li / sa.n_scan1_blocks;
-      scan2_body(sa, li - s * sa.n_scan1_blocks, s);
-    }
-    __syncthreads();
-  }
-}
-
+// The ranks, after one block per run for the end of its sort and of its cycle: buffer parity
+// flipped and cycle counted (the kernel's other blocks read the parities' copy).
 __global__ __launch_bounds__(kBlock) void kb_rank(const BatchArgs b) {
-  const int w = batch_item(b.pre_rank[b.nruns]);
+  if ((int)blockIdx.x < b.nruns) {
+    const int r = (int)blockIdx.x;
+    sort_end_body(run_step(b, r, b.par_rank));
+    if (threadIdx.x == 0) {
+      b.par[r] = b.par_rank[r] ^ 1;
+      b.step_ctr[r] += 1;
+    }
+    return;
+  }
+  const int w = batch_item((int)blockIdx.x - b.nruns, b.pre_rank[b.nruns]);
   if (w < 0) return;
   const int r = find_run(b.pre_rank, b.nruns, w);
-  const StepArgs &sa = run_step(b, r);
+  const StepArgs &sa = run_step(b, r, b.par_rank);
   const int li = w - b.pre_rank[r];
   const int idx = li / sa.nsp;
   if (sa.rank_cells && sa.count_masks)
@@ -2266,15 +2287,6 @@ __global__ __launch_bounds__(kBlock) void kb_rank(const BatchArgs b) {
     rank_cells_body<false>(sa, sa.tile_list[idx], li - idx * sa.nsp);
   else
     rank_body<16>(sa, sa.tile_list[idx], li - idx * sa.nsp);
-}
-
-// End of a cycle: flip every run's buffer parity and count the cycle.
-__global__ void kb_end(const BatchArgs b) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < b.nruns) {
-    b.par[r] ^= 1;
-    b.step_ctr[r] += 1;
-  }
 }
 
 __global__ void k_iota(int32_t *p, int64_t n) {
@@ -2347,11 +2359,10 @@ hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t s) {
 }
 
 hipError_t launch_sort(const StepArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_scan_counts, dim3((unsigned)a.n_scan1_blocks, (unsigned)a.nsp), dim3(kBlock), 0,
-                     s, a);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)a.n_scan1_blocks + 1u, (unsigned)a.nsp), dim3(kBlock),
-                     0, s, a);
-  const dim3 grid(8u * (unsigned)a.t.per_xcd, (unsigned)a.nsp);
+  const dim3 scan((unsigned)a.n_scan_blocks, (unsigned)a.nsp);
+  if (!a.block_sums) hipLaunchKernelGGL(k_block_sums, scan, dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_scan, scan, dim3(kBlock), 0, s, a);
+  const dim3 grid(8u * (unsigned)a.t.per_xcd + 1u, (unsigned)a.nsp);
   if (a.rank_cells) {
     // one thread per cell of a tile, at most a full block
     const int cells = a.t.tx * a.t.tz;
@@ -2390,18 +2401,13 @@ hipError_t launch_batch_cycle(const BatchArgs &b, const BatchLaunch &l, hipStrea
   const dim3 blk(kBlock);
   hipLaunchKernelGGL(kb_solve_e, dim3(8u * (unsigned)std::max(1, (l.items_nodes + 7) / 8)), blk, 0,
                      s, b, l.items_nodes);
-  hipLaunchKernelGGL(kb_update_h, dim3(8u * (unsigned)std::max(1, (l.items_cells + 7) / 8)), blk, 0,
+  hipLaunchKernelGGL(kb_update_h, dim3(8u * (unsigned)std::max(1, (l.items_cells + 7) / 8) + 1u), blk, 0,
                      s, b, l.items_cells);
-  hipLaunchKernelGGL(kb_prefix, dim3(1), dim3(1024), 0, s, b);
   const dim3 gp((unsigned)l.grid_particles);
   hipLaunchKernelGGL(batch_particles_kernel(l.mixed, l.ids, l.pw), gp, dim3(64u * (unsigned)l.waves),
                      l.lds_particles, s, b);
-  // the scans' items are fixed between rebuilds: a block per item (the kernels' loops then run
-  // once per block)
-  hipLaunchKernelGGL(kb_scan1, dim3((unsigned)std::max(1, l.items_scan)), blk, 0, s, b);
-  hipLaunchKernelGGL(kb_scan2, dim3((unsigned)std::max(1, l.items_scan + b.nruns)), blk, 0, s, b);
-  hipLaunchKernelGGL(kb_rank, dim3((unsigned)l.grid_rank), blk, l.lds_rank, s, b);
-  hipLaunchKernelGGL(kb_end, dim3((unsigned)((b.nruns + kBlock - 1) / kBlock)), blk, 0, s, b);
+  hipLaunchKernelGGL(kb_scan, dim3((unsigned)std::max(1, l.items_scan)), blk, 0, s, b, l.items_scan);
+  hipLaunchKernelGGL(kb_rank, dim3((unsigned)(b.nruns + l.grid_rank)), blk, l.lds_rank, s, b);
   return hipGetLastError();
 }
 

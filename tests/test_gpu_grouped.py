@@ -62,3 +62,24 @@ def test_direct_form(pic, nx, nz, ppc, te, bc):  # noqa: F811
     check_particles(ctx, orc, wl, ids=False)
     assert ctx.get_info()["overflow_flags"] == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("rank", [0, 1, 2])
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("nx,nz,ppc,tile", [(37, 29, 5, (0, 0)), (41, 60, 39, (0, 0)),
+                                            (41, 60, 40, (0, 0)), (5, 4, 300, (2, 3)),
+                                            (341, 6, 6, (64, 2)), (3, 683, 7, (0, 0))])
+def test_sort(pic, nx, nz, ppc, tile, bc, rank):  # noqa: F811
+    """Cells in two or three scan blocks, the last one ragged; 64 and 16 lanes per cell in the
+    ranker, with more slots per cell than it loads ahead."""
+    wl = picgen.random_small(120 + ppc, nx=nx, nz=nz, ppc=ppc, bc_x=bc, dx=0.5, dz=0.4, dt=0.4,
+                             temps=(200.0, 0.5))
+    print(f"[gpu-case] sort {nx}x{nz} ppc={ppc} bc={bc} rank={rank}", flush=True)
+    ctx, orc = setup_both(pic, wl, fields=picgen.random_fields(ppc, wl.grid), tile=tile)
+    ctx.set_rank_mode(rank)
+    ctx.step(3)
+    orc.step(3)
+    check_moments(ctx, orc)
+    check_particles(ctx, orc, wl)
+    assert ctx.get_info()["overflow_flags"] == 0
+    ctx.close()
