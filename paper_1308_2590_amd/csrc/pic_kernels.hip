@@ -123,12 +123,19 @@ __device__ __forceinline__ float floorT(float a) { return floorf(a); }  // the m
 // Field solve
 // ------------------------------------------------------------------------------------------
 
-__device__ double incident_ey(const LaserArgs &L, double t, double x, double z) {
-  if (L.a0 == 0.0) return 0.0;
-  double tau = t - x;
-  double st = (tau - L.t_center) / L.fwhm_t;
-  double sz = (z - L.z_center) / L.sigma_z;
-  return L.a0 * sin(L.omega * tau) * exp(-0.5 * sz * sz) * exp(-2.0 * 0.6931471805599453 * st * st);
+// The incident E_y at (t, x, z) is source_s(t - x) exp(-sz^2 / 2) source_e(t - x): Step 4 needs it at
+// two times and two columns, the same for every node but for the factor of z.
+__device__ __forceinline__ double source_s(const LaserArgs &L, double tau) { return L.a0 * sin(L.omega * tau); }
+__device__ __forceinline__ double source_e(const LaserArgs &L, double tau) {
+  const double st = (tau - L.t_center) / L.fwhm_t;
+  return exp(-2.0 * 0.6931471805599453 * st * st);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
 // Whether the moment planes of node n can hold a deposit: the flag of its run of kFlagNodes
@@ -225,46 +232,49 @@ __device__ __forceinline__ void write_e(const FieldArgs &a, int64_t n, const dou
   for (int r = 0; r < 3; ++r) a.E_new[r * nn + n] = en[r];
 }
 
-// Mur boundary (Step 3) at the column i = 0 or i = nx of an absorbing axis, from E^n (eo_in)
-// and the new E (ein) of the inner column next to it; the x = 0 column takes the source of
-// Step 4 on E_y.
-__device__ void mur_node(const FieldArgs &a, double tE, int i, int k, const double eo_in[3],
-                         const double ein[3]) {
-  const GridArgs &g = a.g;
-  const int64_t nn = g.nnodes;
-  const double kappa = (g.dt - g.dx) / (g.dt + g.dx);
-  const double t0 = tE, t1 = tE + g.dt;
-  const double z = (double)k * g.dz;
-  const int64_t nb = (int64_t)k * g.nxn + i;
-  double en[3], eo[3];
+// E^n of a boundary column's node and whether a deposit can have reached it.
+struct MurIn {
+  double e[3];
+  bool dep;
+};
+__device__ __forceinline__ void mur_load(const FieldArgs &a, int64_t nb, MurIn &in) {
 #pragma unroll
-  for (int r = 0; r < 3; ++r) eo[r] = a.E[r * nn + nb];
+  for (int r = 0; r < 3; ++r) in.e[r] = a.E[r * a.g.nnodes + nb];
+  in.dep = node_deposited(a, nb);
+}
+
+// Mur boundary (Step 3) at node nb of the column i = 0 or i = nx of an absorbing axis, from E^n
+// (eo_in) and the new E (ein) of the inner column next to it; the x = 0 column takes the source of
+// Step 4 on E_y, inc: the incident E_y at (t, 0), (t + dt, 0), (t, dx), (t + dt, dx).
+__device__ __forceinline__ void mur_node(const FieldArgs &a, bool left, int64_t nb, const MurIn &b,
+                                         const double eo_in[3], const double ein[3],
+                                         const double inc[4]) {
+  const GridArgs &g = a.g;
+  const double kappa = (g.dt - g.dx) / (g.dt + g.dx);
+  double en[3];
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
-    const double Eo_b = eo[r], Eo_in = eo_in[r];
-    if (i == 0) {
-      double i10 = 0.0, i01 = 0.0, i11 = 0.0, i00 = 0.0;
-      if (r == 1) {
-        i10 = incident_ey(a.laser, t1, 0.0, z);
-        i01 = incident_ey(a.laser, t0, g.dx, z);
-        i11 = incident_ey(a.laser, t1, g.dx, z);
-        i00 = incident_ey(a.laser, t0, 0.0, z);
-      }
-      en[r] = i10 + (Eo_in - i01) + kappa * ((ein[r] - i11) - (Eo_b - i00));
-    } else {
-      en[r] = Eo_in + kappa * (ein[r] - Eo_b);
-    }
+    const bool src = left && r == 1;
+    const double i00 = src ? inc[0] : 0.0, i10 = src ? inc[1] : 0.0;
+    const double i01 = src ? inc[2] : 0.0, i11 = src ? inc[3] : 0.0;
+    if (left)
+      en[r] = i10 + (eo_in[r] - i01) + kappa * ((ein[r] - i11) - (b.e[r] - i00));
+    else
+      en[r] = eo_in[r] + kappa * (ein[r] - b.e[r]);
   }
   write_e(a, nb, en);
   // the boundary node takes deposits too; its planes are not used by the solve
-  if (node_deposited(a, nb)) clear_node_moments(a, nb);
+  if (b.dep) clear_node_moments(a, nb);
 }
 
 // Nodes n0, n0 + stride, ... of the E solve (kSolveNodes per thread, their inputs loaded
 // together).  On an absorbing axis the thread of the inner column next to a boundary column
 // also writes that column, so every node's moments are read and cleared by a single thread (an
-// absorbing axis has nx >= 2).
-
+// absorbing axis has nx >= 2).  What the boundary needs is loaded before the first store (a load
+// after stores waits for them), and the source's four times are evaluated by four lanes at once:
+// one lane evaluating them in turn at the end, a sine and two exponentials each, took 5 of the 18
+// us of a small slab's field solve.  They come first, where their registers are free again before
+// the nodes' loads (beside them they cost a wavefront per SIMD).
 __device__ __forceinline__ void solve_e_body(const FieldArgs &a, double tE, int64_t n0,
                                              int64_t stride) {
   const GridArgs &g = a.g;
@@ -275,24 +285,61 @@ __device__ __forceinline__ void solve_e_body(const FieldArgs &a, double tE, int6
 #pragma unroll
   for (int q = 0; q < kSolveNodes; ++q) {
     const int64_t n = n0 + q * stride;
-    const int k = (int)(n / g.nxn), i = (int)(n - (int64_t)k * g.nxn);
-    ii[q] = i;
-    kk[q] = k;
-    live[q] = n < g.nnodes && !(absorbing && (i == 0 || i == g.nx));
-    if (live[q]) node_load(a, i, k, in[q]);
+    kk[q] = (int)(n / g.nxn);
+    ii[q] = (int)(n - (int64_t)kk[q] * g.nxn);
+    live[q] = n < g.nnodes && !(absorbing && (ii[q] == 0 || ii[q] == g.nx));
   }
+  bool left[kSolveNodes], any_left = false;
+#pragma unroll
+  for (int q = 0; q < kSolveNodes; ++q) {
+    left[q] = absorbing && live[q] && ii[q] == 1;
+    any_left = any_left || left[q];
+  }
+  const bool source = a.laser.a0 != 0.0 && __any(any_left);
+  double ss[4] = {0.0, 0.0, 0.0, 0.0}, se[4] = {0.0, 0.0, 0.0, 0.0};
+  if (source) {
+    const int j = threadIdx.x & 3;
+    const double tau = (j & 1 ? tE + g.dt : tE) - (j & 2 ? g.dx : 0.0);
+    const double s = source_s(a.laser, tau), e = source_e(a.laser, tau);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      ss[t] = lane_value(s, t);
+      se[t] = lane_value(e, t);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kSolveNodes; ++q)
+    if (live[q]) node_load(a, ii[q], kk[q], in[q]);
   double en[kSolveNodes][3];
 #pragma unroll
   for (int q = 0; q < kSolveNodes; ++q)
     if (live[q]) node_solve(a, in[q], en[q]);
+  MurIn mur[kSolveNodes];
+  double ez[kSolveNodes];
+#pragma unroll
+  for (int q = 0; q < kSolveNodes; ++q) {
+    ez[q] = 0.0;
+    if (absorbing && live[q] && (left[q] || ii[q] == g.nx - 1)) {
+      mur_load(a, in[q].n + (left[q] ? -1 : 1), mur[q]);
+      if (source && left[q]) {
+        const double sz = ((double)kk[q] * g.dz - a.laser.z_center) / a.laser.sigma_z;
+        ez[q] = exp(-0.5 * sz * sz);
+      }
+    }
+  }
 #pragma unroll
   for (int q = 0; q < kSolveNodes; ++q) {
     if (!live[q]) continue;
     if (in[q].dep) clear_node_moments(a, in[q].n);
     write_e(a, in[q].n, en[q]);
     if (absorbing) {
-      if (ii[q] == 1) mur_node(a, tE, 0, kk[q], in[q].e, en[q]);
-      if (ii[q] == g.nx - 1) mur_node(a, tE, g.nx, kk[q], in[q].e, en[q]);
+      const double inc[4] = {ss[0] * ez[q] * se[0], ss[1] * ez[q] * se[1], ss[2] * ez[q] * se[2],
+                             ss[3] * ez[q] * se[3]};
+      if (left[q]) mur_node(a, true, in[q].n - 1, mur[q], in[q].e, en[q], inc);
+      if (ii[q] == g.nx - 1) {
+        if (left[q]) mur_load(a, in[q].n + 1, mur[q]);  // (two columns of cells: both boundaries)
+        mur_node(a, false, in[q].n + 1, mur[q], in[q].e, en[q], inc);
+      }
     }
   }
 }
