@@ -621,8 +621,8 @@ constexpr int kStageBytes = kStagePlanes * kStagePitch * 8 + 128 * 4 + 64;
 // end slot of every tile row of every species slot.  Two layouts: the grouped form (waves > 0)
 // has accumulators over the tile and its ring and a staging area per wavefront; the direct form
 // (waves = 0) covers the tile's own nodes and cells, particles leaving the tile deposit to the
-// global planes, and the arrivals are summed from the move counters (no arrival array), which
-// brings a 32 x 4 tile of two species to 40 KB: four blocks per CU.  Accumulators and staging
+// global planes, and the arrivals take the place of the staged fields, which brings a 32 x 4 tile
+// of two species to 40 KB: four blocks per CU.  Accumulators and staging
 // are FP64; fields use the kernel's arithmetic type.
 struct TileLds {
   int LW, LH, plane;          // accumulator node grid (tx + 3) x (tz + 3), or (tx + 1) x (tz + 1)
@@ -658,7 +658,13 @@ struct TileLds {
     hn = ho + 3 * (size_t)HPL * tsize;
     cnt = (hn + 3 * (size_t)NPL * tsize + 7) & ~(size_t)7;
     arr = cnt + (size_t)(n_node - 3) * tx * tz * kMoveCodes * sizeof(int);
-    rows = arr + (ring ? (size_t)(n_node - 3) * (tx + 2) * (tz + 2) * sizeof(int) : 0);
+    const size_t arr_bytes = (size_t)(n_node - 3) * (tx + 2) * (tz + 2) * sizeof(int);
+    rows = arr + arr_bytes;
+    // the direct form counts arrivals where E-bar and H^{n+1/2} were, if they fit
+    if (!ring && arr_bytes <= hn - eb) {
+      rows = arr;
+      arr = eb;
+    }
     bytes = rows + (size_t)(n_node - 3) * tz * 2 * sizeof(int);
   }
 };
@@ -969,7 +975,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   T *Ho = reinterpret_cast<T *>(ldsb + Lo.ho);
   T *Hn = reinterpret_cast<T *>(ldsb + Lo.hn);
   int *cntL = reinterpret_cast<int *>(ldsb + Lo.cnt);  // [species][9 codes][cells of the tile]
-  int *arrL = reinterpret_cast<int *>(ldsb + Lo.arr);  // the layout with the ring
+  int *arrL = reinterpret_cast<int *>(ldsb + Lo.arr);  // [species][tile and ring]
   const int LW = Lo.LW, plane = Lo.plane;  // plane: pitch of the node planes, LW * LH nodes
   // node planes, cell-corner planes and (grouped) the staging areas, which follow them
   const int n_zero = Lo.n_node * plane + 12 * Lo.CPL + (DIRECT ? 0 : nwaves * (kStageBytes / 8));
@@ -988,7 +994,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
     for (int s = 0; s < nsl; ++s)
       for (int e = threadIdx.x; e < (kMoveCodes - 1) * ntc; e += blockDim.x)
         cntL[s * ntc * kMoveCodes + e + (e >= 4 * ntc ? ntc : 0)] = 0;
-    if constexpr (!kTileOnly)
+    if constexpr (!DIRECT)
       for (int e = threadIdx.x; e < nsl * AW * AH; e += blockDim.x) arrL[e] = 0;
   }
   const int cw = i1 - i0, chh = k1 - k0;  // the tile's cells inside the grid
@@ -1429,7 +1435,8 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   // until here, so the species need no barriers between them.  With code masks only the nonzero
   // counts are written (most cells send all their particles with one code).  The grouped form's
   // blocks have more threads than cells: one thread per (code, cell) pair (2.4 -> 1.2 us of a
-  // 32 x 2 tile's time against one per cell, which the direct form keeps).
+  // 32 x 2 tile's time against one per cell, which the direct form keeps, the species dealt to the
+  // wavefronts).
   if constexpr (PUSH && !DIRECT) {
     const SmallDiv div_ntc(ntc), div_tx(t.tx);
     for (int s = 0; s < a.nsp; ++s) {
@@ -1456,25 +1463,32 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
       }
     }
   }
-  for (int s = 0; s < a.nsp; ++s) {
-    const SpeciesArgs &sp = a.sp[s];
-    if (!DIRECT || !sp.active) continue;
-    const int *cntS = cntL + s * ntc * kMoveCodes;
-    {
-      const SmallDiv div_cw(cw);
-      for (int e = threadIdx.x; e < chh * cw; e += blockDim.x) {
-        const int lkk = div_cw.q(e), li = e - lkk * cw;
-        const int64_t cg = (int64_t)(k0 + lkk) * g.nx + (i0 + li);
-        const int *cl = cntS + lkk * t.tx + li;
-        uint32_t mask = 0;
+  if constexpr (DIRECT) {
+    for (int e = threadIdx.x; e < a.nsp * AW * AH; e += blockDim.x) arrL[e] = 0;
+    __syncthreads();
+    const int n_part = (ntc + 63) >> 6;
+    const SmallDiv div_part(n_part), div_tx(t.tx);
+    for (int u = wave; u < a.nsp * n_part; u += nwaves) {
+      const int s = __builtin_amdgcn_readfirstlane(div_part.q(u));
+      const SpeciesArgs &sp = a.sp[s];
+      if (!sp.active) continue;
+      const int *cntS = cntL + s * ntc * kMoveCodes;
+      int *arrS = arrL + s * AW * AH;
+      const int c = (u - s * n_part) * 64 + lane;
+      const int lkk = div_tx.q(c), li = c - lkk * t.tx;
+      if (c >= ntc || li >= cw || lkk >= chh) continue;
+      const int64_t cg = (int64_t)(k0 + lkk) * g.nx + (i0 + li);
+      uint32_t mask = 0;
 #pragma unroll
-        for (int d = 0; d < kMoveCodes; ++d) {
-          const int v = cl[d * ntc];
-          if (!a.count_masks || v) sp.cnt[(int64_t)d * nc + cg] = v;
-          if (v) mask |= 1u << d;
+      for (int d = 0; d < kMoveCodes; ++d) {
+        const int v = cntS[d * ntc + c];
+        if (!a.count_masks || v) sp.cnt[(int64_t)d * nc + cg] = v;
+        if (v) {
+          mask |= 1u << d;
+          atomicAdd(&arrS[(lkk + d / 3) * AW + (li + d % 3)], v);
         }
-        if (a.count_masks) sp.cmask[cg] = (uint16_t)mask;
       }
+      if (a.count_masks) sp.cmask[cg] = (uint16_t)mask;
     }
   }
   // Fold the tile's accumulators into the global FP64 moment planes, one node per thread:
@@ -1551,8 +1565,8 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
     // The particles the tile's cells send to each cell of the tile and its ring (the cell
     // (x - dx, z - dz) sends count[code (dx, dz)]), added to the per-cell arrival counts: the
     // sort's scan reads those instead of gathering nine counts per cell, and to the sums per scan
-    // block.  (The layout with the ring sums them in LDS during the count pass.)
-    if constexpr (!kTileOnly) __syncthreads();
+    // block.  (The count pass sums them in LDS.)
+    __syncthreads();
     // 64 cells per wavefront, the species dealt to the wavefronts too: with every thread doing one
     // species after the other most wavefronts stood idle, 1.5 us of the 8 x 4 tiles' time on a foil.
     const int n_part = (AW * AH + 63) >> 6;
@@ -1565,16 +1579,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
       const int *arrS = arrL + s * AW * AH;
       const int e1 = (u - s * n_part) * 64 + lane, e = min(e1, AW * AH - 1);
       const int az = div_aw.q(e), ax = e - az * AW;
-      int v = 0;
-      if constexpr (kTileOnly) {
-#pragma unroll
-        for (int d = 0; d < kMoveCodes; ++d) {
-          const int sx = ax - d % 3, sz = az - d / 3;  // the source cell, tile-local
-          if (sx >= 0 && sx < cw && sz >= 0 && sz < chh) v += cntS[d * ntc + sz * t.tx + sx];
-        }
-      } else {
-        v = arrS[e];
-      }
+      int v = arrS[e];
       if (e1 != e) v = 0;
       int gi = i0 - 1 + ax;
       const int gk = wrap1(k0 - 1 + az, g.nz);
