@@ -1889,7 +1889,7 @@ __device__ __forceinline__ void rank_cells_body(const StepArgs &a, int tile, int
       }
     }
     if (ck == g.nz - 1 || (periodic_x && ci == g.nx - 1)) {
-#pragma unroll
+#pragma unroll 1
       for (int d2 = 0; d2 < 4; ++d2) {
         int si = ci - (d2 % 3 - 1), sk = ck - (d2 / 3 - 1);
         bool in = true;
@@ -1904,7 +1904,10 @@ __device__ __forceinline__ void rank_cells_body(const StepArgs &a, int tile, int
         if (in && sc < c) stay += source_count(sc, d2);
       }
     }
-    // the other codes a cell uses (particles that change cell: few per cycle)
+    // The other codes a cell uses (particles that change cell: few per cycle).  Away from the
+    // grid's border the sources before this one among a destination's are those with the larger
+    // codes: no wrap and no comparison needed (sort of 2048 x 2048 cells 240 -> 227 us).
+    const bool inner = ci >= 2 && ci < g.nx - 2 && ck >= 2 && ck < g.nz - 2;
 #pragma unroll
     for (int d = 0; d < kMoveCodes; ++d) {
       if (d == 4) {
@@ -1912,6 +1915,15 @@ __device__ __forceinline__ void rank_cells_body(const StepArgs &a, int tile, int
         continue;
       }
       if (cur[d] <= 0) continue;
+      if (inner) {
+        const int dc = c + (d / 3 - 1) * g.nx + (d % 3 - 1);
+        int b = sp.cs_new[dc];
+#pragma unroll
+        for (int d2 = d + 1; d2 < kMoveCodes; ++d2)
+          b += source_count(dc - (d2 / 3 - 1) * g.nx - (d2 % 3 - 1), d2);
+        cur[d] = b;
+        continue;
+      }
       // destination (inside the grid: an absorbed particle has its own code)
       int di = ci + (d % 3 - 1), dk = ck + (d / 3 - 1);
       if (di < 0) di += g.nx;
@@ -1920,7 +1932,7 @@ __device__ __forceinline__ void rank_cells_body(const StepArgs &a, int tile, int
       if (dk >= g.nz) dk -= g.nz;
       const int dc = dk * g.nx + di;
       int b = sp.cs_new[dc];
-#pragma unroll
+#pragma unroll 1
       for (int d2 = 0; d2 < kMoveCodes; ++d2) {
         // the source that sends code d2 to the destination
         int si = di - (d2 % 3 - 1), sk = dk - (d2 / 3 - 1);
