@@ -408,6 +408,21 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
       atomicAdd(&sp.arr[dst], 1);
     }
   }
+  // moments that are not finite go alone: in the group's sums they would reach other cells
+  double all = 0.0;
+#pragma unroll
+  for (int q = 0; q < 12; ++q) all += val[2 + q];
+  if (dep && !isfinite(all)) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const double w = ((c & 1) ? val[0] : 1.0 - val[0]) * ((c & 2) ? val[1] : 1.0 - val[1]);
+      const uint32_t n = stay ? node_src[c] : node_dst[c];
+#pragma unroll
+      for (int q = 0; q < kAltVals; ++q)
+        unsafeAtomicAdd(a.M + (int64_t)(q < 12 ? q : 12 + s) * g.nnodes + n, w * val[2 + q]);
+    }
+    dep = false;
+  }
   alt_deposit(st, act, dep, stay, head || (act && (lane & 15) == 0), src, dst, node_src, node_dst, val,
               a.M, g.nnodes, 12 + s, acc, c0, span);
   if (span == 0) return;  // (the same for the whole block)

@@ -65,7 +65,7 @@ __device__ __forceinline__ int wrap_t(int i, int n, bool near) {
   return near ? wrap1(i, n) : wrap_any(i, n);
 }
 
-// Quotient e / d of non-negative integers (e < 2^22, 0 < d < 2^12) from one multiply:
+// Quotient e / d of integers (0 <= e < 2^22, d > 0) from one multiply:
 // (e + 1/2) / d lies at least 1 / (2 d) away from every integer, and the float product is
 // within a relative 2^-23 of it, i.e. within (e + 1/2) / d 2^-23 < 1 / (2 d) absolutely, so
 // truncating it gives the exact quotient.  Grid coordinates (below 2^22 by the grid's limits)
@@ -562,7 +562,7 @@ __device__ __forceinline__ void deposit_one(const AccLds &acc, int o, int rc, T 
   }
 }
 
-// Chunk-of-2 form: a particle whose new cell (gi, gk) lies outside the tile adds its moments to
+// Direct form: a particle whose new cell (gi, gk) lies outside the tile adds its moments to
 // the global moment planes at once, at the cell's 4 corner nodes: the same products as an LDS
 // deposit, with S-hat expanded with that cell's B as the fold expands the per-cell sums.  At
 // a few particles per cell about one in three hundred leaves its tile in a cycle, and the
@@ -855,7 +855,7 @@ struct Stage {
 //
 // The particles that stay in their cell: a pass takes one cell per block of 16 lanes, in their
 // (sorted) order; the other particles' weights are masked to zero (their staged values are
-// finite: only living particles are staged, and the area starts at zero).  At 64 particles per
+// finite: only particles with finite moments are staged, and the area starts at zero).  At 64 particles per
 // cell a group takes one or two passes, at 11 about three.
 //
 // The movers go one by one, four at a time: 16 lanes compute a mover's 28 products (corner i,
@@ -1261,6 +1261,12 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             }
           }
           if constexpr (PW) scale_compact(m, wcur);
+          // A particle whose moments are not finite (a momentum or a B too large to square) goes
+          // alone: in the group's sums it would reach its neighbours' cells, as zero times it.
+          if (alive && !isfinite(m.a0)) {
+            deposit_one(acc, (key & 0xffff) + (key >> 16), key & 0xffff, dfx, dfz, m, wcur, dplane);
+            alive = false;
+          }
           if (alive) {
             st[own] = (double)dfx;
             st[kStagePitch + own] = (double)dfz;
@@ -1642,7 +1648,7 @@ __device__ int block_excl_scan(int v, int *sh, int *total) {
 // register; the others consecutive ranks per code from ballots of the code's bits, their bases
 // counted on in the LDS table.  (The walk along tile rows in groups of 64 slots searched every
 // lane's cell and ranked all codes alike: about 150 instructions per group, 101 us on 21M particles
-// at 128 per cell, 80 now.)
+// at 128 per cell, about 80 now.)
 template <int LPC>
 __device__ __forceinline__ void rank_body(const StepArgs &a, int tile, int species) {
   const GridArgs &g = a.g;
@@ -1803,7 +1809,7 @@ __device__ __forceinline__ void rank_body(const StepArgs &a, int tile, int speci
 // from an earlier cycle), then walks its cell's slots in order.  Move codes are canonical
 // after the wrap (one code per source and destination pair), so on grids one or two cells
 // wide a source listed under two codes has a zero count under the other.  No LDS and no
-// cross-lane work: for few particles per cell the row walk's per-tile staging costs more.
+// cross-lane work: for few particles per cell the per-tile staging of the other ranker costs more.
 // MASKS: the particle kernel wrote each cell's mask of used codes and only the nonzero counts
 // (most cells send every particle with one code), so a cell's own codes come from its mask
 // and a source's count is read only where the source's mask has the code.

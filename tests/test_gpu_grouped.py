@@ -83,3 +83,31 @@ def test_sort(pic, nx, nz, ppc, tile, bc, rank):  # noqa: F811
     check_particles(ctx, orc, wl)
     assert ctx.get_info()["overflow_flags"] == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("what,mover", [("u", 0), ("h", 0), ("h", 1)])
+def test_moments_that_are_not_finite_stay_in_their_cell(pic, what, mover):  # noqa: F811
+    """A particle's momentum, or a cell's H, overflows when squared: the four nodes of that cell
+    carry it and no others.  (With mover options such a momentum's Lorentz factor is infinite and
+    its moments are zero.)"""
+    wl = picgen.random_small(131, nx=11, nz=7, ppc=9, bc_x=0, dx=0.5, dz=0.4, dt=0.4)
+    sp = wl.species[0]
+    n = sp.ux.size // 2
+    i, k = int(sp.xi_x[n]), int(sp.xi_z[n])
+    e, h = picgen.random_fields(131, wl.grid)
+    if what == "u":
+        sp.ux[n] = 1e200
+    else:
+        h[2, k, i] = 1e200
+    print(f"[gpu-case] overflowing {what}, mover {mover}", flush=True)
+    ctx, _ = setup_both(pic, wl, fields=(e, h))
+    if mover:
+        ctx.set_mover(mover)
+    m = ctx.read_moments()
+    bad = ~np.isfinite(m).all(axis=0)
+    own = np.zeros_like(bad)
+    for dk in (0, 1):
+        for di in (0, 1):
+            own[(k + dk) % m.shape[1], (i + di) % m.shape[2]] = True
+    assert (bad == own).all()
+    ctx.close()
