@@ -222,7 +222,7 @@ pic_status pic_profile_read(pic_ctx *ctx, pic_profile *out);
  * deposit (Step 1) and the push of every later cycle use them.  With any option set, the
  * particle stage of a cycle runs in a kernel with one thread per particle that deposits each
  * particle's expanded moments with global atomics, summed first over the particles of a block
- * that share a node (per-particle B makes S-hat differ from particle to particle): about three
+ * that share a node (per-particle B makes S-hat differ from particle to particle): two to three
  * times slower than the default tile kernel.  If particles are loaded, the
  * moments of the current state are deposited again with the new options.  Errors:
  * PIC_ERR_ARG (unknown bits, or a mixed-precision context: the options are FP64 only),
@@ -273,7 +273,7 @@ void pic_destroy(pic_ctx *ctx);
 /* ---- Batches: many independent runs stepped together ----------------------------------------
  *
  * A batch steps its member contexts with one launch of each kernel per cycle for all members
- * together (persistent blocks over the work items of every member), optionally replaying a
+ * together (a block per work item of every member), optionally replaying a
  * captured HIP graph of one cycle.  This is the same cycle as pic_step (Sec. 3.3), so each
  * member's results are those of stepping it alone, up to the order of floating-point atomic
  * additions.  Members keep their own device memory and stay readable (pic_read_*,
@@ -288,7 +288,8 @@ typedef struct pic_batch pic_batch;
 pic_status pic_batch_create(int32_t device, int32_t precision, pic_batch **out);
 
 /* Add a context (PIC_ERR_ARG if it is NULL, already in a batch, on another device, of another
- * precision, or has no particles) / remove it (PIC_ERR_ARG if it is not a member).  Removal
+ * precision, or has no particles) / remove it (PIC_ERR_ARG if it is not a member).  A member
+ * created without a tile shape takes the batch's; removal gives it its own again.  Removal
  * waits for the batch's queued work and returns the context to its own stream. */
 pic_status pic_batch_add(pic_batch *b, pic_ctx *ctx);
 pic_status pic_batch_remove(pic_batch *b, pic_ctx *ctx);

@@ -1,10 +1,10 @@
 """Tile-shape autotuner.
 
-The particle and rank kernels take one block per tile of cells, one wavefront per tile row.
+The particle and rank kernels take one block per tile of cells, four or eight wavefronts each.
 The tile shape sets the particles per block, the LDS per block and the balance between
-blocks; the context's default comes from a rule of thumb (about 1024 particles per tile row
-and species).  The tuner times whole cycles for candidate shapes on a live context
-(pic_set_tiles, then HIP-event timing of a few cycles) and leaves the fastest shape applied.
+blocks; the context's default comes from the library's model of these.  The tuner times whole
+cycles for candidate shapes on a live context (pic_set_tiles, then HIP-event timing of a few
+cycles) and leaves the fastest shape applied.
 Re-tiling does not change results beyond the order of floating-point atomic additions, but the
 timed cycles do advance the context: tune before the cycles that matter, or on a copy.
 """
