@@ -208,7 +208,21 @@ void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
   const int dx = width <= 16 ? 16 : 32;
   c->direct = ld.ppc <= kDirectMaxPerCell &&
               tiles_over(ld.i_lo, ld.i_hi, dx) * tiles_over(ld.k_lo, ld.k_hi, 4) >= kDirectMinTiles;
-  if (c->batch) {
+  // single mixed runs keep the kernel of lane runs (why: pic_runs.hip) and its tiles: 8 cells wide
+  // above 16 per cell, else 32, about 2048 particles per species, two blocks per CU
+  c->runs = mixed(c) && !c->batch && !c->direct;
+  bool pw = false;
+  for (int q = 0; q < c->S; ++q) pw = pw || (c->sp[q].loaded && c->sp[q].pw);
+  if (c->runs) {
+    waves = 4;
+    if (!fixed) {
+      const double w = ld.row_width;
+      tx = w <= 16.0 ? 16 : ld.ppc > 16.0 ? 8 : 32;
+      tz = (int)std::lround(2048.0 / std::max(1.0, std::min((double)tx, w) * ld.ppc));
+      tz = std::min(4, std::max(1, tz));
+      while (tx > 4 && pic::runs_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, pw) > c->lds_max / 2) tx /= 2;
+    }
+  } else if (c->batch) {
     waves = 4;
     if (!fixed) {
       tx = kBatchTileX;
@@ -299,13 +313,14 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   a.dense = c->load.ppc >= kRankDensePerCell ? 1 : 0;
   // the direct form is not instantiated for particle labels, batches and mover options
   a.direct = (c->direct && !c->batch && !c->mover && !c->d.track_ids) ? 1 : 0;
-  a.slot_codes = a.direct ? 0 : 1;
+  a.runs = (c->runs && !c->batch) ? 1 : 0;
+  a.slot_codes = a.direct || a.runs ? 0 : 1;
   a.waves = c->waves;
   // the per-cell ranker reads code masks, which the tile kernel writes (not the per-particle
   // kernel of the mover options, which accumulates full counts)
   a.count_masks = (a.rank_cells && !c->mover) ? 1 : 0;
   a.n_scan_blocks = c->n_scan_blocks;
-  a.block_sums = !c->mover;
+  a.block_sums = !c->mover && !a.runs;
   a.nsp = c->S;
   const int cur = c->cur, nxt = 1 - c->cur;
   for (int s = 0; s < c->S; ++s) {
@@ -460,7 +475,7 @@ pic_status retile(pic_ctx *c) {
       if (csh[cc + 1] > csh[cc]) occ[cc] = 1;
     total += csh[nc];
   }
-  int64_t occupied = 0;
+  int64_t occupied = 0, rows = 0;
   pic::LoadShape ld;
   ld.i_lo = c->g.nx;
   ld.k_lo = c->g.nz;
@@ -470,6 +485,7 @@ pic_status retile(pic_ctx *c) {
     for (int64_t i = 0; i < c->g.nx; ++i) in_row += row[i];
     if (!in_row) continue;
     occupied += in_row;
+    ++rows;
     ld.k_lo = std::min(ld.k_lo, k);
     ld.k_hi = k + 1;
     const int64_t first = static_cast<const uint8_t *>(std::memchr(row, 1, (size_t)c->g.nx)) - row;
@@ -486,9 +502,13 @@ pic_status retile(pic_ctx *c) {
     ld.i_hi = c->g.nx;
     ld.k_hi = c->g.nz;
   }
+  ld.row_width = rows > 0 ? (double)occupied / (double)rows : (double)c->g.nx;
   choose_tiles(c, ld);
   c->rank_cells_auto = occupied >= kRankCellsMinCells && ld.ppc <= kRankCellsMaxPerCell;
-  if (pic::particle_lds_bytes(c->g, c->tiles, mixed(c), c->waves) > c->lds_max)
+  bool pw = false;
+  for (int q = 0; q < c->S; ++q) pw = pw || (c->sp[q].loaded && c->sp[q].pw);
+  if ((c->runs ? pic::runs_lds_bytes(c->g, c->tiles, pw)
+               : pic::particle_lds_bytes(c->g, c->tiles, mixed(c), c->waves)) > c->lds_max)
     return fail(c, PIC_ERR_ARG, "tile too large: its LDS accumulators exceed the LDS of a block");
   return PIC_OK;
 }

@@ -58,6 +58,7 @@ struct LoadShape {
   double ppc = 1.0;
   int64_t i_lo = 0, i_hi = 0;
   int64_t k_lo = 0, k_hi = 0;
+  double row_width = 1.0;  // occupied cells per occupied row
 };
 
 struct ProfEvents {
@@ -95,6 +96,7 @@ struct pic_ctx {
   int32_t rank_mode = PIC_RANK_AUTO;
   bool rank_cells_auto = false;  // the automatic choice, made with the tile shape
   bool direct = false;           // the particle kernel's direct form (about 2 particles per lane and row)
+  bool runs = false;             // the mixed kernel of lane runs (pic_runs.hip)
   int32_t waves = 4;             // wavefronts per block of its grouped form
   int32_t n_scan_blocks = 0;     // blocks of the scan of a cycle's sort
   std::string err;

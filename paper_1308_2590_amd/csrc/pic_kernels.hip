@@ -2410,6 +2410,7 @@ static void launch_particles_t(const StepArgs &a, bool ids, bool pw, dim3 grid, 
 }
 
 hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t s) {
+  if (a.runs) return launch_particles_runs(a, push, s);
   bool ids = false, pw = false;
   for (int q = 0; q < a.nsp; ++q) {
     ids = ids || a.sp[q].dst_id != nullptr;
