@@ -1,6 +1,6 @@
 // The mixed-precision particle kernel of single runs above a few particles per cell: lanes walk
 // runs of a tile row and sum their deposits in FP32 registers.  The grouped kernel (pic_kernels.hip)
-// is faster there (21M particles at 128 per cell: 340 against about 470 us), but adds the same FP32
+// is faster there (21M particles at 128 per cell: 340 against 470 us), but adds the same FP32
 // moments in FP64: the sums then differ by 1e-8, the last bits of E-bar by one rounding here and
 // there, and after 20 cycles of 21M particles some particle next to a cell's face falls on its other
 // side and takes another cell's B: single field values differ by 2e-3 of their scale from earlier
