@@ -197,23 +197,32 @@ constexpr int kSlabTileCells = 32;
 // 391, 32 x 4 346, 16 x 4 306, 8 x 2 368; ten runs in mixed precision 139, 16 x 2 139, 32 x 2 160).
 constexpr int kBatchTileX = 8, kBatchTileZ = 4;
 
-void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
+// What a context takes for a load, alone or as a member of a batch.
+struct TileChoice {
+  int tx, tz, waves;
+  bool direct, runs;
+};
+
+int64_t tile_count(const pic_ctx *c, const TileChoice &t) {
+  return tiles_over(0, c->g.nx, t.tx) * tiles_over(0, c->g.nz, t.tz);
+}
+
+TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch) {
   const int64_t width = ld.i_hi - ld.i_lo;
   const bool fixed = c->d.tile_x > 0 && c->d.tile_z > 0;
   auto lds = [&](int tx, int tz, int waves) {
     return pic::particle_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, mixed(c), waves);
   };
-  c->load = ld;
   int tx = c->d.tile_x, tz = c->d.tile_z, waves = pic::kMaxWaves;
   const int dx = width <= 16 ? 16 : 32;
-  c->direct = ld.ppc <= kDirectMaxPerCell &&
-              tiles_over(ld.i_lo, ld.i_hi, dx) * tiles_over(ld.k_lo, ld.k_hi, 4) >= kDirectMinTiles;
+  const bool direct = ld.ppc <= kDirectMaxPerCell &&
+                      tiles_over(ld.i_lo, ld.i_hi, dx) * tiles_over(ld.k_lo, ld.k_hi, 4) >= kDirectMinTiles;
   // single mixed runs keep the kernel of lane runs (why: pic_runs.hip) and its tiles: 8 cells wide
   // above 16 per cell, else 32, about 2048 particles per species, two blocks per CU
-  c->runs = mixed(c) && !c->batch && !c->direct;
+  const bool runs = mixed(c) && !in_batch && !direct;
   bool pw = false;
   for (int q = 0; q < c->S; ++q) pw = pw || (c->sp[q].loaded && c->sp[q].pw);
-  if (c->runs) {
+  if (runs) {
     waves = 4;
     if (!fixed) {
       const double w = ld.row_width;
@@ -222,13 +231,13 @@ void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
       tz = std::min(4, std::max(1, tz));
       while (tx > 4 && pic::runs_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, pw) > c->lds_max / 2) tx /= 2;
     }
-  } else if (c->batch) {
+  } else if (in_batch) {
     waves = 4;
     if (!fixed) {
       tx = kBatchTileX;
       tz = kBatchTileZ;
     }
-  } else if (c->direct) {
+  } else if (direct) {
     waves = 4;
     if (!fixed) {
       tx = dx;
@@ -244,6 +253,7 @@ void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
     const double kFixed = 12.0, kGroup = 1.2, kGroupWave = 1.1, kRankTile = 0.007;
     const double cus = 256.0;
     double best = 0.0;
+    int best_x = tx, best_z = tz;
     const bool spreads = 2 * width * (ld.k_hi - ld.k_lo) < c->g.ncells;
     for (const auto &sh : shapes) {
       if (!fixed && spreads && sh[0] * sh[1] < kSlabTileCells) continue;
@@ -265,25 +275,31 @@ void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
         const double t = block * (rounds <= 1.0 ? 1.0 : rounds + 0.35) * (1.0 + 0.0015 * cx * cz) + kRankTile * nt;
         if (best == 0.0 || t < best) {
           best = t;
-          c->tiles.tx = cx;
-          c->tiles.tz = cz;
+          best_x = cx;
+          best_z = cz;
           waves = w;
         }
       }
       if (fixed) break;
     }
-    if (!fixed) {
-      tx = c->tiles.tx;
-      tz = c->tiles.tz;
-    }
+    tx = best_x;
+    tz = best_z;
   }
   // a block's staging must fit beside the tile (the loads' deposit uses the grouped form too)
   while (waves > 1 && lds(tx, tz, waves) > c->lds_max) waves /= 2;
-  c->waves = waves;
-  c->tiles.tx = tx;
-  c->tiles.tz = tz;
-  c->tiles.ntx = (c->g.nx + tx - 1) / tx;
-  c->tiles.ntz = (c->g.nz + tz - 1) / tz;
+  return TileChoice{tx, tz, waves, direct, runs};
+}
+
+void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
+  const TileChoice t = tile_choice(c, ld, c->batch != nullptr);
+  c->load = ld;
+  c->direct = t.direct;
+  c->runs = t.runs;
+  c->waves = t.waves;
+  c->tiles.tx = t.tx;
+  c->tiles.tz = t.tz;
+  c->tiles.ntx = (c->g.nx + t.tx - 1) / t.tx;
+  c->tiles.ntz = (c->g.nz + t.tz - 1) / t.tz;
   c->tiles.ntiles = c->tiles.ntx * c->tiles.ntz;
   c->tiles.per_xcd = (c->tiles.ntiles + 7) / 8;
 }
@@ -380,12 +396,11 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   return a;
 }
 
-// (Re)allocate the active-tile arrays, for the current tile decomposition and for the one the
-// context takes in a batch (so that joining or leaving one allocates nothing).
+// (Re)allocate the active-tile arrays, for the tiles that the context takes for its load alone and
+// as a member of a batch, whichever it is now (so that joining or leaving one allocates nothing).
 pic_status alloc_tiles(pic_ctx *c) {
-  int64_t nt = c->tiles.ntiles;
-  if (c->d.tile_x <= 0)
-    nt = std::max(nt, tiles_over(0, c->g.nx, kBatchTileX) * tiles_over(0, c->g.nz, kBatchTileZ));
+  const int64_t nt = std::max(tile_count(c, tile_choice(c, c->load, false)),
+                              tile_count(c, tile_choice(c, c->load, true)));
   if (nt <= c->tiles_alloc) return PIC_OK;
   for (int b = 0; b < 2; ++b) {
     dfree(c, c->tact[b], (size_t)std::max(c->tiles_alloc, 1));
@@ -540,6 +555,8 @@ namespace pic {
 pic_status batch_retile(pic_ctx *c) {
   const TileArgs before = c->tiles;
   choose_tiles(c, LoadShape(c->load));
+  if (c->tiles.ntiles > c->tiles_alloc)
+    return fail(c, PIC_ERR_STATE, "the tile arrays are too short for the context's tiles");
   if (c->tiles.tx == before.tx && c->tiles.tz == before.tz) return PIC_OK;
   return build_tile_list(c);
 }

@@ -1,0 +1,71 @@
+"""Tile bookkeeping of contexts that join, change and leave a batch, on the CPU.
+
+The library's host files are compiled against stand-ins for the HIP calls (fake_hip.cpp): memory
+has exactly the size asked for, and every launch checks the tile arrays its kernel would write.
+The kernels themselves do not run.
+"""
+from __future__ import annotations
+
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+import picgen
+from paper_1308_2590_amd import binding
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1308_2590_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("fake") / "libfake.so")
+    # (symbolic: the stand-ins, not a HIP runtime that torch has loaded)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-w", "-fPIC", "-shared", "-Wl,-Bsymbolic",
+                           "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+                           "-I", CSRC, "-o", lib, os.path.join(ROOT, "tests", "fake_hip.cpp"),
+                           os.path.join(CSRC, "pic_capi.cpp"), os.path.join(CSRC, "pic_batch.cpp")])
+    saved, binding._lib = binding._lib, None
+    try:
+        yield binding.load_library(lib)
+    finally:
+        binding._lib = saved
+
+
+def load(ctx, wl):
+    for s, sp in enumerate(wl.species):
+        ctx.load_particles(s, sp.q, sp.m, sp.w, sp.xi_x, sp.xi_z, sp.ux, sp.uy, sp.uz)
+
+
+def plasma(nx, nz, ppc):
+    return picgen.random_small(5, nx=nx, nz=nz, ppc=ppc, bc_x=0, dx=0.5, dz=0.4, dt=0.3)
+
+
+@pytest.mark.parametrize("mixed", [0, 1])
+@pytest.mark.parametrize("leave", ["remove", "destroy"])
+@pytest.mark.parametrize("nx,nz,before,after,tiles", [
+    (64, 64, 4, 64, None), (64, 64, 4, 16, None), (192, 96, 1, 128, None), (37, 29, 3, 40, None),
+    (64, 64, 64, 4, None), (64, 64, 16, None, (64, 1)), (64, 64, 16, None, (1, 1))])
+def test_tile_arrays_hold_the_tiles_of_a_member_that_leaves(fake, nx, nz, before, after, tiles, leave, mixed):
+    """A member is reloaded with another number of particles per cell, or given a fixed tile shape
+    and then the automatic one, inside the batch; then it leaves and is stepped alone."""
+    short = fake.fake_short_arrays()
+    wl = plasma(nx, nz, before)
+    ctx = binding.Context(wl.grid, precision=mixed, tile=tiles or (0, 0))
+    load(ctx, wl)
+    batch = binding.Batch(0, mixed)
+    batch.add(ctx)
+    batch.step(1)
+    if after:
+        load(ctx, plasma(nx, nz, after))
+    if tiles:
+        ctx.set_tiles(0, 0)
+    batch.step(2)
+    batch.close() if leave == "destroy" else batch.remove(ctx)
+    ctx.step(2)
+    assert fake.fake_short_arrays() == short
+    ctx.close()
+    if leave == "remove":
+        batch.close()
