@@ -160,6 +160,13 @@ bool finite3(const double *v) { return std::isfinite(v[0]) && std::isfinite(v[1]
 
 bool mixed(const pic_ctx *c) { return c->d.precision == PIC_PREC_MIXED; }
 
+// Whether some loaded species carries per-particle densities (the kernels with them run).
+bool any_pw(const pic_ctx *c) {
+  for (int s = 0; s < c->S; ++s)
+    if (c->sp[s].loaded && c->sp[s].pw) return true;
+  return false;
+}
+
 int64_t tiles_over(int64_t lo, int64_t hi, int64_t t) { return hi > lo ? (hi - 1) / t - lo / t + 1 : 0; }
 
 // The particle kernel's direct form up to this many particles per occupied cell and species, if
@@ -220,8 +227,6 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
   // single mixed runs keep the kernel of lane runs (why: pic_runs.hip) and its tiles: 8 cells wide
   // above 16 per cell, else 32, about 2048 particles per species, two blocks per CU
   const bool runs = mixed(c) && !in_batch && !direct;
-  bool pw = false;
-  for (int q = 0; q < c->S; ++q) pw = pw || (c->sp[q].loaded && c->sp[q].pw);
   if (runs) {
     waves = 4;
     if (!fixed) {
@@ -229,7 +234,7 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
       tx = w <= 16.0 ? 16 : ld.ppc > 16.0 ? 8 : 32;
       tz = (int)std::lround(2048.0 / std::max(1.0, std::min((double)tx, w) * ld.ppc));
       tz = std::min(4, std::max(1, tz));
-      while (tx > 4 && pic::runs_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, pw) > c->lds_max / 2) tx /= 2;
+      while (tx > 4 && pic::runs_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, any_pw(c)) > c->lds_max / 2) tx /= 2;
     }
   } else if (in_batch) {
     waves = 4;
@@ -288,6 +293,12 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
   // a block's staging must fit beside the tile (the loads' deposit uses the grouped form too)
   while (waves > 1 && lds(tx, tz, waves) > c->lds_max) waves /= 2;
   return TileChoice{tx, tz, waves, direct, runs};
+}
+
+// LDS of a block of the particle kernel in the form chosen.
+size_t lds_bytes(const pic_ctx *c, const TileChoice &t) {
+  const pic::TileArgs shape{t.tx, t.tz, 0, 0, 0, 0};
+  return t.runs ? pic::runs_lds_bytes(c->g, shape, any_pw(c)) : pic::particle_lds_bytes(c->g, shape, mixed(c), t.waves);
 }
 
 void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
@@ -520,11 +531,11 @@ pic_status retile(pic_ctx *c) {
   ld.row_width = rows > 0 ? (double)occupied / (double)rows : (double)c->g.nx;
   choose_tiles(c, ld);
   c->rank_cells_auto = occupied >= kRankCellsMinCells && ld.ppc <= kRankCellsMaxPerCell;
-  bool pw = false;
-  for (int q = 0; q < c->S; ++q) pw = pw || (c->sp[q].loaded && c->sp[q].pw);
-  if ((c->runs ? pic::runs_lds_bytes(c->g, c->tiles, pw)
-               : pic::particle_lds_bytes(c->g, c->tiles, mixed(c), c->waves)) > c->lds_max)
-    return fail(c, PIC_ERR_ARG, "tile too large: its LDS accumulators exceed the LDS of a block");
+  // in the form it takes alone and in that of a batch's members: a shape set in a batch has to fit
+  // when the context leaves it
+  for (const bool in_batch : {false, true})
+    if (lds_bytes(c, tile_choice(c, ld, in_batch)) > c->lds_max)
+      return fail(c, PIC_ERR_ARG, "tile too large: its LDS accumulators exceed the LDS of a block");
   return PIC_OK;
 }
 
@@ -750,6 +761,7 @@ pic_status pic_load_particles(pic_ctx *c, int32_t s, double q, double m, int64_t
   }
   SpeciesState &st = c->sp[s];
   free_species(c, st);
+  pic::batch_touch(c);  // (here: the batch's tables name the freed arrays also if the load fails)
   st.q = q;
   st.m = m;
   st.pw = w != nullptr;
@@ -853,7 +865,6 @@ pic_status pic_load_particles(pic_ctx *c, int32_t s, double q, double m, int64_t
     if (rt != PIC_OK) return rt;
   }
   HIP_TRY(c, hipMemsetAsync(c->flags, 0, sizeof(uint32_t), c->stream), "clear flags");
-  pic::batch_touch(c);
   return redeposit(c);
 }
 

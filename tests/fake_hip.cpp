@@ -94,7 +94,11 @@ hipError_t launch_particles_alt(const StepArgs &a, bool push, int, int32_t, hipS
 }
 hipError_t launch_sort(const StepArgs &a, hipStream_t) { tiles_need(a, "sort"); return hipSuccess; }
 hipError_t launch_batch_cycle(const BatchArgs &b, const BatchLaunch &l, hipStream_t) {
-  for (int r = 0; r < 2 * b.nruns; ++r) tiles_need(b.step[r], "batch cycle");
+  for (int r = 0; r < 2 * b.nruns; ++r) {
+    tiles_need(b.step[r], "batch cycle");
+    for (int s = 0; s < b.step[r].nsp; ++s)
+      if (b.step[r].sp[s].active) need(b.step[r].sp[s].cs, (size_t)(b.step[r].g.ncells + 1) * sizeof(int32_t), "cell starts");
+  }
   return l.lds_particles <= 160 * 1024 ? hipSuccess : hipErrorInvalidValue;
 }
 hipError_t launch_field_solve(const FieldArgs &, hipStream_t) { return hipSuccess; }

@@ -69,3 +69,49 @@ def test_tile_arrays_hold_the_tiles_of_a_member_that_leaves(fake, nx, nz, before
     ctx.close()
     if leave == "remove":
         batch.close()
+
+
+def test_member_takes_no_tile_shape_that_it_cannot_keep_alone(fake):
+    """22 x 24 cells fit the LDS (163,840 bytes) in the grouped form (here 160,224 bytes) but not in
+    the form of a mixed run alone (164,992): refused in the batch as it is outside, and the old
+    shape stays."""
+    wl = plasma(64, 64, 16)
+    ctx, other = binding.Context(wl.grid, precision=1), binding.Context(wl.grid, precision=1)
+    load(ctx, wl)
+    load(other, wl)
+    batch = binding.Batch(0, 1)
+    batch.add(ctx)
+    for c in (ctx, other):
+        old = c.get_info()["tile"]
+        with pytest.raises(binding.PicError) as e:
+            c.set_tiles(22, 24)
+        assert e.value.status == 1 and c.get_info()["tile"] == old
+    batch.step(1)
+    batch.remove(ctx)
+    ctx.step(1)
+    for x in (batch, ctx, other):
+        x.close()
+
+
+def test_batch_does_not_step_freed_arrays_after_a_refused_load(fake):
+    """Densities per particle take another KB of LDS, which 20 x 26 cells do not leave: the load
+    fails after the species' old arrays are gone."""
+    wl = plasma(64, 64, 4)
+    ctx, other = binding.Context(wl.grid, precision=1, tile=(20, 26)), binding.Context(wl.grid, precision=1)
+    load(ctx, wl)
+    load(other, wl)
+    batch = binding.Batch(0, 1)
+    batch.add(ctx)
+    batch.add(other)
+    batch.step(1)
+    short = fake.fake_short_arrays()
+    with pytest.raises(binding.PicError) as e:
+        load(ctx, picgen.with_particle_densities(plasma(64, 64, 64), seed=3))
+    assert e.value.status == 1
+    try:
+        batch.step(1)   # (may refuse the member's shape)
+    except binding.PicError:
+        pass
+    assert fake.fake_short_arrays() == short
+    for x in (batch, ctx, other):
+        x.close()
