@@ -1123,7 +1123,8 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
       const Stage stage(ldsb + Lo.stage + wave * kStageBytes);
       double *const st = stage.v;
       const int own = lane + (lane >> 4);  // this lane's particle in a staging plane
-      if constexpr (!PW) st[5 * kStagePitch + own] = (double)K.w;
+      // (a density beyond 32 bits goes with its particles, alone)
+      if constexpr (!PW) st[5 * kStagePitch + own] = MIXED && !isfinite(K.w) ? 0.0 : (double)K.w;
       // The tile's groups, row by row, are dealt to the wavefronts (a power of two) in turn, on
       // from where the last species ended: group gr of row r holds slots jg .. jg + ngr - 1
       // (ngr = 0: no group left).
@@ -1261,9 +1262,11 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             }
           }
           if constexpr (PW) scale_compact(m, wcur);
-          // A particle whose moments are not finite (a momentum or a B too large to square) goes
-          // alone: in the group's sums it would reach its neighbours' cells, as zero times it.
-          if (alive && !isfinite(m.a0)) {
+          // A particle with a moment that is not finite (a momentum or a B too large to square, in
+          // 32 bits with a0 = 0 beside it, or a density times a charge) goes alone: in the group's
+          // sums it would reach its neighbours' cells, as zero times it.
+          const T all = m.a0 + m.a1 + m.a2 + m.j0 + m.j1 + m.j2;
+          if (alive && !(isfinite(all) && (!MIXED || isfinite(wcur)))) {
             deposit_one(acc, (key & 0xffff) + (key >> 16), key & 0xffff, dfx, dfz, m, wcur, dplane);
             alive = false;
           }
