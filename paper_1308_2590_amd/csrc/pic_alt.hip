@@ -132,10 +132,12 @@ __device__ void moments13(const SpeciesArgs &sp, double gam, const double u[3], 
 constexpr int kAltPlanes = 15;  // f_x, f_z, the 13 values
 constexpr int kAltPitch = 68;   // particle P at P + P / 16: the 16 lanes of an LDS pass hit 16 banks
 constexpr int kAltWaveBytes = kAltPlanes * kAltPitch * 8 + 2 * 64 * 4 * 4 + 2 * 64 + 2 * 64 * 4;
-// A block's particles lie in consecutive cells; where those are at most kAltCells, the sums go to
-// LDS accumulators per (cell, corner, value) first and from there to the nodes, each value once
+// A block's particles lie in consecutive cells; the sums of the first kAltCells go to LDS
+// accumulators per (cell, corner, value) first and from there to the nodes, each value once
 // per block: the global atomics, executed at the memory side, were half of the kernel's time
-// (16 particles per cell: 96 us with one set per wavefront block and cell, 44 without any).
+// (16 particles per cell: 96 us with one set per wavefront block and cell, 44 without any).  (400 x
+// 400 cells at 10 per cell, where a block fills 26 or 27: 522 us without accumulators for any of
+// them, 327 so; 26 accumulators leave two blocks per CU instead of three, 16 per cell 430 -> 508.)
 constexpr int kAltCells = 24;
 constexpr int kAltVals = 13;
 
@@ -247,12 +249,43 @@ __device__ __forceinline__ void alt_deposit(const AltStage &st, bool act, bool d
   }
 }
 
+// Few particles per cell: a block's 256 particles fill many more cells than the accumulators hold, and
+// the matrix cores take a pass per cell of a few particles.  There the values are summed over each
+// run of lanes with one cell by shuffles towards its first lane, few steps for short runs, which
+// issues one global atomic per value.  All 64 lanes take part; a lane without a value has a key of
+// its own (negative).
+struct Seg {
+  int lane, seg_end, steps;
+  bool head;
+};
+
+__device__ __forceinline__ Seg seg_of(int key) {
+  const int lane = threadIdx.x & 63;
+  const int prev = __shfl_up(key, 1, 64);
+  const bool head = lane == 0 || prev != key;
+  const uint64_t heads = __ballot(head);
+  const uint64_t above = heads & ~((2ull << lane) - 1ull);
+  Seg sg{lane, above ? __ffsll((unsigned long long)above) - 1 : 64, 0, head};
+  while (sg.steps < 6 && __any(lane + (1 << sg.steps) < sg.seg_end)) ++sg.steps;
+  return sg;
+}
+
+__device__ __forceinline__ double seg_sum(const Seg &sg, double v) {
+  for (int q = 0; q < sg.steps; ++q) {
+    const int d = 1 << q;
+    const double t = __shfl_down(v, d, 64);
+    if (sg.lane + d < sg.seg_end) v += t;
+  }
+  return v;
+}
+
 // The same lane's value in the lane before (all 64 lanes active; lane 0 gets its own).
 __device__ __forceinline__ int alt_lane_before(int v) {
   return __builtin_amdgcn_update_dpp(v, v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
 }
 
-template <bool PUSH>
+// SPARSE: the deposit by shuffles (see Seg), without LDS.
+template <bool PUSH, bool SPARSE>
 __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int mover) {
   const GridArgs &g = a.g;
   // the next order's tile flags are set by the sort's scan; every node may hold deposits
@@ -270,11 +303,11 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   const int n = sp.cs[g.ncells];
   if ((int)(blockIdx.x * blockDim.x) >= n) return;  // the whole block past the particles
-  __shared__ __align__(16) char lds[(kBlock / 64) * kAltWaveBytes];
-  __shared__ double acc[kAltCells * 4 * kAltVals];
+  __shared__ __align__(16) char lds[SPARSE ? 16 : (kBlock / 64) * kAltWaveBytes];
+  __shared__ double acc[SPARSE ? 1 : kAltCells * 4 * kAltVals];
   __shared__ int range[2];  // first and last cell of the block
-  const AltStage st(lds + (threadIdx.x >> 6) * kAltWaveBytes);
-  for (int e = threadIdx.x; e < kAltCells * 4 * kAltVals; e += blockDim.x) acc[e] = 0.0;
+  if constexpr (!SPARSE)
+    for (int e = threadIdx.x; e < kAltCells * 4 * kAltVals; e += blockDim.x) acc[e] = 0.0;
   const int lane = threadIdx.x & 63;
   // the particle's old cell (act), whether it deposits (dep) and where: its old cell (stay) or not
   bool act = false, dep = false, stay = false;
@@ -384,12 +417,6 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
       }
     }
   }
-  if (threadIdx.x == 0) range[0] = src;
-  if (threadIdx.x == min((int)blockDim.x, n - (int)(blockIdx.x * blockDim.x)) - 1) range[1] = src;
-  __syncthreads();
-  // the cells of the block, in sorted order (a misplaced particle, flagged above, can be anywhere)
-  const int c0 = range[0];
-  const int span = c0 >= 0 && range[1] >= c0 && range[1] - c0 < kAltCells ? range[1] - c0 + 1 : 0;
   const int before = alt_lane_before(src);  // (all lanes active)
   const bool head = act && (lane == 0 || before != src);
   if (PUSH) {
@@ -408,6 +435,25 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
       atomicAdd(&sp.arr[dst], 1);
     }
   }
+  if constexpr (SPARSE) {
+    const Seg sd = seg_of(dep ? dst : -1 - lane);
+    for (int c = 0; c < 4; ++c) {
+      const double w = ((c & 1) ? val[0] : 1.0 - val[0]) * ((c & 2) ? val[1] : 1.0 - val[1]);
+      const uint32_t node = stay ? node_src[c] : node_dst[c];
+      for (int q = 0; q < kAltVals; ++q) {
+        const double t = seg_sum(sd, w * val[2 + q]);
+        if (dep && sd.head) unsafeAtomicAdd(a.M + (int64_t)(q < 12 ? q : 12 + s) * g.nnodes + node, t);
+      }
+    }
+    return;
+  }
+  if (threadIdx.x == 0) range[0] = src;
+  if (threadIdx.x == min((int)blockDim.x, n - (int)(blockIdx.x * blockDim.x)) - 1) range[1] = src;
+  __syncthreads();
+  // the block's first cells, in sorted order (a misplaced particle, flagged above, can be anywhere)
+  const int c0 = range[0];
+  const int span = c0 >= 0 && range[1] >= c0 ? min(range[1] - c0 + 1, kAltCells) : 0;
+  const AltStage st(lds + (threadIdx.x >> 6) * kAltWaveBytes);
   // moments that are not finite go alone: in the group's sums they would reach other cells
   double all = 0.0;
 #pragma unroll
@@ -605,10 +651,14 @@ hipError_t launch_particles_alt(const StepArgs &a, bool push, int mover, int32_t
   const unsigned nb = (unsigned)std::max<int64_t>(
       1, std::max<int64_t>((max_n + kBlock - 1) / kBlock, (a.t.ntiles + kBlock - 1) / kBlock));
   const dim3 grid(nb, (unsigned)a.nsp);
-  if (push)
-    hipLaunchKernelGGL(k_particles_alt<true>, grid, dim3(kBlock), 0, s, a, mover);
+  if (push && a.sparse)
+    hipLaunchKernelGGL((k_particles_alt<true, true>), grid, dim3(kBlock), 0, s, a, mover);
+  else if (push)
+    hipLaunchKernelGGL((k_particles_alt<true, false>), grid, dim3(kBlock), 0, s, a, mover);
+  else if (a.sparse)
+    hipLaunchKernelGGL((k_particles_alt<false, true>), grid, dim3(kBlock), 0, s, a, mover);
   else
-    hipLaunchKernelGGL(k_particles_alt<false>, grid, dim3(kBlock), 0, s, a, mover);
+    hipLaunchKernelGGL((k_particles_alt<false, false>), grid, dim3(kBlock), 0, s, a, mover);
   return hipGetLastError();
 }
 

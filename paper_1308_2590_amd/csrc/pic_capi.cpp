@@ -324,6 +324,14 @@ constexpr double kRankCellsMaxPerCell = 16.0;
 constexpr int64_t kRankCellsMinCells = 100000;
 // The per-tile ranker gives a cell a whole wavefront from this many particles on.
 constexpr double kRankDensePerCell = 40.0;
+// The mover-option kernel sums the deposit by lane shuffles up to this many particles per cell on
+// at least this many occupied cells, otherwise on the matrix cores (pic_alt.hip has why).  Particle
+// kernel, shuffles / matrix cores, two species at 1 keV: 400 x 400 cells at 1 per cell 130 / 388
+// us, at 2 153 / 386, at 4 209 / 286, at 5 248 / 309, at 6 283 / 298, at 8 349 / 288, at 16 671 / 429;
+// 96 x 96 at 2 30 / 39, at 5 36 / 34; 64 x 64 at 2 29 / 28, at 5 33 / 25; 200 x 200 at 100 keV, where
+// the particles changing cell cut the runs short, at 2 80 / 123, at 5 147 / 125.
+constexpr double kAltSparseMaxPerCell = 5.5;
+constexpr int64_t kAltSparseMinCells = 8192;
 
 bool rank_cells(const pic_ctx *c) {
   if (c->rank_mode == PIC_RANK_CELLS) return true;
@@ -338,6 +346,7 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   a.mixed = mixed(c) ? 1 : 0;
   a.rank_cells = rank_cells(c) ? 1 : 0;
   a.dense = c->load.ppc >= kRankDensePerCell ? 1 : 0;
+  a.sparse = c->load.ppc <= kAltSparseMaxPerCell && c->load.cells >= kAltSparseMinCells ? 1 : 0;
   // the direct form is not instantiated for particle labels, batches and mover options
   a.direct = (c->direct && !c->batch && !c->mover && !c->d.track_ids) ? 1 : 0;
   a.runs = (c->runs && !c->batch) ? 1 : 0;
@@ -528,6 +537,7 @@ pic_status retile(pic_ctx *c) {
     ld.i_hi = c->g.nx;
     ld.k_hi = c->g.nz;
   }
+  ld.cells = occupied;
   ld.row_width = rows > 0 ? (double)occupied / (double)rows : (double)c->g.nx;
   choose_tiles(c, ld);
   c->rank_cells_auto = occupied >= kRankCellsMinCells && ld.ppc <= kRankCellsMaxPerCell;

@@ -58,6 +58,7 @@ struct LoadShape {
   double ppc = 1.0;
   int64_t i_lo = 0, i_hi = 0;
   int64_t k_lo = 0, k_hi = 0;
+  int64_t cells = 0;       // occupied
   double row_width = 1.0;  // occupied cells per occupied row
 };
 

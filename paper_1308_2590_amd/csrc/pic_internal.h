@@ -85,6 +85,7 @@ struct StepArgs {
   int32_t mixed;             // 1: mixed-precision particle state and arithmetic
   int32_t rank_cells;        // 1: destinations ranked one thread per cell, 0: per tile
   int32_t dense;             // per tile: 64 lanes per cell (1) or 16 (0)
+  int32_t sparse;            // 1: the mover-option kernel's deposit for few particles per cell
   int32_t direct;            // 1: the particle kernel's direct form (few particles per cell), 0: grouped
   int32_t runs;              // 1: the mixed particle kernel of pic_runs.hip
   int32_t slot_codes;        // 1: the particle kernel writes a byte per slot (see locode)
