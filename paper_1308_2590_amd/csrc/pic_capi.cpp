@@ -224,7 +224,7 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
   const int dx = width <= 16 ? 16 : 32;
   const bool direct = ld.ppc <= kDirectMaxPerCell &&
                       tiles_over(ld.i_lo, ld.i_hi, dx) * tiles_over(ld.k_lo, ld.k_hi, 4) >= kDirectMinTiles;
-  // single mixed runs keep the kernel of lane runs (why: pic_runs.hip) and its tiles: 8 cells wide
+  // single mixed runs keep the kernel of lane runs (why: pic_runs.h) and its tiles: 8 cells wide
   // above 16 per cell, else 32, about 2048 particles per species, two blocks per CU
   const bool runs = mixed(c) && !in_batch && !direct;
   if (runs) {
@@ -356,7 +356,7 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   // kernel of the mover options, which accumulates full counts)
   a.count_masks = (a.rank_cells && !c->mover) ? 1 : 0;
   a.n_scan_blocks = c->n_scan_blocks;
-  a.block_sums = !c->mover && !a.runs;
+  a.block_sums = !c->mover;
   a.nsp = c->S;
   const int cur = c->cur, nxt = 1 - c->cur;
   for (int s = 0; s < c->S; ++s) {

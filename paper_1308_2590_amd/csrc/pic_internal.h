@@ -87,7 +87,7 @@ struct StepArgs {
   int32_t dense;             // per tile: 64 lanes per cell (1) or 16 (0)
   int32_t sparse;            // 1: the mover-option kernel's deposit for few particles per cell
   int32_t direct;            // 1: the particle kernel's direct form (few particles per cell), 0: grouped
-  int32_t runs;              // 1: the mixed particle kernel of pic_runs.hip
+  int32_t runs;              // 1: the mixed particle kernel of lane runs (pic_runs.h)
   int32_t slot_codes;        // 1: the particle kernel writes a byte per slot (see locode)
   int32_t waves;             // wavefronts per block of the grouped form
   int32_t count_masks;       // 1: the particle kernel writes code masks and nonzero counts only
@@ -169,7 +169,6 @@ hipError_t launch_field_solve(const FieldArgs &a, hipStream_t s);
 // launch_particles also clears the next order's tile flags, which the sort's scan sets again;
 // launch_sort is the sort of a cycle (scan with tile flags, then ranks and tile list).
 hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t s);
-hipError_t launch_particles_runs(const StepArgs &a, bool push, hipStream_t s);
 hipError_t launch_sort(const StepArgs &a, hipStream_t s);
 // The particle stage with mover options (PIC_MOVER_* bits), one thread per slot: max_n bounds
 // the particles of every species; the move counts must be zero on entry.
