@@ -200,8 +200,8 @@ constexpr int64_t kDirectMinTiles = 256;
 constexpr int kSlabTileCells = 32;
 
 // A batch's members share the GPU, so small tiles that fill it with one run's blocks only add
-// work: 8 x 4 cells and four wavefronts (32 uneven slab runs 306 us per FP64 cycle, with eight
-// 391, 32 x 4 346, 16 x 4 306, 8 x 2 368; ten runs in mixed precision 139, 16 x 2 139, 32 x 2 160).
+// work: 8 x 4 cells and four wavefronts in 64 bits (32 uneven slab runs 306 us per cycle, with eight
+// 391, 32 x 4 346, 16 x 4 306, 8 x 2 368).
 constexpr int kBatchTileX = 8, kBatchTileZ = 4;
 
 // What a context takes for a load, alone or as a member of a batch.
@@ -222,12 +222,14 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
   };
   int tx = c->d.tile_x, tz = c->d.tile_z, waves = pic::kMaxWaves;
   const int dx = width <= 16 ? 16 : 32;
-  const bool direct = ld.ppc <= kDirectMaxPerCell &&
-                      tiles_over(ld.i_lo, ld.i_hi, dx) * tiles_over(ld.k_lo, ld.k_hi, 4) >= kDirectMinTiles;
-  // single mixed runs keep the kernel of lane runs (why: pic_runs.h) and its tiles: 8 cells wide
-  // above 16 per cell, else 32, about 2048 particles per species, two blocks per CU
-  const bool runs = mixed(c) && !in_batch && !direct;
-  if (runs) {
+  bool direct = ld.ppc <= kDirectMaxPerCell &&
+                tiles_over(ld.i_lo, ld.i_hi, dx) * tiles_over(ld.k_lo, ld.k_hi, 4) >= kDirectMinTiles;
+  bool runs = false;
+  if (mixed(c) && !direct) {
+    // Lane runs (why: pic_runs.h) and their tiles: 8 cells wide above 16 per cell, else 32, about 2048
+    // particles per species, two blocks per CU.  In a batch too: FP32 sums differ with the form and
+    // the tile, and a member's results are those of the run alone.
+    runs = true;
     waves = 4;
     if (!fixed) {
       const double w = ld.row_width;
@@ -236,18 +238,19 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
       tz = std::min(4, std::max(1, tz));
       while (tx > 4 && pic::runs_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, any_pw(c)) > c->lds_max / 2) tx /= 2;
     }
-  } else if (in_batch) {
-    waves = 4;
-    if (!fixed) {
-      tx = kBatchTileX;
-      tz = kBatchTileZ;
-    }
-  } else if (direct) {
+  } else if (direct && (mixed(c) || !in_batch)) {
     waves = 4;
     if (!fixed) {
       tx = dx;
       tz = 4;
       while (tx > 4 && lds(tx, tz, 0) > c->lds_max / 2) tx /= 2;
+    }
+  } else if (in_batch) {
+    direct = false;
+    waves = 4;
+    if (!fixed) {
+      tx = kBatchTileX;
+      tz = kBatchTileZ;
     }
   } else {
     // (of equally cheap shapes the first: square ones have the smaller rings)
@@ -295,10 +298,11 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
   return TileChoice{tx, tz, waves, direct, runs};
 }
 
-// LDS of a block of the particle kernel in the form chosen.
-size_t lds_bytes(const pic_ctx *c, const TileChoice &t) {
-  const pic::TileArgs shape{t.tx, t.tz, 0, 0, 0, 0};
-  return t.runs ? pic::runs_lds_bytes(c->g, shape, any_pw(c)) : pic::particle_lds_bytes(c->g, shape, mixed(c), t.waves);
+// LDS of a block that decides whether a tile shape is accepted: the largest of the context's forms,
+// so that a shape is kept over loads.
+size_t lds_bytes(const pic_ctx *c) {
+  return mixed(c) ? pic::runs_lds_bytes(c->g, c->tiles, any_pw(c))
+                  : pic::particle_lds_bytes(c->g, c->tiles, false, c->waves);
 }
 
 void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
@@ -347,9 +351,9 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   a.rank_cells = rank_cells(c) ? 1 : 0;
   a.dense = c->load.ppc >= kRankDensePerCell ? 1 : 0;
   a.sparse = c->load.ppc <= kAltSparseMaxPerCell && c->load.cells >= kAltSparseMinCells ? 1 : 0;
-  // the direct form is not instantiated for particle labels, batches and mover options
-  a.direct = (c->direct && !c->batch && !c->mover && !c->d.track_ids) ? 1 : 0;
-  a.runs = (c->runs && !c->batch) ? 1 : 0;
+  // the direct form is not instantiated for particle labels in 64 bits and for mover options
+  a.direct = (c->direct && !c->mover && (mixed(c) || !c->d.track_ids)) ? 1 : 0;
+  a.runs = c->runs ? 1 : 0;
   a.slot_codes = a.direct || a.runs ? 0 : 1;
   a.waves = c->waves;
   // the per-cell ranker reads code masks, which the tile kernel writes (not the per-particle
@@ -380,7 +384,8 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
       x.msrc_w = st.mwbuf[cur];
       x.mdst_w = push ? st.mwbuf[nxt] : nullptr;
     } else {
-      // the species' single density, read with stride 0 and never written
+      // the species' single density, read with stride 0 and never written (for the density plane; the
+      // moments have it in their constants)
       x.w_stride = 0;
       x.src_w = c->wconst64 + s;
       x.dst_w = c->wconst64 + s;
@@ -541,11 +546,8 @@ pic_status retile(pic_ctx *c) {
   ld.row_width = rows > 0 ? (double)occupied / (double)rows : (double)c->g.nx;
   choose_tiles(c, ld);
   c->rank_cells_auto = occupied >= kRankCellsMinCells && ld.ppc <= kRankCellsMaxPerCell;
-  // in the form it takes alone and in that of a batch's members: a shape set in a batch has to fit
-  // when the context leaves it
-  for (const bool in_batch : {false, true})
-    if (lds_bytes(c, tile_choice(c, ld, in_batch)) > c->lds_max)
-      return fail(c, PIC_ERR_ARG, "tile too large: its LDS accumulators exceed the LDS of a block");
+  if (lds_bytes(c) > c->lds_max)
+    return fail(c, PIC_ERR_ARG, "tile too large: its LDS accumulators exceed the LDS of a block");
   return PIC_OK;
 }
 

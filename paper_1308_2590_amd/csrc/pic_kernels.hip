@@ -349,12 +349,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t store_rsrc(void *p) {
 __device__ __forceinline__ void store_or_drop(double *p, int i, bool on, double v) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), store_rsrc(p), on ? i * 8 : kStoreDrop, 0, 0);
 }
-__device__ __forceinline__ void store_or_drop(float *p, int i, bool on, float v) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
-}
-__device__ __forceinline__ void store_or_drop(int32_t *p, int i, bool on, int32_t v) {
-  __builtin_amdgcn_raw_buffer_store_b32((uint32_t)v, store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
-}
 __device__ __forceinline__ void store_or_drop(uint8_t *p, int i, bool on, uint8_t v) {
   __builtin_amdgcn_raw_buffer_store_b8(v, store_rsrc(p), on ? i : kStoreDrop, 0, 0);
 }
@@ -621,6 +615,7 @@ template <bool PUSH, bool MIXED, bool IDS, bool PW, bool DIRECT = false>
 __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   using T = typename std::conditional<MIXED, float, double>::type;
   static_assert(PUSH || !DIRECT, "the deposit of a loaded state uses the grouped form");
+  static_assert(!MIXED || DIRECT || !PUSH, "mixed runs push in the direct form or in lane runs");
   const GridArgs &g = a.g;
   const TileArgs &t = a.t;
   const int tzi = tile / t.ntx, txi = tile - tzi * t.ntx;
@@ -756,7 +751,10 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
     const SpeciesArgs &sp = a.sp[s];
     if (!sp.active) continue;
     int *const cntS = cntL + s * ntc * kMoveCodes;  // the species' move counters
-    const SpConst<T> K{(T)sp.beta, (T)(PW ? sp.cS1 : sp.cS), (T)(PW ? sp.kJ1 : sp.kJ), (T)sp.w};
+    // (a species with one density keeps its own constants, also in a kernel with densities per
+    // particle: its moments are then the same bits in both)
+    const bool own_w = PW && sp.w_stride != 0;
+    const SpConst<T> K{(T)sp.beta, (T)(own_w ? sp.cS1 : sp.cS), (T)(own_w ? sp.kJ1 : sp.kJ), (T)sp.w};
     const typename Pstate<MIXED>::Src src(sp);
     // per-particle densities: index p * wstride (stride 0 reads a species' single density)
     const T *wsrc = nullptr;
@@ -900,24 +898,13 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             dfx = o.fx;
             dfz = o.fz;
             next_loads();
-            if constexpr (MIXED) {
-              store_or_drop(sp.mdst_cell, j, ok, o.k2 * g.nx + o.i2);
-              store_or_drop(sp.mdst[0], j, ok, o.xn);
-              store_or_drop(sp.mdst[1], j, ok, o.zn);
-              store_or_drop(sp.mdst[2], j, ok, o.n0);
-              store_or_drop(sp.mdst[3], j, ok, o.n1);
-              store_or_drop(sp.mdst[4], j, ok, o.n2);
-              if constexpr (PW) store_or_drop(wdst, j, ok && wstride != 0, wcur);
-              store_or_drop(reinterpret_cast<uint8_t *>(sp.locode), j, ok, (uint8_t)code);
-            } else {
-              store_or_drop(sp.dst[0], j, ok, o.xn);
-              store_or_drop(sp.dst[1], j, ok, o.zn);
-              store_or_drop(sp.dst[2], j, ok, o.n0);
-              store_or_drop(sp.dst[3], j, ok, o.n1);
-              store_or_drop(sp.dst[4], j, ok, o.n2);
-              if constexpr (PW) store_or_drop(wdst, j, ok && wstride != 0, wcur);
-              store_or_drop(reinterpret_cast<uint8_t *>(sp.locode), j, ok, (uint8_t)code);
-            }
+            store_or_drop(sp.dst[0], j, ok, o.xn);
+            store_or_drop(sp.dst[1], j, ok, o.zn);
+            store_or_drop(sp.dst[2], j, ok, o.n0);
+            store_or_drop(sp.dst[3], j, ok, o.n1);
+            store_or_drop(sp.dst[4], j, ok, o.n2);
+            if constexpr (PW) store_or_drop(wdst, j, ok && wstride != 0, wcur);
+            store_or_drop(reinterpret_cast<uint8_t *>(sp.locode), j, ok, (uint8_t)code);
             // particle ids (tests only)
             if (IDS && ok && sp.dst_id) sp.dst_id[j] = sp.src_id[p];
             if (ok && code != 4u) {
@@ -925,7 +912,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
               if (alive) atomicAdd(&cntS[__mul24((int)code, ntc) + hc], 1);
             }
           }
-          if constexpr (PW) scale_compact(m, wcur);
+          if constexpr (PW) scale_compact(m, own_w ? wcur : T(1));
           // A particle with a moment that is not finite (a momentum or a B too large to square, in
           // 32 bits with a0 = 0 beside it, or a density times a charge) goes alone: in the group's
           // sums it would reach its neighbours' cells, as zero times it.
@@ -1061,7 +1048,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             // the new cell, tile-local (a dead particle stays, unused)
             const int ldx = li + o.di, ldz = lk + o.dk;
             const bool inside = ldx >= 0 && ldx < cw && ldz >= 0 && ldz < chh;
-            if constexpr (PW) scale_compact(m, wp);
+            if constexpr (PW) scale_compact(m, own_w ? wp : T(1));
             if constexpr (MIXED) {
               if (ok) {
                 sp.mdst_cell[loc] = o.k2 * g.nx + o.i2;
@@ -1894,14 +1881,29 @@ __global__ __launch_bounds__(kBlock) void kb_update_h(const BatchArgs b, int tot
 // differ in cost, so the bands load the XCDs unequally.)
 __device__ __forceinline__ int batch_item(int w, int total) { return w < total ? w : -1; }
 
-template <bool MIXED, bool IDS, bool PW>
+template <bool IDS, bool PW>
 __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void kb_particles(const BatchArgs b) {
   const int w = batch_item((int)blockIdx.x, b.pre_tiles[b.nruns]);
   if (w < 0) return;
   const int r = find_run(b.pre_tiles, b.nruns, w);
   const StepArgs &sa = run_step(b, r, b.par);
-  particles_body<true, MIXED, IDS, PW>(sa, sa.tile_list[w - b.pre_tiles[r]]);
+  particles_body<true, false, IDS, PW>(sa, sa.tile_list[w - b.pre_tiles[r]]);
+}
+
+// Mixed members, each in the form that it takes alone.
+template <bool IDS, bool PW>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void kb_particles_mixed(const BatchArgs b) {
+  const int w = batch_item((int)blockIdx.x, b.pre_tiles[b.nruns]);
+  if (w < 0) return;
+  const int r = find_run(b.pre_tiles, b.nruns, w);
+  const StepArgs &sa = run_step(b, r, b.par);
+  const int tile = sa.tile_list[w - b.pre_tiles[r]];
+  if (sa.runs)
+    runs_body<true, IDS, PW>(sa, tile);
+  else
+    particles_body<true, true, IDS, PW, true>(sa, tile);
 }
 
 // The scan of every run's sort, over (run, species, block of cells) items, which are fixed between
@@ -1971,30 +1973,22 @@ hipError_t launch_field_solve(const FieldArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The kernel instantiation for a cycle (push) or a deposit of the current state (no push):
-// precision, particle-id copy (push only) and per-particle densities.
-template <bool PUSH, bool MIXED>
-static void launch_particles_t(const StepArgs &a, bool ids, bool pw, dim3 grid, size_t lds,
-                               hipStream_t s) {
-  const dim3 blk(64u * (unsigned)a.waves);
-  // the pushing kernels without ids in the direct form (few particles per lane)
-  if constexpr (PUSH) {
-    if (a.direct) {
-      if (pw)
-        hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, true, true>), grid, blk, lds, s, a);
-      else
-        hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, false, true>), grid, blk, lds, s, a);
-      return;
-    }
-  }
-  if (PUSH && ids && pw)
-    hipLaunchKernelGGL((k_particles<PUSH, MIXED, PUSH, true>), grid, blk, lds, s, a);
-  else if (PUSH && ids)
-    hipLaunchKernelGGL((k_particles<PUSH, MIXED, PUSH, false>), grid, blk, lds, s, a);
-  else if (pw)
-    hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, true>), grid, blk, lds, s, a);
+// The kernel instantiation of the direct and grouped forms for a cycle (push) or a deposit of the
+// current state: precision, particle-id copy (push only) and per-particle densities.  A mixed run
+// pushes in the direct form or in lane runs.
+template <bool IDS, bool PW>
+static void launch_tiles(const StepArgs &a, bool push, size_t lds, hipStream_t s) {
+  const dim3 grid(8u * (unsigned)a.t.per_xcd), blk(64u * (unsigned)a.waves);
+  if (a.mixed && push)
+    hipLaunchKernelGGL((k_particles<true, true, IDS, PW, true>), grid, blk, lds, s, a);
+  else if (a.mixed)
+    hipLaunchKernelGGL((k_particles<false, true, false, PW>), grid, blk, lds, s, a);
+  else if (!push)
+    hipLaunchKernelGGL((k_particles<false, false, false, PW>), grid, blk, lds, s, a);
+  else if (!IDS && a.direct)
+    hipLaunchKernelGGL((k_particles<true, false, false, PW, true>), grid, blk, lds, s, a);
   else
-    hipLaunchKernelGGL((k_particles<PUSH, MIXED, false, false>), grid, blk, lds, s, a);
+    hipLaunchKernelGGL((k_particles<true, false, IDS, PW>), grid, blk, lds, s, a);
 }
 
 static void launch_runs(const StepArgs &a, bool push, bool ids, bool pw, hipStream_t s) {
@@ -2026,14 +2020,14 @@ hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t s) {
   }
   // the direct form has no staging
   const size_t lds = particle_lds_bytes(a.g, a.t, a.mixed != 0, push && a.direct ? 0 : a.waves);
-  const dim3 grid(8u * (unsigned)a.t.per_xcd);
-  if (a.mixed) {
-    if (push) launch_particles_t<true, true>(a, ids, pw, grid, lds, s);
-    else launch_particles_t<false, true>(a, ids, pw, grid, lds, s);
-  } else {
-    if (push) launch_particles_t<true, false>(a, ids, pw, grid, lds, s);
-    else launch_particles_t<false, false>(a, ids, pw, grid, lds, s);
-  }
+  if (ids && pw)
+    launch_tiles<true, true>(a, push, lds, s);
+  else if (ids)
+    launch_tiles<true, false>(a, push, lds, s);
+  else if (pw)
+    launch_tiles<false, true>(a, push, lds, s);
+  else
+    launch_tiles<false, false>(a, push, lds, s);
   return hipGetLastError();
 }
 
@@ -2069,11 +2063,11 @@ typedef void (*BatchParticlesKernel)(BatchArgs);
 // The batched particle kernel instantiation: precision, particle-id copy, per-particle densities.
 static BatchParticlesKernel batch_particles_kernel(bool mixed, bool ids, bool pw) {
   if (mixed) {
-    if (ids) return pw ? kb_particles<true, true, true> : kb_particles<true, true, false>;
-    return pw ? kb_particles<true, false, true> : kb_particles<true, false, false>;
+    if (ids) return pw ? kb_particles_mixed<true, true> : kb_particles_mixed<true, false>;
+    return pw ? kb_particles_mixed<false, true> : kb_particles_mixed<false, false>;
   }
-  if (ids) return pw ? kb_particles<false, true, true> : kb_particles<false, true, false>;
-  return pw ? kb_particles<false, false, true> : kb_particles<false, false, false>;
+  if (ids) return pw ? kb_particles<true, true> : kb_particles<true, false>;
+  return pw ? kb_particles<false, true> : kb_particles<false, false>;
 }
 
 hipError_t launch_batch_cycle(const BatchArgs &b, const BatchLaunch &l, hipStream_t s) {

@@ -309,7 +309,10 @@ __device__ __forceinline__ void runs_body(const StepArgs &a, int tile) {
     const SpeciesArgs &sp = a.sp[s];
     if (!sp.active) continue;
     int *const cntS = cntL + s * ntc * kMoveCodes;  // the species' move counters
-    const SpConst<float> K{(float)sp.beta, (float)(PW ? sp.cS1 : sp.cS), (float)(PW ? sp.kJ1 : sp.kJ), (float)sp.w};
+    // (a species with one density keeps its own constants, also in a kernel with densities per
+    // particle: its moments are then the same bits in both)
+    const bool own_w = PW && sp.w_stride != 0;
+    const SpConst<float> K{(float)sp.beta, (float)(own_w ? sp.cS1 : sp.cS), (float)(own_w ? sp.kJ1 : sp.kJ), (float)sp.w};
     const Pstate<true>::Src src(sp);
     // per-particle densities: index p * wstride (stride 0 reads a species' single density)
     const float *wsrc = sp.msrc_w;
@@ -419,7 +422,7 @@ __device__ __forceinline__ void runs_body(const StepArgs &a, int tile) {
           if constexpr (!PUSH) {
             const float ginv = rsqT(fmaf(ps.u2, ps.u2, fmaf(ps.u1, ps.u1, fmaf(ps.u0, ps.u0, 1.0f))));
             Compact<float> m0 = compact_moments(K, ginv, ps.u0, ps.u1, ps.u2, fB[0], fB[1], fB[2]);
-            if constexpr (PW) scale_compact(m0, wp);
+            if constexpr (PW) scale_compact(m0, own_w ? wp : float(1));
             if (newcell) {
               if (ca.cell >= 0) ca.flush(acc, lz, dplane);
               ca.clear();
@@ -436,7 +439,7 @@ __device__ __forceinline__ void runs_body(const StepArgs &a, int tile) {
             // of the new cell (read before any LDS atomic of this particle is issued)
             const int hn = (lk + o.dk + 1) * Lo.NW + (li + o.di + 1);
             Compact<float> m = compact_moments(K, o.rg1, o.n0, o.n1, o.n2, Hn[hn], Hn[Lo.NPL + hn], Hn[2 * Lo.NPL + hn]);
-            if constexpr (PW) scale_compact(m, wp);
+            if constexpr (PW) scale_compact(m, own_w ? wp : float(1));
             if (newcell) {
               if (ca.cell >= 0) ca.flush(acc, lz, dplane);
               ca.clear();
