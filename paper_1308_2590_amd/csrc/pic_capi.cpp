@@ -360,7 +360,10 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   // kernel of the mover options, which accumulates full counts)
   a.count_masks = (a.rank_cells && !c->mover) ? 1 : 0;
   a.n_scan_blocks = c->n_scan_blocks;
-  a.block_sums = !c->mover;
+  // lane runs alone leave the block sums to a kernel: their tiles end at one time on some grids, and
+  // the atomics then wait for each other (256 x 256 cells at 16 per cell 100 us a cycle, so 95; 64 x 64
+  // at 32 60, so 63; a batch has no such kernel)
+  a.block_sums = !c->mover && (!c->runs || c->batch);
   a.nsp = c->S;
   const int cur = c->cur, nxt = 1 - c->cur;
   for (int s = 0; s < c->S; ++s) {
