@@ -176,6 +176,10 @@ int64_t tiles_over(int64_t lo, int64_t hi, int64_t t) { return hi > lo ? (hi - 1
 // On 128 x 128 cells (128 tiles) at 4 per cell 29 / 23.
 constexpr double kDirectMaxPerCell = 9.0;
 constexpr int64_t kDirectMinTiles = 256;
+// In mixed precision also up to this many particles per lane and row of the lane runs' tiles, on any
+// grid: a lane's and a wavefront's FP32 sums would hold what the direct form adds one by one in
+// FP64, in the same time (64 x 64 cells at 4 per cell 25 / 25 us).
+constexpr double kDirectMaxPerLane = 2.5;
 
 // Tile shape, wavefronts per block and form of the particle kernel from the load.
 //
@@ -229,7 +233,6 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
     // Lane runs (why: pic_runs.h) and their tiles: 8 cells wide above 16 per cell, else 32, about 2048
     // particles per species, two blocks per CU.  In a batch too: FP32 sums differ with the form and
     // the tile, and a member's results are those of the run alone.
-    runs = true;
     waves = 4;
     if (!fixed) {
       const double w = ld.row_width;
@@ -238,6 +241,9 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
       tz = std::min(4, std::max(1, tz));
       while (tx > 4 && pic::runs_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, any_pw(c)) > c->lds_max / 2) tx /= 2;
     }
+    const double per_lane = std::min((double)tx, ld.row_width) * ld.ppc / (64.0 * (tz >= 4 ? 1 : 4 / tz));
+    direct = per_lane <= kDirectMaxPerLane;
+    runs = !direct;
   } else if (direct && (mixed(c) || !in_batch)) {
     waves = 4;
     if (!fixed) {
