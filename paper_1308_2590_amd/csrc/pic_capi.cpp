@@ -357,8 +357,7 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   a.rank_cells = rank_cells(c) ? 1 : 0;
   a.dense = c->load.ppc >= kRankDensePerCell ? 1 : 0;
   a.sparse = c->load.ppc <= kAltSparseMaxPerCell && c->load.cells >= kAltSparseMinCells ? 1 : 0;
-  // the direct form is not instantiated for particle labels in 64 bits and for mover options
-  a.direct = (c->direct && !c->mover && (mixed(c) || !c->d.track_ids)) ? 1 : 0;
+  a.direct = (c->direct && !c->mover) ? 1 : 0;  // (the mover options have their own kernel)
   a.runs = c->runs ? 1 : 0;
   a.slot_codes = a.direct || a.runs ? 0 : 1;
   a.waves = c->waves;

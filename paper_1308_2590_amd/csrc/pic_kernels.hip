@@ -1985,8 +1985,8 @@ static void launch_tiles(const StepArgs &a, bool push, size_t lds, hipStream_t s
     hipLaunchKernelGGL((k_particles<false, true, false, PW>), grid, blk, lds, s, a);
   else if (!push)
     hipLaunchKernelGGL((k_particles<false, false, false, PW>), grid, blk, lds, s, a);
-  else if (!IDS && a.direct)
-    hipLaunchKernelGGL((k_particles<true, false, false, PW, true>), grid, blk, lds, s, a);
+  else if (a.direct)
+    hipLaunchKernelGGL((k_particles<true, false, IDS, PW, true>), grid, blk, lds, s, a);
   else
     hipLaunchKernelGGL((k_particles<true, false, IDS, PW>), grid, blk, lds, s, a);
 }
