@@ -103,13 +103,14 @@ pic_status rebuild(pic_batch *b) {
   std::vector<int64_t> ctr(n);
   std::vector<int32_t> pre(5 * (n + 1), 0);
   size_t lds_p = 0, lds_r = 0;
-  bool ids = false, pw = false;
+  bool ids = false, pw = false, direct = false;
   // one block size for all members: the smallest of theirs (each fits its own tile in LDS); lane runs
   // always take four wavefronts, which their sums depend on
   int32_t waves = b->precision == PIC_PREC_MIXED ? pic::kBlock / 64 : pic::kMaxWaves;
   for (size_t r = 0; r < n; ++r) {
     pic_ctx *c = b->runs[r];
     if (b->precision != PIC_PREC_MIXED) waves = std::min(waves, c->waves);
+    direct = direct || c->direct;
     ids = ids || c->d.track_ids != 0;
     for (int q = 0; q < c->S; ++q) pw = pw || (c->sp[q].loaded && c->sp[q].pw);
   }
@@ -163,6 +164,7 @@ pic_status rebuild(pic_batch *b) {
   a.pre_rank = b->d_pre + 4 * stride;
   pic::BatchLaunch &l = b->launch;
   l.mixed = b->precision == PIC_PREC_MIXED;
+  l.direct = direct;
   l.ids = ids;
   l.pw = pw;
   l.waves = waves;

@@ -203,10 +203,17 @@ constexpr double kDirectMaxPerLane = 2.5;
 // and 29.  Such a load takes tiles of 32 cells or more.
 constexpr int kSlabTileCells = 32;
 
-// A batch's members share the GPU, so small tiles that fill it with one run's blocks only add
-// work: 8 x 4 cells and four wavefronts in 64 bits (32 uneven slab runs 306 us per cycle, with eight
-// 391, 32 x 4 346, 16 x 4 306, 8 x 2 368).
+// A batch's members share the GPU, so small tiles that fill it with one run's blocks only add work.
+// In 64 bits: 8 x 4 cells and four wavefronts for slabs (32 uneven slab runs 277 us per cycle, with
+// 16 x 4 281, 32 x 4 319, 8 x 2 368; ten 20-cell slabs at 64 per cell 194, with 16 x 4 230), 16 x 4
+// from 64 occupied columns on (eight 80-cell slabs at 50 per cell 291 against 304; six runs of 300 x
+// 300 cells at 12 per cell 580 against 674; twenty of 64 x 64 at 2 per cell 92 against 115, three 49
+// against 49), and 32 x 4 for few particles per cell on wide loads (eight runs of 128 x 128 cells at
+// 2 per cell 119 against 130 with 16 x 4 and 161 with 8 x 4; at 8 per cell 143, 146 and 162).  The
+// direct form as alone (six runs of 300 x 300 cells at 4 per cell 331 us, with 32 x 4 grouped 430).
 constexpr int kBatchTileX = 8, kBatchTileZ = 4;
+constexpr int kBatchWide = 64, kBatchWideSparse = 96;  // occupied columns
+constexpr double kBatchSparseMaxPerCell = 6.5;
 
 // What a context takes for a load, alone or as a member of a batch.
 struct TileChoice {
@@ -244,7 +251,7 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
     const double per_lane = std::min((double)tx, ld.row_width) * ld.ppc / (64.0 * (tz >= 4 ? 1 : 4 / tz));
     direct = per_lane <= kDirectMaxPerLane;
     runs = !direct;
-  } else if (direct && (mixed(c) || !in_batch)) {
+  } else if (direct) {
     waves = 4;
     if (!fixed) {
       tx = dx;
@@ -252,11 +259,12 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
       while (tx > 4 && lds(tx, tz, 0) > c->lds_max / 2) tx /= 2;
     }
   } else if (in_batch) {
-    direct = false;
     waves = 4;
     if (!fixed) {
-      tx = kBatchTileX;
+      const bool sparse = width >= kBatchWideSparse && ld.ppc <= kBatchSparseMaxPerCell;
+      tx = sparse ? 4 * kBatchTileX : width >= kBatchWide ? 2 * kBatchTileX : kBatchTileX;
       tz = kBatchTileZ;
+      while (tx > kBatchTileX && lds(tx, tz, waves) > c->lds_max / 2) tx /= 2;
     }
   } else {
     // (of equally cheap shapes the first: square ones have the smaller rings)

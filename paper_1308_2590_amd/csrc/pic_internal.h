@@ -155,6 +155,7 @@ struct BatchLaunch {
   size_t lds_particles, lds_rank;
   int32_t waves;             // wavefronts per block of the particle kernel
   bool mixed;
+  bool direct;               // some run takes the direct form
   bool ids;                  // some run copies particle ids (the kernel instantiation with ids)
   bool pw;                   // some run carries per-particle densities
 };

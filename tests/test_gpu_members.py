@@ -7,6 +7,7 @@ import pytest
 import picgen
 from tests.test_gpu_batch import TOL64, TOLMIX, compare, rel
 from tests.test_gpu_batch import pic  # noqa: F401  -- fixture
+from tests.test_gpu_parity import check_fields, check_moments, check_particles, setup_both
 
 pytestmark = pytest.mark.gpu
 
@@ -120,3 +121,29 @@ def same(a, b, nsp, labels):
         pa, pb = a.read_particles(s, ids=labels), b.read_particles(s, ids=labels)
         for k in pa:
             assert rel(pa[k], pb[k]) <= TOL64, f"species {s} {k}"
+
+
+@pytest.mark.parametrize("labels", [True, False])
+def test_member_forms_in_64_bits(pic, labels):  # noqa: F811
+    """Members in the direct form and in the grouped one with each of the batch's tile widths, beside
+    each other, against the oracle at 1e-10."""
+    shapes = [(39, 1037, 3, 0), (16, 1026, 9, 1), (130, 33, 2, 0), (130, 33, 7, 1), (96, 21, 6, 0), (95, 21, 6, 1),
+              (64, 9, 17, 0), (63, 9, 30, 0), (5, 4, 65, 1)]
+    print(f"[gpu-case] member forms in 64 bits, labels {labels}", flush=True)
+    batch = pic.Batch(0, 0)
+    runs = []
+    for i, (nx, nz, ppc, bc) in enumerate(shapes):
+        wl = picgen.random_small(60 + i, nx=nx, nz=nz, ppc=ppc, bc_x=bc, dx=0.5, dz=0.4, dt=0.4, temps=(50.0, 0.5))
+        runs.append((wl, *setup_both(pic, wl, fields=picgen.random_fields(i, wl.grid), track_ids=labels)))
+        batch.add(runs[-1][1])
+    batch.step(2)
+    for wl, ctx, orc in runs:
+        orc.step(2)
+        check_fields(ctx, orc)
+        check_moments(ctx, orc)
+        check_particles(ctx, orc, wl, ids=labels)
+        assert ctx.get_info()["overflow_flags"] == 0
+    for _, ctx, _ in runs:
+        batch.remove(ctx)
+        ctx.close()
+    batch.close()
