@@ -1183,9 +1183,11 @@ pic_status pic_energy(pic_ctx *c, double *out, int32_t len) {
   pic::StepArgs a = step_args(c, false);
   hipError_t e = hipMemsetAsync(d, 0, (1 + (size_t)c->S) * sizeof(double), c->stream);
   if (e == hipSuccess) e = pic::launch_energy(a, c->E[c->ecur], c->H[c->hcur], d, c->stream);
-  const hipError_t w = e == hipSuccess ? copy_wait(c, out, d, (1 + (size_t)c->S) * sizeof(double), hipMemcpyDeviceToHost)
-                                       : hipStreamSynchronize(c->stream);  // (before d is freed)
+  // (a wait, then the copy: a copy to pageable memory queued behind the cycles is staged by a slower
+  // path, 1190 us for 19 cycles and the energies of 33,264 cells against 1121)
+  const hipError_t w = hipStreamSynchronize(c->stream);  // (also after an error: before d is freed)
   if (e == hipSuccess) e = w;
+  if (e == hipSuccess) e = copy_wait(c, out, d, (1 + (size_t)c->S) * sizeof(double), hipMemcpyDeviceToHost);
   dfree(c, d, (1 + (size_t)c->S) * sizeof(double));
   if (e != hipSuccess) return hip_fail(c, e, "energy");
   return PIC_OK;
