@@ -232,9 +232,9 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
     return pic::particle_lds_bytes(c->g, pic::TileArgs{tx, tz, 0, 0, 0, 0}, mixed(c), waves);
   };
   int tx = c->d.tile_x, tz = c->d.tile_z, waves = pic::kMaxWaves;
+  auto tiles = [&](int tx, int tz) { return tiles_over(ld.i_lo, ld.i_hi, tx) * tiles_over(ld.k_lo, ld.k_hi, tz); };
   const int dx = width <= 16 ? 16 : 32;
-  bool direct = ld.ppc <= kDirectMaxPerCell &&
-                tiles_over(ld.i_lo, ld.i_hi, dx) * tiles_over(ld.k_lo, ld.k_hi, 4) >= kDirectMinTiles;
+  bool direct = ld.ppc <= kDirectMaxPerCell && tiles(dx, 4) >= kDirectMinTiles;
   bool runs = false;
   if (mixed(c) && !direct) {
     // Lane runs (why: pic_runs.h) and their tiles: 8 cells wide above 16 per cell, else 32, about 2048
@@ -251,6 +251,20 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
     const double per_lane = std::min((double)tx, ld.row_width) * ld.ppc / (64.0 * (tz >= 4 ? 1 : 4 / tz));
     direct = per_lane <= kDirectMaxPerLane;
     runs = !direct;
+    if (direct && !fixed) {
+      // few tiles: smaller ones.  Particle kernel + sort, us: 64 x 64 cells at 4 per cell 32 x 4 27 + 20,
+      // 8 x 4 21 + 13; 300 x 300 at 18 per cell 100 + 26, 162 + 31; 150 x 150 at 18 53 + 24, 55 + 16; a
+      // 3-cell slab of 512 rows at 50 16 x 4 34 + 18, 16 x 2 33 + 14; a 15-cell one at 10 on two
+      // columns of tiles 32 + 16, 36 + 16.
+      if (width <= 16) {
+        tx = 16;
+        tz = tiles(16, 4) <= 128 ? 2 : 4;
+      } else {
+        tx = tiles(32, 4) >= kDirectMinTiles ? 32 : 8;
+        tz = 4;
+      }
+      while (tx > 4 && lds(tx, tz, 0) > c->lds_max / 2) tx /= 2;
+    }
   } else if (direct) {
     waves = 4;
     if (!fixed) {
