@@ -255,8 +255,13 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
       // few tiles: smaller ones.  Particle kernel + sort, us: 64 x 64 cells at 4 per cell 32 x 4 27 + 20,
       // 8 x 4 21 + 13; 300 x 300 at 18 per cell 100 + 26, 162 + 31; 150 x 150 at 18 53 + 24, 55 + 16; a
       // 3-cell slab of 512 rows at 50 16 x 4 34 + 18, 16 x 2 33 + 14; a 15-cell one at 10 on two
-      // columns of tiles 32 + 16, 36 + 16.
-      if (width <= 16) {
+      // columns of tiles 32 + 16, 36 + 16.  In a batch, per cycle: twenty runs of 64 x 64 at 4 per cell
+      // 32 x 4 82, 16 x 4 97, 8 x 4 116; eight 60-cell slabs at 20 182, 215, 246; ten runs with such a
+      // slab among them 147, 142, 142; ten 10-cell slabs at 14 116, 109, 100.
+      if (in_batch) {
+        tx = width <= 16 ? 8 : ld.ppc <= kDirectMaxPerCell ? 32 : 16;
+        tz = 4;
+      } else if (width <= 16) {
         tx = 16;
         tz = tiles(16, 4) <= 128 ? 2 : 4;
       } else {
