@@ -31,7 +31,7 @@ sys.path.insert(0, ROOT)
 
 import picgen  # noqa: E402
 
-KERNEL_SOURCE = os.path.join(ROOT, "paper_1308_2590_amd", "csrc", "pic_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_1308_2590_amd", "csrc")
 PROFILES = os.path.join(ROOT, "profiles")
 
 
@@ -42,21 +42,30 @@ def parse_tile(text):
     return int(text), int(text)
 
 
+def kernel_sources_sha256():
+    """Hash of everything that the device code is made from: every kernel file and header."""
+    import hashlib
+    h = hashlib.sha256()
+    for name in sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".h"))):
+        h.update(name.encode() + b"\0")
+        with open(os.path.join(CSRC, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
 def measured_traffic(workload, precision, tile):
     """HBM bytes per launch of the particle kernel from the committed counter summary of this
-    workload, precision and tile shape, if it was taken on the current kernel source (else
+    workload, precision and tile shape, if it was taken on the current kernel sources (else
     None)."""
-    import hashlib
     path = os.path.join(PROFILES, f"k_particles_{workload}_{precision}_{tile[0]}x{tile[1]}_traffic.md")
     if not os.path.exists(path):
         return None
-    sha = hashlib.sha256(open(KERNEL_SOURCE, "rb").read()).hexdigest()
     vals = {}
     for line in open(path):
         if ":" in line and line.startswith("- "):
             k, v = line[2:].split(":", 1)
             vals[k.strip()] = v.strip().strip("`")
-    if vals.get("kernel_source_sha256") != sha:
+    if vals.get("kernel_sources_sha256") != kernel_sources_sha256():
         return None
     try:
         return float(vals["hbm_bytes_per_launch"])
@@ -442,7 +451,7 @@ def mover_options(binding, torch, steps):
 def batched(binding, torch, nruns, steps, warmup, autotune=False):
     """The batched form in both precisions: `nruns` independent foil runs of uneven size (drawn
     like the serving stream: sides log-uniform in [32, 512], slab 5-15 % of x, density 10-200
-    n_c, 8-64 particles per cell) stepped together by the persistent batch kernels with graph
+    n_c, 8-64 particles per cell) stepped together by the batch kernels with graph
     replay, first all in FP64, then all in mixed precision: aggregate particle-steps/s of each
     (particles alive, averaged over the timed cycles) and the speedup of the mixed batch.  With
     autotune, the tile shape is tuned on the whole batch (every member takes the candidate
