@@ -30,8 +30,9 @@
  *
  * Precision.  PIC_PREC_FP64 holds and pushes particles in FP64.  PIC_PREC_MIXED stores each
  * particle as an int32 cell key (k * nx + i), FP32 offsets within the cell in [0, 1) and FP32
- * momenta; the gather, the push and each particle's moments are computed in FP32, and a
- * lane's FP32 partial sums are added into FP64 accumulators and the FP64 moment planes.  The
+ * momenta; the gather, the push and each particle's moments are computed in FP32, and added one
+ * by one (few particles per cell) or as a lane's FP32 partial sums into FP64 accumulators and
+ * the FP64 moment planes.  The
  * field solve, E, E-bar, H and the moments stay FP64 in both forms.  Loading rounds offsets
  * and momenta to FP32 (an offset that would round to 1 becomes the largest float below 1);
  * positions read back as i + offset, exactly.  An offset carried past a face by the push
@@ -160,7 +161,8 @@ pic_status pic_load_fields(pic_ctx *ctx, const double *e, const double *h);
 
 /* Change the tile shape (cells per particle tile; 0, 0 picks it from the particles per
  * occupied cell).  The tiling only distributes work: results are unchanged up to the order of
- * floating-point atomic additions.  Waits for the stream.  Errors: PIC_ERR_ARG (sizes outside
+ * floating-point atomic additions, in mixed precision up to the order of the FP32 partial sums
+ * too.  Waits for the stream.  Errors: PIC_ERR_ARG (sizes outside
  * 1..64, or the tile's LDS accumulators would exceed the LDS a block may use on the device;
  * the old shape is kept),
  * PIC_ERR_STATE (no particles loaded). */
@@ -222,8 +224,8 @@ pic_status pic_profile_read(pic_ctx *ctx, pic_profile *out);
  * deposit (Step 1) and the push of every later cycle use them.  With any option set, the
  * particle stage of a cycle runs in a kernel with one thread per particle that deposits each
  * particle's expanded moments with global atomics, summed first over the particles of a block
- * that share a node (per-particle B makes S-hat differ from particle to particle): two to three
- * times slower than the default tile kernel.  If particles are loaded, the
+ * that share a node, or over the neighbours in its cell where those are few (per-particle B makes
+ * S-hat differ from particle to particle): two to three times slower than the default tile kernel.  If particles are loaded, the
  * moments of the current state are deposited again with the new options.  Errors:
  * PIC_ERR_ARG (unknown bits, or a mixed-precision context: the options are FP64 only),
  * PIC_ERR_STATE (the context is in a batch). */
@@ -289,7 +291,8 @@ pic_status pic_batch_create(int32_t device, int32_t precision, pic_batch **out);
 
 /* Add a context (PIC_ERR_ARG if it is NULL, already in a batch, on another device, of another
  * precision, or has no particles) / remove it (PIC_ERR_ARG if it is not a member).  A member
- * created without a tile shape takes the batch's; removal gives it its own again.  Removal
+ * created without a tile shape may take another one in the batch, where that changes the order of
+ * FP64 additions only; removal gives it its own again.  Removal
  * waits for the batch's queued work and returns the context to its own stream. */
 pic_status pic_batch_add(pic_batch *b, pic_ctx *ctx);
 pic_status pic_batch_remove(pic_batch *b, pic_ctx *ctx);

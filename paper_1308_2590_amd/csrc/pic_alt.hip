@@ -8,9 +8,10 @@
 //                    code, then the deposit of S-hat, delta-j and density (Step 1, Eq. (3)) at
 //                    the new position with the same options, into the global moment planes with
 //                    FP64 atomics, each value first summed over a block's particles per cell
-//                    (matrix cores, then LDS) and over the cells around a node.  It writes the move codes, counts and arrivals
-//                    the cycle's sort reads, exactly as the tile kernel does.  Without push it
-//                    deposits the current state.
+//                    (matrix cores, then LDS) and over the cells around a node, or, for few
+//                    particles per cell, over a wavefront's runs of one cell (shuffles).  It
+//                    writes the move codes, counts and arrivals the cycle's sort reads, exactly as
+//                    the tile kernel does.  Without push it deposits the current state.
 //   k_energy         field energy (1/2)(sum |E|^2 over nodes + sum |H|^2 over cells) dx dz and
 //                    kinetic energy sum w m (gamma - 1) dx dz per species.
 //
@@ -19,29 +20,21 @@
 // differ from particle to particle, so these kernels deposit each particle's expanded moments
 // instead of per-cell sums; they trade speed for the choice.
 
+#include <algorithm>
 #include <mutex>
 
+#include "pic_device.h"
 #include "pic_internal.h"
 
 namespace pic {
 namespace {
 
-constexpr uint32_t kFlagNonFiniteA = PIC_FLAG_NONFINITE;
-constexpr uint32_t kFlagJumpA = PIC_FLAG_JUMP;
-constexpr uint32_t kFlagOrderA = PIC_FLAG_ORDER;
-
-__device__ __forceinline__ int wrapc(int i, int n) {
-  if (i < 0) return i + n;
-  if (i >= n) return i - n;
-  return i;
-}
-
 // The four corner nodes of cell (i, k) (order (i,k), (i+1,k), (i,k+1), (i+1,k+1)) and the
 // linear weights of offsets (fx, fz).
 __device__ __forceinline__ void corners(const GridArgs &g, int i, int k, double fx, double fz,
                                         int64_t node[4], double W[4]) {
-  const int i1 = g.bc_x == PIC_BC_PERIODIC ? wrapc(i + 1, g.nx) : i + 1;
-  const int k1 = wrapc(k + 1, g.nz);
+  const int i1 = g.bc_x == PIC_BC_PERIODIC ? wrap1(i + 1, g.nx) : i + 1;
+  const int k1 = wrap1(k + 1, g.nz);
   node[0] = (int64_t)k * g.nxn + i;
   node[1] = (int64_t)k * g.nxn + i1;
   node[2] = (int64_t)k1 * g.nxn + i;
@@ -71,8 +64,8 @@ __device__ void b_at(const GridArgs &g, const double *H, int mover, double x, do
   int ci[2], ck[2];
   for (int t = 0; t < 2; ++t) {
     const int ii = ic + t;
-    ci[t] = g.bc_x == PIC_BC_PERIODIC ? wrapc(ii, g.nx) : min(max(ii, 0), g.nx - 1);
-    ck[t] = wrapc(kc + t, g.nz);
+    ci[t] = g.bc_x == PIC_BC_PERIODIC ? wrap1(ii, g.nx) : min(max(ii, 0), g.nx - 1);
+    ck[t] = wrap1(kc + t, g.nz);
   }
   const double Wc[4] = {(1.0 - gx) * (1.0 - gz), gx * (1.0 - gz), (1.0 - gx) * gz, gx * gz};
   const int64_t c4[4] = {(int64_t)ck[0] * g.nx + ci[0], (int64_t)ck[0] * g.nx + ci[1],
@@ -279,11 +272,6 @@ __device__ __forceinline__ double seg_sum(const Seg &sg, double v) {
   return v;
 }
 
-// The same lane's value in the lane before (all 64 lanes active; lane 0 gets its own).
-__device__ __forceinline__ int alt_lane_before(int v) {
-  return __builtin_amdgcn_update_dpp(v, v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
-}
-
 // SPARSE: the deposit by shuffles (see Seg), without LDS.
 template <bool PUSH, bool SPARSE>
 __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int mover) {
@@ -324,7 +312,7 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
     const double wp = sp.w_stride ? sp.src_w[p] : sp.w;
     const int i = (int)floor(x), k = (int)floor(z);
     if (i < 0 || i >= g.nx || k < 0 || k >= g.nz) {
-      atomicOr(a.flags, kFlagOrderA);
+      atomicOr(a.flags, kFlagOrder);
       if (PUSH) reinterpret_cast<uint8_t *>(sp.locode)[j] = kAbsorbed;
     } else {
       int64_t node[4];
@@ -375,7 +363,7 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
         if (zn < 0.0) zn += (double)g.nz;
         if (zn >= (double)g.nz) zn -= (double)g.nz;
         const bool finite = isfinite(g1) && isfinite(xn) && isfinite(zn);
-        if (!finite) atomicOr(a.flags, kFlagNonFiniteA);
+        if (!finite) atomicOr(a.flags, kFlagNonFinite);
         alive = alive && finite;
         const int i2 = finite ? (int)floor(xn) : i, k2 = finite ? (int)floor(zn) : k;
         int di = i2 - i, dk = k2 - k;
@@ -384,7 +372,7 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
         if (dk > 1) dk -= g.nz;
         if (dk < -1) dk += g.nz;
         const bool jump = di < -1 || di > 1 || dk < -1 || dk > 1;
-        if (alive && jump) atomicOr(a.flags, kFlagJumpA);
+        if (alive && jump) atomicOr(a.flags, kFlagJump);
         alive = alive && !jump;
         code = alive ? (uint32_t)((dk + 1) * 3 + (di + 1)) : kAbsorbed;
         // the pushed state goes to location j of the other buffer; the sort reads the codes
@@ -417,7 +405,7 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
       }
     }
   }
-  const int before = alt_lane_before(src);  // (all lanes active)
+  const int before = lane_before(src);  // (all lanes active)
   const bool head = act && (lane == 0 || before != src);
   if (PUSH) {
     // move counts and arrivals: the particles of a run that keep their cell together, the others
@@ -485,12 +473,12 @@ __global__ __launch_bounds__(kBlock) void k_particles_alt(const StepArgs a, int 
     if (joined) left += right;
     if (left != 0.0) {
       const int k = (c0 + l) / g.nx, i = c0 + l - k * g.nx;
-      unsafeAtomicAdd(M + (int64_t)(up ? wrapc(k + 1, g.nz) : k) * g.nxn + i, left);
+      unsafeAtomicAdd(M + (int64_t)(up ? wrap1(k + 1, g.nz) : k) * g.nxn + i, left);
     }
     if (!joined && right != 0.0) {
       const int k = cr / g.nx, i = cr - k * g.nx;
-      const int i1 = g.bc_x == PIC_BC_PERIODIC ? wrapc(i + 1, g.nx) : i + 1;
-      unsafeAtomicAdd(M + (int64_t)(up ? wrapc(k + 1, g.nz) : k) * g.nxn + i1, right);
+      const int i1 = g.bc_x == PIC_BC_PERIODIC ? wrap1(i + 1, g.nx) : i + 1;
+      unsafeAtomicAdd(M + (int64_t)(up ? wrap1(k + 1, g.nz) : k) * g.nxn + i1, right);
     }
   }
 }

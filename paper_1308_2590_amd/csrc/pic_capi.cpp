@@ -170,10 +170,12 @@ bool any_pw(const pic_ctx *c) {
 int64_t tiles_over(int64_t lo, int64_t hi, int64_t t) { return hi > lo ? (hi - 1) / t - lo / t + 1 : 0; }
 
 // The particle kernel's direct form up to this many particles per occupied cell and species, if
-// its tiles fill the GPU.  Particle kernel, 0.1 keV, 700 x 700 cells, direct (32 x 4 cells, four
-// wavefronts) against grouped (32 x 2, eight): 161 / 306 us at 4 per cell, 248 / 358 at 8,
-// 352 / 411 at 12; a 171-cell slab at 1 keV, 11 per cell, three species with densities: 75 / 71.
-// On 128 x 128 cells (128 tiles) at 4 per cell 29 / 23.
+// its tiles fill the GPU.  Particle kernel, direct (32 x 4 cells, four wavefronts) / grouped: 700 x 700
+// cells at 0.1 keV at 4 per cell 161 / 306 us, at 8 248 / 358, at 12 352 / 389; a 171-cell slab at 1
+// keV, 11 per cell, three species with densities, 75 / 71; 128 x 128 cells (128 tiles) at 4 per cell
+// 29 / 23.  The number per cell does not tell the cold full grid, where direct is faster up to 12 or
+// so, from slabs and hot plasmas, where particles leave their tiles: the line is where the first
+// loses little (at 10 per cell 351 / 366) and the others nothing.
 constexpr double kDirectMaxPerCell = 9.0;
 constexpr int64_t kDirectMinTiles = 256;
 // In mixed precision also up to this many particles per lane and row of the lane runs' tiles, on any

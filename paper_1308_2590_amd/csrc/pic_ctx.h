@@ -96,7 +96,7 @@ struct pic_ctx {
   int32_t mover = 0;       // PIC_MOVER_* options; 0: the tile kernel's default mover
   int32_t rank_mode = PIC_RANK_AUTO;
   bool rank_cells_auto = false;  // the automatic choice, made with the tile shape
-  bool direct = false;           // the particle kernel's direct form (about 2 particles per lane and row)
+  bool direct = false;           // the particle kernel's direct form (few particles per cell or lane)
   bool runs = false;             // the mixed kernel of lane runs (pic_runs.h)
   int32_t waves = 4;             // wavefronts per block of its grouped form
   int32_t n_scan_blocks = 0;     // blocks of the scan of a cycle's sort

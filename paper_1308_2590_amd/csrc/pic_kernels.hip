@@ -4,19 +4,20 @@
 //   k_solve_e   Eq. (4) per node: E_new = (I + S)^{-1}[(I - S)E + dt(curl H - dj)] with curl H
 //               from the 2x2 neighbouring cells (Sec. 3.3 Step 5); on an absorbing x axis the
 //               thread of the inner node next to a boundary node also applies the first-order
-//               Mur condition to E - E_inc there (Steps 3, 4, 6); writes E-bar.  Moments are
-//               read, then cleared for the next deposit, only in tiles the deposit reached.
+//               Mur condition to E - E_inc there (Steps 3, 4, 6).  Moments are read, then
+//               cleared for the next deposit, only where the deposit flags say so.
 //   k_update_h  Eq. (5) at cell centres with curl E from the 4 corner nodes (Steps 8-9), and
-//               clears the deposit flags of the tiles.
+//               clears the deposit flags.
 // Particles (one block per tile of cells; a wavefront takes groups of 64 consecutive slots of the
-// tile's rows, or a row of the tile where cells hold few particles):
+// tile's rows, or a row of the tile where cells hold few particles and in mixed precision):
 //   k_particles gather E-bar (bilinear from the 4 corner nodes) and B (the particle's cell),
 //               implicit push (Eq. (2a) solved for the time-centred momentum), position
 //               advance, move code, then deposit of S-hat, delta-j and density (Step 1,
 //               Eq. (3)) at the new position into LDS accumulators covering the tile plus a
 //               halo, folded once per tile into the FP64 moment planes with global atomics.
 //               It also counts the particles leaving each cell per move code and arriving in
-//               each cell.  Instantiated for FP64 and for the mixed form (FP32 particles).
+//               each cell.  FP64: grouped or direct form; mixed form (FP32 particles): direct, or
+//   k_particles_runs  lane runs (pic_runs.h).  The loads' deposit takes the grouped form or lane runs.
 // Sort (stable by cell, removed particles dropped):
 //   k_scan      exclusive scan of the arrival counts -> next cell start offsets, and flags of
 //               the tiles holding particles in the next order;
@@ -604,7 +605,7 @@ __device__ __forceinline__ void deposit_group(const AccLds &acc, const Stage &st
 // locations.  The group's moments are summed per cell by deposit_group, movers like the others,
 // into accumulators that cover the tile and its ring.
 //
-// The direct form (few particles per cell: a lane holds about two particles per row) splits the
+// The direct form (few particles per cell: a lane holds one to five particles per row) splits the
 // row into 64 contiguous runs, one per lane, whose lengths differ by at most one, loads two
 // particles of a lane at a time, adds each particle's moments to LDS at once, keeps accumulators
 // for the tile's own nodes and cells only and sends the moments of a particle that leaves the
@@ -1021,7 +1022,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             // discard the results, so the main path has no branches around it.
             const int li = ok ? i - i0 : 0;
             const int hc = lk * t.tx + li;
-            // The fields are read from LDS for every particle (a lane holds about two per row,
+            // The fields are read from LDS for every particle (a lane holds a few per row,
             // and fields kept across particles would hold about 30 registers).
             T fB[3], fE[12];
 #pragma unroll
@@ -1782,8 +1783,6 @@ __global__ __launch_bounds__(kBlock) void k_rank(const StepArgs a) {
 // found in the exclusive prefix of item counts.
 // ------------------------------------------------------------------------------------------
 
-// The run owning work item w: the largest r with pre[r] <= w (runs without items are skipped
-// because their prefix equals the next run's).
 // The run owning work item w: the last r with pre[r] <= w (pre is the exclusive prefix of the
 // runs' item counts, non-decreasing, pre[0] = 0; a run without items is skipped).  The 64
 // lanes of the wavefront each load one pivot, spaced evenly over the range left, and a ballot
