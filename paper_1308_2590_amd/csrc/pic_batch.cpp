@@ -109,6 +109,7 @@ pic_status rebuild(pic_batch *b) {
   int32_t waves = b->precision == PIC_PREC_MIXED ? pic::kBlock / 64 : pic::kMaxWaves;
   for (size_t r = 0; r < n; ++r) {
     pic_ctx *c = b->runs[r];
+    if ((st = pic::tiles_fit(c)) != PIC_OK) return bfail(b, st, c->err);
     if (b->precision != PIC_PREC_MIXED) waves = std::min(waves, c->waves);
     direct = direct || c->direct;
     ids = ids || c->d.track_ids != 0;

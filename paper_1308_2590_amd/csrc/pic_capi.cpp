@@ -464,18 +464,23 @@ pic_status alloc_tiles(pic_ctx *c) {
   const int64_t nt = std::max(tile_count(c, tile_choice(c, c->load, false)),
                               tile_count(c, tile_choice(c, c->load, true)));
   if (nt <= c->tiles_alloc) return PIC_OK;
-  for (int b = 0; b < 2; ++b) {
-    dfree(c, c->tact[b], (size_t)std::max(c->tiles_alloc, 1));
-    dfree(c, c->tlist[b], ((size_t)c->tiles_alloc + 1) * sizeof(int32_t));
-    c->tact[b] = nullptr;
-    c->tlist[b] = nullptr;
+  // the new arrays first: without memory for them the old ones stay
+  uint8_t *act[2] = {};
+  int32_t *list[2] = {};
+  pic_status st = PIC_OK;
+  for (int b = 0; b < 2 && st == PIC_OK; ++b) {
+    st = dalloc(c, &act[b], (size_t)nt, "alloc tile flags");
+    if (st == PIC_OK) st = dalloc(c, &list[b], (size_t)nt + 1, "alloc tile list");
   }
-  c->tiles_alloc = 0;
-  pic_status st;
   for (int b = 0; b < 2; ++b) {
-    if ((st = dalloc(c, &c->tact[b], (size_t)nt, "alloc tile flags")) != PIC_OK) return st;
-    if ((st = dalloc(c, &c->tlist[b], (size_t)nt + 1, "alloc tile list")) != PIC_OK) return st;
+    if (st == PIC_OK) {
+      std::swap(act[b], c->tact[b]);
+      std::swap(list[b], c->tlist[b]);
+    }
+    dfree(c, act[b], 0);
+    dfree(c, list[b], 0);
   }
+  if (st != PIC_OK) return st;
   c->tiles_alloc = (int32_t)nt;
   return PIC_OK;
 }
@@ -612,11 +617,16 @@ void prof_accumulate(pic_ctx *c) {
 
 namespace pic {
 
+pic_status tiles_fit(pic_ctx *c) {
+  if (c->tiles.ntiles <= c->tiles_alloc) return PIC_OK;
+  return fail(c, PIC_ERR_STATE, "no memory for the context's tiles: load its particles again");
+}
+
 pic_status batch_retile(pic_ctx *c) {
   const TileArgs before = c->tiles;
   choose_tiles(c, LoadShape(c->load));
-  if (c->tiles.ntiles > c->tiles_alloc)
-    return fail(c, PIC_ERR_STATE, "the tile arrays are too short for the context's tiles");
+  const pic_status st = tiles_fit(c);
+  if (st != PIC_OK) return st;
   if (c->tiles.tx == before.tx && c->tiles.tz == before.tz) return PIC_OK;
   return build_tile_list(c);
 }
@@ -945,6 +955,7 @@ pic_status pic_set_tiles(pic_ctx *c, int32_t tile_x, int32_t tile_z) {
   c->d.tile_x = tile_x;
   c->d.tile_z = tile_z;
   pic_status st = retile(c);
+  if (st == PIC_OK) st = alloc_tiles(c);
   if (st != PIC_OK) {
     const std::string msg = c->err;
     c->d.tile_x = ox;
@@ -953,7 +964,6 @@ pic_status pic_set_tiles(pic_ctx *c, int32_t tile_x, int32_t tile_z) {
     c->err = msg;
     return st;
   }
-  if ((st = alloc_tiles(c)) != PIC_OK) return st;
   if ((st = build_tile_list(c)) != PIC_OK) return st;
   pic::batch_touch(c);
   return PIC_OK;
@@ -983,6 +993,8 @@ pic_status pic_step(pic_ctx *c, int32_t nsteps) {
   bool any = false;
   for (int s = 0; s < c->S; ++s) any = any || c->sp[s].loaded;
   if (!any) return fail(c, PIC_ERR_STATE, "no particles loaded");
+  const pic_status fit = pic::tiles_fit(c);
+  if (fit != PIC_OK) return fit;
   for (int32_t it = 0; it < nsteps; ++it) {
     ProfEvents *pe = nullptr;
     if (c->prof_on && (c->prof_count++ % c->prof_every) == 0) {

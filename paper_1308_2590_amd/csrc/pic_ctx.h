@@ -119,6 +119,8 @@ namespace pic {
 // them for a cycle, and the field-solve arguments of the same cycle.
 StepArgs cycle_step_args(pic_ctx *c, int p);
 FieldArgs cycle_field_args(pic_ctx *c, int p);
+// Whether the tile arrays hold the context's tiles (not after a load without memory for them).
+pic_status tiles_fit(pic_ctx *c);
 // Tiles of a context that has joined or left a batch (c->batch), and their list in the current
 // order, queued on the context's stream.
 pic_status batch_retile(pic_ctx *c);

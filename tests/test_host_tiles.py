@@ -115,3 +115,48 @@ def test_batch_does_not_step_freed_arrays_after_a_refused_load(fake):
     assert fake.fake_short_arrays() == short
     for x in (batch, ctx, other):
         x.close()
+
+
+@pytest.fixture
+def short_of_memory(fake):
+    """The library's memory through a hook that returns none while the yielded list is not empty."""
+    refuse = []
+    fake.hipMalloc.argtypes = [C.POINTER(C.c_void_p), C.c_size_t]
+    fake.hipFree.argtypes = [C.c_void_p]
+
+    def alloc(nbytes, device):
+        p = C.c_void_p()
+        return 0 if refuse or fake.hipMalloc(C.byref(p), nbytes) else p.value
+
+    binding.set_allocator(alloc, lambda ptr, nbytes, device: fake.hipFree(ptr))
+    try:
+        yield refuse
+    finally:
+        binding.set_allocator(None, None)
+
+
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("how", ["tiles", "fields"])
+def test_without_memory_for_more_tiles_the_old_ones_stay(fake, short_of_memory, how, batched):
+    wl = plasma(64, 64, 16)
+    ctx = binding.Context(wl.grid, tile=(16, 16))
+    load(ctx, wl)
+    batch = binding.Batch(0, 0)
+    if batched:
+        batch.add(ctx)
+        batch.step(1)
+    short = fake.fake_short_arrays()
+    short_of_memory.append(True)
+    with pytest.raises(binding.PicError) as e:
+        ctx.set_tiles(1, 1)
+    assert e.value.status == 2 and ctx.get_info()["tile"] == (16, 16)
+    if how == "fields":
+        ctx.load_fields(None, None)
+    (batch if batched else ctx).step(2)
+    assert fake.fake_short_arrays() == short
+    del short_of_memory[:]
+    ctx.set_tiles(1, 1)
+    (batch if batched else ctx).step(1)
+    assert fake.fake_short_arrays() == short
+    batch.close()
+    ctx.close()
