@@ -278,7 +278,13 @@ void pic_destroy(pic_ctx *ctx);
  * together (a block per work item of every member), optionally replaying a
  * captured HIP graph of one cycle.  This is the same cycle as pic_step (Sec. 3.3), so each
  * member's results are those of stepping it alone, up to the order of floating-point atomic
- * additions.  Members keep their own device memory and stay readable (pic_read_*,
+ * additions, in 64 bits.  In mixed precision a member's FP32 moments are added in FP64, where
+ * pic_step may add a lane's in FP32 first or round each share of a node to FP32 (see Precision):
+ * the moments of a cycle then differ by about 1e-7 of a plane's largest value, the member's being
+ * the less rounded ones, and a run that joins or leaves a batch changes its rounding at that cycle.
+ * What a run makes of such a difference is its own: over tens of cycles a particle next to a
+ * cell's face can fall on its other side, and values near it then differ by up to 3e-3 of their
+ * array's largest.  Members keep their own device memory and stay readable (pic_read_*,
  * pic_get_info) between batch steps; while in a batch they run on the batch's stream and
  * pic_step / pic_set_stream on them return PIC_ERR_STATE.  Loading particles or fields into a
  * member, or pic_set_step, is allowed and takes effect at the next batch step.  All members
@@ -291,9 +297,8 @@ pic_status pic_batch_create(int32_t device, int32_t precision, pic_batch **out);
 
 /* Add a context (PIC_ERR_ARG if it is NULL, already in a batch, on another device, of another
  * precision, or has no particles) / remove it (PIC_ERR_ARG if it is not a member).  A member
- * created without a tile shape may take another one in the batch, where that changes the order of
- * FP64 additions only; removal gives it its own again.  Removal
- * waits for the batch's queued work and returns the context to its own stream. */
+ * created without a tile shape may take another one in the batch; removal gives it its own again.
+ * Removal waits for the batch's queued work and returns the context to its own stream. */
 pic_status pic_batch_add(pic_batch *b, pic_ctx *ctx);
 pic_status pic_batch_remove(pic_batch *b, pic_ctx *ctx);
 

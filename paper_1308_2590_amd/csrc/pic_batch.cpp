@@ -104,13 +104,12 @@ pic_status rebuild(pic_batch *b) {
   std::vector<int32_t> pre(5 * (n + 1), 0);
   size_t lds_p = 0, lds_r = 0;
   bool ids = false, pw = false, direct = false;
-  // one block size for all members: the smallest of theirs (each fits its own tile in LDS); lane runs
-  // always take four wavefronts, which their sums depend on
-  int32_t waves = b->precision == PIC_PREC_MIXED ? pic::kBlock / 64 : pic::kMaxWaves;
+  // one block size for all members: the smallest of theirs (each fits its own tile in LDS)
+  int32_t waves = pic::kMaxWaves;
   for (size_t r = 0; r < n; ++r) {
     pic_ctx *c = b->runs[r];
     if ((st = pic::tiles_fit(c)) != PIC_OK) return bfail(b, st, c->err);
-    if (b->precision != PIC_PREC_MIXED) waves = std::min(waves, c->waves);
+    waves = std::min(waves, c->waves);
     direct = direct || c->direct;
     ids = ids || c->d.track_ids != 0;
     for (int q = 0; q < c->S; ++q) pw = pw || (c->sp[q].loaded && c->sp[q].pw);
@@ -131,10 +130,8 @@ pic_status rebuild(pic_batch *b) {
         (int32_t)((g.ncells + pic::kHCells * pic::kBlock - 1) / (pic::kHCells * pic::kBlock)),
         c->n_scan_blocks * c->S};
     for (int k = 0; k < 3; ++k) pre[k * (n + 1) + r + 1] = pre[k * (n + 1) + r] + items[k];
-    // (the members' forms: see tile_choice; the kernel's variant follows pw for all of them)
-    lds_p = std::max(lds_p, c->runs ? pic::runs_lds_bytes(c->g, c->tiles, pw)
-                                    : pic::particle_lds_bytes(c->g, c->tiles, b->precision == PIC_PREC_MIXED,
-                                                              c->direct ? 0 : waves));
+    lds_p = std::max(lds_p, pic::particle_lds_bytes(c->g, c->tiles, b->precision == PIC_PREC_MIXED,
+                                                    c->direct ? 0 : waves));
     lds_r = std::max(lds_r, pic::rank_lds_bytes(c->tiles));
   }
   if (n > 0) {

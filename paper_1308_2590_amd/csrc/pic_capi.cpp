@@ -178,9 +178,9 @@ int64_t tiles_over(int64_t lo, int64_t hi, int64_t t) { return hi > lo ? (hi - 1
 // loses little (at 10 per cell 351 / 366) and the others nothing.
 constexpr double kDirectMaxPerCell = 9.0;
 constexpr int64_t kDirectMinTiles = 256;
-// In mixed precision also up to this many particles per lane and row of the lane runs' tiles, on any
-// grid: a lane's and a wavefront's FP32 sums would hold what the direct form adds one by one in
-// FP64, in the same time (64 x 64 cells at 4 per cell 25 / 25 us).
+// In mixed precision single runs also up to this many particles per lane and row of the lane runs'
+// tiles, on any grid: a lane's and a wavefront's FP32 sums would hold what the direct form adds one by
+// one in FP64, in the same time (64 x 64 cells at 4 per cell 25 / 25 us on the same tiles).
 constexpr double kDirectMaxPerLane = 2.5;
 
 // Tile shape, wavefronts per block and form of the particle kernel from the load.
@@ -205,14 +205,17 @@ constexpr double kDirectMaxPerLane = 2.5;
 // and 29.  Such a load takes tiles of 32 cells or more.
 constexpr int kSlabTileCells = 32;
 
-// A batch's members share the GPU, so small tiles that fill it with one run's blocks only add work.
-// In 64 bits: 8 x 4 cells and four wavefronts for slabs (32 uneven slab runs 277 us per cycle, with
+// A batch's members share the GPU, so small tiles that fill it with one run's blocks only add work:
+// 8 x 4 cells and four wavefronts for slabs (32 uneven slab runs 277 us per cycle, with
 // 16 x 4 281, 32 x 4 319, 8 x 2 368; ten 20-cell slabs at 64 per cell 194, with 16 x 4 230), 16 x 4
 // from 64 occupied columns on (eight 80-cell slabs at 50 per cell 291 against 304; six runs of 300 x
 // 300 cells at 12 per cell 580 against 674; twenty of 64 x 64 at 2 per cell 92 against 115, three 49
 // against 49), and 32 x 4 for few particles per cell on wide loads (eight runs of 128 x 128 cells at
 // 2 per cell 119 against 130 with 16 x 4 and 161 with 8 x 4; at 8 per cell 143, 146 and 162).  The
 // direct form as alone (six runs of 300 x 300 cells at 4 per cell 331 us, with 32 x 4 grouped 430).
+// Mixed members that are lane runs alone, or direct for their few particles per lane, take the
+// grouped form too: it adds their FP32 moments in FP64, which holds more bits, and in less time (ten
+// runs 112 us a cycle, each in the form it takes alone 143).
 constexpr int kBatchTileX = 8, kBatchTileZ = 4;
 constexpr int kBatchWide = 64, kBatchWideSparse = 96;  // occupied columns
 constexpr double kBatchSparseMaxPerCell = 6.5;
@@ -238,10 +241,9 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
   const int dx = width <= 16 ? 16 : 32;
   bool direct = ld.ppc <= kDirectMaxPerCell && tiles(dx, 4) >= kDirectMinTiles;
   bool runs = false;
-  if (mixed(c) && !direct) {
+  if (mixed(c) && !direct && !in_batch) {
     // Lane runs (why: pic_runs.h) and their tiles: 8 cells wide above 16 per cell, else 32, about 2048
-    // particles per species, two blocks per CU.  In a batch too: FP32 sums differ with the form and
-    // the tile, and a member's results are those of the run alone.
+    // particles per species, two blocks per CU.
     waves = 4;
     if (!fixed) {
       const double w = ld.row_width;
@@ -257,13 +259,8 @@ TileChoice tile_choice(const pic_ctx *c, const pic::LoadShape &ld, bool in_batch
       // few tiles: smaller ones.  Particle kernel + sort, us: 64 x 64 cells at 4 per cell 32 x 4 27 + 20,
       // 8 x 4 21 + 13; 300 x 300 at 18 per cell 100 + 26, 162 + 31; 150 x 150 at 18 53 + 24, 55 + 16; a
       // 3-cell slab of 512 rows at 50 16 x 4 34 + 18, 16 x 2 33 + 14; a 15-cell one at 10 on two
-      // columns of tiles 32 + 16, 36 + 16.  In a batch, per cycle: twenty runs of 64 x 64 at 4 per cell
-      // 32 x 4 82, 16 x 4 97, 8 x 4 116; eight 60-cell slabs at 20 182, 215, 246; ten runs with such a
-      // slab among them 147, 142, 142; ten 10-cell slabs at 14 116, 109, 100.
-      if (in_batch) {
-        tx = width <= 16 ? 8 : ld.ppc <= kDirectMaxPerCell ? 32 : 16;
-        tz = 4;
-      } else if (width <= 16) {
+      // columns of tiles 32 + 16, 36 + 16.
+      if (width <= 16) {
         tx = 16;
         tz = tiles(16, 4) <= 128 ? 2 : 4;
       } else {
@@ -394,10 +391,10 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   // kernel of the mover options, which accumulates full counts)
   a.count_masks = (a.rank_cells && !c->mover) ? 1 : 0;
   a.n_scan_blocks = c->n_scan_blocks;
-  // lane runs alone leave the block sums to a kernel: their tiles end at one time on some grids, and
-  // the atomics then wait for each other (256 x 256 cells at 16 per cell 100 us a cycle, so 95; 64 x 64
-  // at 32 60, so 63; a batch has no such kernel)
-  a.block_sums = !c->mover && (!c->runs || c->batch);
+  // lane runs leave the block sums to a kernel: their tiles end at one time on some grids, and the
+  // atomics then wait for each other (256 x 256 cells at 16 per cell 100 us a cycle, so 95; 64 x 64
+  // at 32 60, so 63)
+  a.block_sums = !c->mover && !c->runs;
   a.nsp = c->S;
   const int cur = c->cur, nxt = 1 - c->cur;
   for (int s = 0; s < c->S; ++s) {

@@ -16,8 +16,9 @@
 //               Eq. (3)) at the new position into LDS accumulators covering the tile plus a
 //               halo, folded once per tile into the FP64 moment planes with global atomics.
 //               It also counts the particles leaving each cell per move code and arriving in
-//               each cell.  FP64: grouped or direct form; mixed form (FP32 particles): direct, or
-//   k_particles_runs  lane runs (pic_runs.h).  The loads' deposit takes the grouped form or lane runs.
+//               each cell.  Grouped or direct form, FP64 and mixed (FP32 particles); mixed runs alone
+//               take the direct form or
+//   k_particles_runs  lane runs (pic_runs.h).
 // Sort (stable by cell, removed particles dropped):
 //   k_scan      exclusive scan of the arrival counts -> next cell start offsets, and flags of
 //               the tiles holding particles in the next order;
@@ -350,6 +351,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t store_rsrc(void *p) {
 __device__ __forceinline__ void store_or_drop(double *p, int i, bool on, double v) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), store_rsrc(p), on ? i * 8 : kStoreDrop, 0, 0);
 }
+__device__ __forceinline__ void store_or_drop(float *p, int i, bool on, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
+}
+__device__ __forceinline__ void store_or_drop(int32_t *p, int i, bool on, int32_t v) {
+  __builtin_amdgcn_raw_buffer_store_b32((uint32_t)v, store_rsrc(p), on ? i * 4 : kStoreDrop, 0, 0);
+}
 __device__ __forceinline__ void store_or_drop(uint8_t *p, int i, bool on, uint8_t v) {
   __builtin_amdgcn_raw_buffer_store_b8(v, store_rsrc(p), on ? i : kStoreDrop, 0, 0);
 }
@@ -616,7 +623,6 @@ template <bool PUSH, bool MIXED, bool IDS, bool PW, bool DIRECT = false>
 __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   using T = typename std::conditional<MIXED, float, double>::type;
   static_assert(PUSH || !DIRECT, "the deposit of a loaded state uses the grouped form");
-  static_assert(!MIXED || DIRECT || !PUSH, "mixed runs push in the direct form or in lane runs");
   const GridArgs &g = a.g;
   const TileArgs &t = a.t;
   const int tzi = tile / t.ntx, txi = tile - tzi * t.ntx;
@@ -899,11 +905,20 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
             dfx = o.fx;
             dfz = o.fz;
             next_loads();
-            store_or_drop(sp.dst[0], j, ok, o.xn);
-            store_or_drop(sp.dst[1], j, ok, o.zn);
-            store_or_drop(sp.dst[2], j, ok, o.n0);
-            store_or_drop(sp.dst[3], j, ok, o.n1);
-            store_or_drop(sp.dst[4], j, ok, o.n2);
+            if constexpr (MIXED) {
+              store_or_drop(sp.mdst_cell, j, ok, o.k2 * g.nx + o.i2);
+              store_or_drop(sp.mdst[0], j, ok, o.xn);
+              store_or_drop(sp.mdst[1], j, ok, o.zn);
+              store_or_drop(sp.mdst[2], j, ok, o.n0);
+              store_or_drop(sp.mdst[3], j, ok, o.n1);
+              store_or_drop(sp.mdst[4], j, ok, o.n2);
+            } else {
+              store_or_drop(sp.dst[0], j, ok, o.xn);
+              store_or_drop(sp.dst[1], j, ok, o.zn);
+              store_or_drop(sp.dst[2], j, ok, o.n0);
+              store_or_drop(sp.dst[3], j, ok, o.n1);
+              store_or_drop(sp.dst[4], j, ok, o.n2);
+            }
             if constexpr (PW) store_or_drop(wdst, j, ok && wstride != 0, wcur);
             store_or_drop(reinterpret_cast<uint8_t *>(sp.locode), j, ok, (uint8_t)code);
             // particle ids (tests only)
@@ -1882,7 +1897,7 @@ __device__ __forceinline__ int batch_item(int w, int total) { return w < total ?
 
 // DIRECT: some member takes the direct form (a pass of 32 runs without one, 20 cycles: 9675 us, with
 // the branch 9782).
-template <bool IDS, bool PW, bool DIRECT>
+template <bool MIXED, bool IDS, bool PW, bool DIRECT>
 __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void kb_particles(const BatchArgs b) {
   const int w = batch_item((int)blockIdx.x, b.pre_tiles[b.nruns]);
@@ -1891,24 +1906,9 @@ void kb_particles(const BatchArgs b) {
   const StepArgs &sa = run_step(b, r, b.par);
   const int tile = sa.tile_list[w - b.pre_tiles[r]];
   if (DIRECT && sa.direct)
-    particles_body<true, false, IDS, PW, true>(sa, tile);
+    particles_body<true, MIXED, IDS, PW, true>(sa, tile);
   else
-    particles_body<true, false, IDS, PW>(sa, tile);
-}
-
-// Mixed members, each in the form that it takes alone.
-template <bool IDS, bool PW>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 3)))
-void kb_particles_mixed(const BatchArgs b) {
-  const int w = batch_item((int)blockIdx.x, b.pre_tiles[b.nruns]);
-  if (w < 0) return;
-  const int r = find_run(b.pre_tiles, b.nruns, w);
-  const StepArgs &sa = run_step(b, r, b.par);
-  const int tile = sa.tile_list[w - b.pre_tiles[r]];
-  if (sa.runs)
-    runs_body<true, IDS, PW>(sa, tile);
-  else
-    particles_body<true, true, IDS, PW, true>(sa, tile);
+    particles_body<true, MIXED, IDS, PW>(sa, tile);
 }
 
 // The scan of every run's sort, over (run, species, block of cells) items, which are fixed between
@@ -1979,7 +1979,7 @@ hipError_t launch_field_solve(const FieldArgs &a, hipStream_t s) {
 }
 
 // The kernel instantiation of the direct and grouped forms for a cycle (push) or a deposit of the
-// current state: precision, particle-id copy (push only) and per-particle densities.  A mixed run
+// current state: precision, particle-id copy (push only) and per-particle densities.  A mixed run alone
 // pushes in the direct form or in lane runs.
 template <bool IDS, bool PW>
 static void launch_tiles(const StepArgs &a, bool push, size_t lds, hipStream_t s) {
@@ -2065,15 +2065,16 @@ hipError_t launch_tile_list(const StepArgs &a, bool from_next_order, hipStream_t
 
 typedef void (*BatchParticlesKernel)(BatchArgs);
 
-// The batched particle kernel instantiation: particle-id copy, per-particle densities, precision and
-// (64 bits) whether some member takes the direct form.
-template <bool IDS, bool PW>
-static BatchParticlesKernel batch_particles_kernel(bool mixed, bool direct) {
-  return mixed ? kb_particles_mixed<IDS, PW> : direct ? kb_particles<IDS, PW, true> : kb_particles<IDS, PW, false>;
+// The batched particle kernel instantiation: precision, particle-id copy, per-particle densities and
+// whether some member takes the direct form.
+template <bool MIXED, bool IDS, bool PW>
+static BatchParticlesKernel batch_particles_kernel(bool direct) {
+  return direct ? kb_particles<MIXED, IDS, PW, true> : kb_particles<MIXED, IDS, PW, false>;
 }
+template <bool MIXED>
 static BatchParticlesKernel batch_particles_kernel(const BatchLaunch &l) {
-  if (l.ids) return l.pw ? batch_particles_kernel<true, true>(l.mixed, l.direct) : batch_particles_kernel<true, false>(l.mixed, l.direct);
-  return l.pw ? batch_particles_kernel<false, true>(l.mixed, l.direct) : batch_particles_kernel<false, false>(l.mixed, l.direct);
+  if (l.ids) return l.pw ? batch_particles_kernel<MIXED, true, true>(l.direct) : batch_particles_kernel<MIXED, true, false>(l.direct);
+  return l.pw ? batch_particles_kernel<MIXED, false, true>(l.direct) : batch_particles_kernel<MIXED, false, false>(l.direct);
 }
 
 hipError_t launch_batch_cycle(const BatchArgs &b, const BatchLaunch &l, hipStream_t s) {
@@ -2083,7 +2084,7 @@ hipError_t launch_batch_cycle(const BatchArgs &b, const BatchLaunch &l, hipStrea
   hipLaunchKernelGGL(kb_update_h, dim3(8u * (unsigned)std::max(1, (l.items_cells + 7) / 8) + 1u), blk, 0,
                      s, b, l.items_cells);
   const dim3 gp((unsigned)l.grid_particles);
-  hipLaunchKernelGGL(batch_particles_kernel(l), gp, dim3(64u * (unsigned)l.waves),
+  hipLaunchKernelGGL(l.mixed ? batch_particles_kernel<true>(l) : batch_particles_kernel<false>(l), gp, dim3(64u * (unsigned)l.waves),
                      l.lds_particles, s, b);
   hipLaunchKernelGGL(kb_scan, dim3((unsigned)std::max(1, l.items_scan)), blk, 0, s, b, l.items_scan);
   hipLaunchKernelGGL(kb_rank, dim3((unsigned)(b.nruns + l.grid_rank)), blk, l.lds_rank, s, b);

@@ -78,16 +78,16 @@ def test_member_reloaded_then_alone(pic, guarded, nx, nz, before, after, tiles, 
 
 @pytest.mark.parametrize("graph", [False, True])
 @pytest.mark.parametrize("labels", [True, False])
-def test_mixed_member_is_the_run_alone(pic, labels, graph):  # noqa: F811
-    """FP32 sums depend on which particles a lane adds up and in which order: a member's are those of
-    the run alone, so only the order of the FP64 additions differs (TOL64, not the rounding of 32
-    bits).  Lane runs and the direct form beside each other, joining and leaving at other cycles,
-    with densities per particle in some."""
+def test_mixed_member_and_the_run_alone(pic, labels, graph):  # noqa: F811
+    """A mixed member adds its particles' FP32 moments in FP64.  Alone, a run in the direct form by
+    its tiles does the same: only the order of the additions differs (TOL64).  A run of lane sums, or
+    direct for its few particles per lane, rounds to 32 bits on the way: moments within TOLMIX.  With
+    densities per particle in some, which must not change the others, and joining at other cycles."""
     shapes = [(64, 48, 40, 0), (37, 29, 20, 1), (9, 7, 100, 1), (39, 1037, 3, 0), (20, 17, 2, 1), (16, 1026, 9, 1)]
     wls = [plasma(nx, nz, ppc, 40 + i, 0) for i, (nx, nz, ppc, _) in enumerate(shapes)]
     wls = [picgen.fp32_representable(picgen.with_particle_densities(wl, seed=3) if s[3] else wl)
            for wl, s in zip(wls, shapes)]
-    print(f"[gpu-case] mixed members against runs alone, labels {labels} graph {graph}", flush=True)
+    print(f"[gpu-case] mixed members and runs alone, labels {labels} graph {graph}", flush=True)
     mem, solo = ([pic.Context(wl.grid, precision=1, track_ids=labels) for wl in wls] for _ in range(2))
     for cs in (mem, solo):
         for c, wl in zip(cs, wls):
@@ -104,23 +104,23 @@ def test_mixed_member_is_the_run_alone(pic, labels, graph):  # noqa: F811
     batch.remove(mem[0])
     mem[0].step(1)
     batch.step(1)
-    for c, s, wl in zip(mem, solo, wls):
+    for c, s, wl, (nx, nz, ppc, _) in zip(mem, solo, wls, shapes):
         s.step(4)
-        same(c, s, len(wl.species), labels)
+        same(c, s, len(wl.species), labels, TOL64 if nz > 1000 else TOLMIX)
     for x in (batch, *mem, *solo):
         x.close()
 
 
-def same(a, b, nsp, labels):
+def same(a, b, nsp, labels, tol):
     ma, mb = a.read_moments(), b.read_moments()
     for p in range(ma.shape[0]):
-        assert rel(ma[p], mb[p]) <= TOL64, f"moment plane {p}: {rel(ma[p], mb[p]):.2e}"
+        assert rel(ma[p], mb[p]) <= tol, f"moment plane {p}: {rel(ma[p], mb[p]):.2e}"
     for x, y in zip(a.read_fields(), b.read_fields()):
-        assert rel(x, y) <= TOL64
+        assert rel(x, y) <= tol
     for s in range(nsp):
         pa, pb = a.read_particles(s, ids=labels), b.read_particles(s, ids=labels)
         for k in pa:
-            assert rel(pa[k], pb[k]) <= TOL64, f"species {s} {k}"
+            assert rel(pa[k], pb[k]) <= tol, f"species {s} {k}"
 
 
 @pytest.mark.parametrize("labels", [True, False])
