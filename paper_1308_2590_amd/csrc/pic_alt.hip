@@ -634,16 +634,16 @@ hipError_t launch_energy_scratch(const StepArgs &a, const double *E, const doubl
   return hipGetLastError();
 }
 
-hipError_t launch_particles_alt(const StepArgs &a, bool push, int mover, int32_t max_n,
+hipError_t launch_particles_alt(const StepArgs &a, bool push, int mover, bool sparse, int32_t max_n,
                                 hipStream_t s) {
   const unsigned nb = (unsigned)std::max<int64_t>(
       1, std::max<int64_t>((max_n + kBlock - 1) / kBlock, (a.t.ntiles + kBlock - 1) / kBlock));
   const dim3 grid(nb, (unsigned)a.nsp);
-  if (push && a.sparse)
+  if (push && sparse)
     hipLaunchKernelGGL((k_particles_alt<true, true>), grid, dim3(kBlock), 0, s, a, mover);
   else if (push)
     hipLaunchKernelGGL((k_particles_alt<true, false>), grid, dim3(kBlock), 0, s, a, mover);
-  else if (a.sparse)
+  else if (sparse)
     hipLaunchKernelGGL((k_particles_alt<false, true>), grid, dim3(kBlock), 0, s, a, mover);
   else
     hipLaunchKernelGGL((k_particles_alt<false, false>), grid, dim3(kBlock), 0, s, a, mover);

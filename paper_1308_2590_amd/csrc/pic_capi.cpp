@@ -369,6 +369,10 @@ constexpr double kRankDensePerCell = 40.0;
 constexpr double kAltSparseMaxPerCell = 5.5;
 constexpr int64_t kAltSparseMinCells = 8192;
 
+bool alt_sparse(const pic_ctx *c) {
+  return c->load.ppc <= kAltSparseMaxPerCell && c->load.cells >= kAltSparseMinCells;
+}
+
 bool rank_cells(const pic_ctx *c) {
   if (c->rank_mode == PIC_RANK_CELLS) return true;
   if (c->rank_mode == PIC_RANK_ROWS) return false;
@@ -382,7 +386,6 @@ pic::StepArgs step_args(pic_ctx *c, bool push) {
   a.mixed = mixed(c) ? 1 : 0;
   a.rank_cells = rank_cells(c) ? 1 : 0;
   a.dense = c->load.ppc >= kRankDensePerCell ? 1 : 0;
-  a.sparse = c->load.ppc <= kAltSparseMaxPerCell && c->load.cells >= kAltSparseMinCells ? 1 : 0;
   a.direct = (c->direct && !c->mover) ? 1 : 0;  // (the mover options have their own kernel)
   a.runs = c->runs ? 1 : 0;
   a.slot_codes = a.direct || a.runs ? 0 : 1;
@@ -515,7 +518,7 @@ pic_status redeposit(pic_ctx *c) {
   a.Hnew = c->H[c->hcur];
   a.M = c->M;
   if (c->mover)
-    HIP_TRY(c, pic::launch_particles_alt(a, false, c->mover, max_particles(c), c->stream), "deposit kernel");
+    HIP_TRY(c, pic::launch_particles_alt(a, false, c->mover, alt_sparse(c), max_particles(c), c->stream), "deposit kernel");
   else
     HIP_TRY(c, pic::launch_particles(a, false, c->stream), "deposit kernel");
   return PIC_OK;
@@ -532,7 +535,7 @@ pic_status particle_stage(pic_ctx *c, const pic::StepArgs &a) {
     if (c->sp[s].loaded)
       HIP_TRY(c, hipMemsetAsync(c->sp[s].cnt, 0, (size_t)pic::kMoveCodes * c->g.ncells * sizeof(int32_t),
                                 c->stream), "clear move counts");
-  HIP_TRY(c, pic::launch_particles_alt(a, true, c->mover, max_particles(c), c->stream), "particle kernel");
+  HIP_TRY(c, pic::launch_particles_alt(a, true, c->mover, alt_sparse(c), max_particles(c), c->stream), "particle kernel");
   return PIC_OK;
 }
 

@@ -429,7 +429,8 @@ __device__ __forceinline__ void fold_tile(const StepArgs &a, const Layout &Lo, c
 
 // The particles the tile's cells send to each cell of the tile and its ring, summed in LDS (arrL
 // [species][AH][AW]), added to the per-cell arrival counts: the sort's scan reads those instead of
-// gathering nine counts per cell, and (block_sums) to the sums per scan block.
+// gathering nine counts per cell, and (BLOCK_SUMS) to the sums per scan block.
+template <bool BLOCK_SUMS>
 __device__ __forceinline__ void add_arrivals(const StepArgs &a, const int *arrL, int i0, int k0) {
   const GridArgs &g = a.g;
   const int AW = a.t.tx + 2, AH = a.t.tz + 2;
@@ -452,7 +453,7 @@ __device__ __forceinline__ void add_arrivals(const StepArgs &a, const int *arrL,
     if (g.bc_x == PIC_BC_PERIODIC) gi = wrap1(gi, g.nx);
     const int cell = gk * g.nx + gi;
     if (v) atomicAdd(&sp.arr[cell], v);
-    if (a.block_sums) add_block_sums(sp.bsum, v, cell, lane);
+    if constexpr (BLOCK_SUMS) add_block_sums(sp.bsum, v, cell, lane);
   }
 }
 

@@ -85,7 +85,6 @@ struct StepArgs {
   int32_t mixed;             // 1: mixed-precision particle state and arithmetic
   int32_t rank_cells;        // 1: destinations ranked one thread per cell, 0: per tile
   int32_t dense;             // per tile: 64 lanes per cell (1) or 16 (0)
-  int32_t sparse;            // 1: the mover-option kernel's deposit for few particles per cell
   int32_t direct;            // 1: the particle kernel's direct form (few particles per cell), 0: grouped
   int32_t runs;              // 1: the mixed particle kernel of lane runs (pic_runs.h)
   int32_t slot_codes;        // 1: the particle kernel writes a byte per slot (see locode)
@@ -172,8 +171,9 @@ hipError_t launch_field_solve(const FieldArgs &a, hipStream_t s);
 hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t s);
 hipError_t launch_sort(const StepArgs &a, hipStream_t s);
 // The particle stage with mover options (PIC_MOVER_* bits), one thread per slot: max_n bounds
-// the particles of every species; the move counts must be zero on entry.
-hipError_t launch_particles_alt(const StepArgs &a, bool push, int mover, int32_t max_n,
+// the particles of every species; the move counts must be zero on entry.  sparse: the deposit for
+// few particles per cell.
+hipError_t launch_particles_alt(const StepArgs &a, bool push, int mover, bool sparse, int32_t max_n,
                                 hipStream_t s);
 // Field and kinetic energies into out[1 + nsp] (accumulated: zero it first).
 hipError_t launch_energy(const StepArgs &a, const double *E, const double *H, double *out,

@@ -1170,7 +1170,7 @@ __device__ __forceinline__ void particles_body(const StepArgs &a, int tile) {
   fold_tile<PUSH, kTileOnly>(a, Lo, acc, Ho, Hn, i0, k0, nearx, nearz);
   if constexpr (PUSH) {
     __syncthreads();  // (the count pass sums the arrivals in LDS)
-    add_arrivals(a, arrL, i0, k0);
+    add_arrivals<true>(a, arrL, i0, k0);
   }
 }
 

@@ -530,7 +530,7 @@ __device__ __forceinline__ void runs_body(const StepArgs &a, int tile) {
   fold_tile<PUSH, false>(a, Lo, acc, Ho, Hn, i0, k0, nearx, nearz);
   if constexpr (PUSH) {
     __syncthreads();
-    add_arrivals(a, arrL, i0, k0);
+    add_arrivals<false>(a, arrL, i0, k0);  // (block sums: see StepArgs::block_sums)
   }
 }
 

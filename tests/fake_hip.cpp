@@ -88,7 +88,7 @@ hipError_t launch_particles(const StepArgs &a, bool push, hipStream_t) {
   if (push) tiles_need(a, "particles");
   return hipSuccess;
 }
-hipError_t launch_particles_alt(const StepArgs &a, bool push, int, int32_t, hipStream_t) {
+hipError_t launch_particles_alt(const StepArgs &a, bool push, int, bool, int32_t, hipStream_t) {
   if (push) tiles_need(a, "particles");
   return hipSuccess;
 }
