@@ -3,8 +3,9 @@
 // is faster there (21M particles at 128 per cell: 340 against 470 us), but adds the same FP32
 // moments in FP64: the sums then differ by 1e-8, the last bits of E-bar by one rounding here and
 // there, and after 20 cycles of 21M particles some particle next to a cell's face falls on its other
-// side and takes another cell's B: single field values differ by 2e-3 of their scale from earlier
-// results, although neither is nearer to the 64-bit ones (5e-6 both).  Results of such runs are kept.
+// side and takes another cell's B: single field values differ by up to 3e-3 of their scale from
+// earlier results, although neither is nearer to the 64-bit ones (5e-6 both).  Results of such runs
+// are kept.
 #pragma once
 
 #include "pic_device.h"
