@@ -952,16 +952,25 @@ pic_status pic_set_tiles(pic_ctx *c, int32_t tile_x, int32_t tile_z) {
   for (int s = 0; s < c->S; ++s) any = any || c->sp[s].loaded;
   if (!any) return fail(c, PIC_ERR_STATE, "no particles loaded");
   const int32_t ox = c->d.tile_x, oz = c->d.tile_z;
+  // The shape that the tile list was built for: after a refusal it stays.  (Chosen again it could
+  // be another, as the particles have moved since.)
+  const pic::TileArgs tiles = c->tiles;
+  const pic::LoadShape ld = c->load;
+  const bool direct = c->direct, runs = c->runs, cells = c->rank_cells_auto;
+  const int32_t waves = c->waves;
   c->d.tile_x = tile_x;
   c->d.tile_z = tile_z;
   pic_status st = retile(c);
   if (st == PIC_OK) st = alloc_tiles(c);
   if (st != PIC_OK) {
-    const std::string msg = c->err;
     c->d.tile_x = ox;
     c->d.tile_z = oz;
-    (void)retile(c);
-    c->err = msg;
+    c->tiles = tiles;
+    c->load = ld;
+    c->direct = direct;
+    c->runs = runs;
+    c->rank_cells_auto = cells;
+    c->waves = waves;
     return st;
   }
   if ((st = build_tile_list(c)) != PIC_OK) return st;

@@ -160,3 +160,22 @@ def test_without_memory_for_more_tiles_the_old_ones_stay(fake, short_of_memory, 
     assert fake.fake_short_arrays() == short
     batch.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("how", ["memory", "too large"])
+def test_a_refused_shape_leaves_the_one_that_the_tile_list_is_for(fake, short_of_memory, how):
+    """The library's choice follows the particles, which have moved since the load (here none is
+    left after a cycle, as the kernels do not run): a refused call must not make it again."""
+    wl = picgen.with_particle_densities(plasma(256, 64, 16), seed=3)
+    ctx = binding.Context(wl.grid, precision=1 if how == "too large" else 0)
+    load(ctx, wl)
+    before = ctx.get_info()["tile"]
+    ctx.step(1)
+    if how == "memory":
+        short_of_memory.append(True)
+    with pytest.raises(binding.PicError) as e:
+        ctx.set_tiles(*((1, 1) if how == "memory" else (64, 64)))
+    assert e.value.status == (2 if how == "memory" else 1)
+    assert ctx.get_info()["tile"] == before
+    ctx.step(1)
+    ctx.close()
