@@ -108,7 +108,7 @@ pic_status rebuild(pic_batch *b) {
   int32_t waves = pic::kMaxWaves;
   for (size_t r = 0; r < n; ++r) {
     pic_ctx *c = b->runs[r];
-    if ((st = pic::tiles_fit(c)) != PIC_OK) return bfail(b, st, c->err);
+    if ((st = pic::tiles_ready(c)) != PIC_OK) return bfail(b, st, c->err);
     waves = std::min(waves, c->waves);
     direct = direct || c->direct;
     ids = ids || c->d.track_ids != 0;
@@ -266,7 +266,9 @@ pic_status pic_batch_add(pic_batch *b, pic_ctx *c) {
     c->batch = nullptr;
     c->stream = c->stream_before_batch;
     c->stream_before_batch = nullptr;
-    return bfail(b, st, c->err);
+    b->err = c->err;
+    (void)pic::batch_retile(c);  // (back to what it takes alone)
+    return st;
   }
   b->runs.push_back(c);
   b->dirty = true;

@@ -340,6 +340,7 @@ size_t lds_bytes(const pic_ctx *c) {
 void choose_tiles(pic_ctx *c, const pic::LoadShape &ld) {
   const TileChoice t = tile_choice(c, ld, c->batch != nullptr);
   c->load = ld;
+  c->tiles_listed = false;
   c->direct = t.direct;
   c->runs = t.runs;
   c->waves = t.waves;
@@ -491,6 +492,7 @@ pic_status build_tile_list(pic_ctx *c) {
   a.tile_active_next = c->tact[c->cur];
   a.tile_list_next = c->tlist[c->cur];
   HIP_TRY(c, pic::launch_tile_list(a, false, c->stream), "tile list");
+  c->tiles_listed = true;
   return PIC_OK;
 }
 
@@ -617,17 +619,20 @@ void prof_accumulate(pic_ctx *c) {
 
 namespace pic {
 
-pic_status tiles_fit(pic_ctx *c) {
-  if (c->tiles.ntiles <= c->tiles_alloc) return PIC_OK;
-  return fail(c, PIC_ERR_STATE, "no memory for the context's tiles: load its particles again");
+pic_status tiles_ready(pic_ctx *c) {
+  if (c->tiles_listed) return PIC_OK;
+  return fail(c, PIC_ERR_STATE, "the tiles of the last load could not be set up: load the particles again");
 }
 
 pic_status batch_retile(pic_ctx *c) {
   const TileArgs before = c->tiles;
+  const bool listed = c->tiles_listed;
   choose_tiles(c, LoadShape(c->load));
-  const pic_status st = tiles_fit(c);
-  if (st != PIC_OK) return st;
-  if (c->tiles.tx == before.tx && c->tiles.tz == before.tz) return PIC_OK;
+  if (listed && c->tiles.tx == before.tx && c->tiles.tz == before.tz) {
+    c->tiles_listed = true;
+    return PIC_OK;
+  }
+  if (!listed || c->tiles.ntiles > c->tiles_alloc) return tiles_ready(c);
   return build_tile_list(c);
 }
 
@@ -956,7 +961,7 @@ pic_status pic_set_tiles(pic_ctx *c, int32_t tile_x, int32_t tile_z) {
   // be another, as the particles have moved since.)
   const pic::TileArgs tiles = c->tiles;
   const pic::LoadShape ld = c->load;
-  const bool direct = c->direct, runs = c->runs, cells = c->rank_cells_auto;
+  const bool listed = c->tiles_listed, direct = c->direct, runs = c->runs, cells = c->rank_cells_auto;
   const int32_t waves = c->waves;
   c->d.tile_x = tile_x;
   c->d.tile_z = tile_z;
@@ -967,6 +972,7 @@ pic_status pic_set_tiles(pic_ctx *c, int32_t tile_x, int32_t tile_z) {
     c->d.tile_z = oz;
     c->tiles = tiles;
     c->load = ld;
+    c->tiles_listed = listed;
     c->direct = direct;
     c->runs = runs;
     c->rank_cells_auto = cells;
@@ -1002,7 +1008,7 @@ pic_status pic_step(pic_ctx *c, int32_t nsteps) {
   bool any = false;
   for (int s = 0; s < c->S; ++s) any = any || c->sp[s].loaded;
   if (!any) return fail(c, PIC_ERR_STATE, "no particles loaded");
-  const pic_status fit = pic::tiles_fit(c);
+  const pic_status fit = pic::tiles_ready(c);
   if (fit != PIC_OK) return fit;
   for (int32_t it = 0; it < nsteps; ++it) {
     ProfEvents *pe = nullptr;

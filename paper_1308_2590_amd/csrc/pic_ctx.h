@@ -90,6 +90,7 @@ struct pic_ctx {
   int32_t *tlist[2] = {};  // ordered active-tile lists, count at [ntiles]
   uint8_t *mflag = nullptr;  // deposit flags, one per kFlagNodes nodes (moments can be nonzero)
   int32_t tiles_alloc = 0;   // tiles the arrays have room for
+  bool tiles_listed = false; // tact and tlist are those of the current shape and load
   pic::LoadShape load;       // what the tile shape was chosen from
   int64_t step = 0;
   size_t lds_max = 65536;  // LDS a block may use on the context's device
@@ -119,8 +120,8 @@ namespace pic {
 // them for a cycle, and the field-solve arguments of the same cycle.
 StepArgs cycle_step_args(pic_ctx *c, int p);
 FieldArgs cycle_field_args(pic_ctx *c, int p);
-// Whether the tile arrays hold the context's tiles (not after a load without memory for them).
-pic_status tiles_fit(pic_ctx *c);
+// Whether the context's tiles are listed (not after a load without memory for them).
+pic_status tiles_ready(pic_ctx *c);
 // Tiles of a context that has joined or left a batch (c->batch), and their list in the current
 // order, queued on the context's stream.
 pic_status batch_retile(pic_ctx *c);

@@ -179,3 +179,43 @@ def test_a_refused_shape_leaves_the_one_that_the_tile_list_is_for(fake, short_of
     assert ctx.get_info()["tile"] == before
     ctx.step(1)
     ctx.close()
+
+
+@pytest.mark.parametrize("then", ["step", "add", "batched"])
+def test_a_load_without_memory_for_its_tiles_is_not_stepped(fake, then):
+    """16 x 4 cells, which a batch member takes at 12 per cell, need more than the tile arrays hold;
+    the shape that the context takes alone fits them, but they list the last load's tiles."""
+    refuse = []
+    fake.hipMalloc.argtypes = [C.POINTER(C.c_void_p), C.c_size_t]
+    fake.hipFree.argtypes = [C.c_void_p]
+
+    def alloc(nbytes, device):
+        p = C.c_void_p()
+        return 0 if nbytes in refuse or fake.hipMalloc(C.byref(p), nbytes) else p.value
+
+    binding.set_allocator(alloc, lambda ptr, nbytes, device: fake.hipFree(ptr))
+    try:
+        ctx = binding.Context(plasma(256, 256, 2).grid)
+        load(ctx, plasma(256, 256, 2))
+        assert ctx.get_info()["tile"] == (32, 4)   # 512 tiles
+        batch = binding.Batch(0, 0)
+        if then == "batched":
+            batch.add(ctx)
+        refuse += [1024, 4 * 1025]
+        with pytest.raises(binding.PicError) as e:
+            load(ctx, plasma(256, 256, 12))
+        assert e.value.status == 2
+        with pytest.raises(binding.PicError) as e:
+            batch.add(ctx) if then == "add" else batch.step(1) if then == "batched" else ctx.step(1)
+        assert e.value.status == 4
+        alone = ctx.get_info()["tile"]
+        assert (alone == (16, 4)) == (then == "batched")
+        del refuse[:]
+        ctx.load_fields(None, None)   # (deposits again, and lists the tiles)
+        assert ctx.get_info()["tile"] == alone
+        (batch if then == "batched" else ctx).step(2)
+        batch.close()
+        ctx.step(1)
+        ctx.close()
+    finally:
+        binding.set_allocator(None, None)
