@@ -148,7 +148,9 @@ pic_status pic_init_grid(const pic_grid_desc *desc, pic_ctx **out);
  * track_ids is set, particle a gets label a.  Errors: PIC_ERR_ARG (s out of range, n < 0,
  * m <= 0, q or w_uniform not finite, NULL position or momentum array with n > 0),
  * PIC_ERR_RANGE (a position outside [0, nx) x [0, nz), or a non-finite momentum or w[a]),
- * PIC_ERR_OOM.  At most 2^28 - 1 particles per species. */
+ * PIC_ERR_OOM.  At most 2^28 - 1 particles per species.  After an error in setting up the tiles
+ * (a fixed tile shape without the LDS for densities, no memory for the tile arrays) the species
+ * is loaded, but pic_step and pic_batch_* return PIC_ERR_STATE until a load succeeds. */
 pic_status pic_load_particles(pic_ctx *ctx, int32_t species, double q, double m, int64_t n,
                               const double *xi_x, const double *xi_z, const double *ux,
                               const double *uy, const double *uz, const double *w,
@@ -163,9 +165,9 @@ pic_status pic_load_fields(pic_ctx *ctx, const double *e, const double *h);
  * occupied cell).  The tiling only distributes work: results are unchanged up to the order of
  * floating-point atomic additions, in mixed precision up to the order of the FP32 partial sums
  * too.  Waits for the stream.  Errors: PIC_ERR_ARG (sizes outside
- * 1..64, or the tile's LDS accumulators would exceed the LDS a block may use on the device;
- * the old shape is kept),
- * PIC_ERR_STATE (no particles loaded). */
+ * 1..64, or the tile's LDS accumulators would exceed the LDS a block may use on the device),
+ * PIC_ERR_OOM (the tile arrays), PIC_ERR_STATE (no particles loaded).  After an error the old
+ * shape is kept. */
 pic_status pic_set_tiles(pic_ctx *ctx, int32_t tile_x, int32_t tile_z);
 
 /* Choose how the cell sort ranks the particles (the result is the same stable order either
@@ -183,7 +185,8 @@ pic_status pic_set_step(pic_ctx *ctx, int64_t step);
 
 /* Advance nsteps cycles (Sec. 3.3): field solve, gather-push-deposit, sort.  Work is queued
  * on the context's stream; the call returns without waiting.  Errors: PIC_ERR_STATE if no
- * species is loaded, PIC_ERR_ARG for nsteps < 0, PIC_ERR_DEVICE. */
+ * species is loaded or the last load could not set up its tiles, PIC_ERR_ARG for nsteps < 0,
+ * PIC_ERR_DEVICE. */
 pic_status pic_step(pic_ctx *ctx, int32_t nsteps);
 
 /* Copy the moment planes M^{k+1/2} ((12 + S) * nodes doubles) into out; len is the size of
@@ -255,7 +258,8 @@ pic_status pic_energy_noalloc(pic_ctx *ctx, double *out, int32_t len);
  * alloc(bytes, device, user) returns device memory of at least bytes bytes on the given HIP
  * device, aligned to 256 bytes, or NULL when it cannot; the library call then fails with
  * PIC_ERR_OOM (pic_init_grid returns no context, pic_load_particles leaves the species
- * without particles, pic_set_tiles keeps the old tiles).  free(ptr, bytes, device, user)
+ * without particles or, without memory for the tiles alone, a context that is not stepped,
+ * pic_set_tiles keeps the old tiles).  free(ptr, bytes, device, user)
  * releases a block with the size it was allocated with.  This is how a framework such as
  * PyTorch lends the library its caching allocator.  The library frees memory only after the
  * work queued on it has finished.  Passing NULL for both restores hipMalloc / hipFree.
